@@ -32,7 +32,7 @@
 #include <cstdint>
 #include <type_traits>
 
-#include "quan_launch.h"
+#include "qconv2d_wgrad.h"
 
 namespace quan {
 namespace {
@@ -42,25 +42,23 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// Bit 4*p + q is set when entry (p, q) of the Hamilton matrix (eq. 6) is
-// negative.  Row r: + - - -, row i: + + - +, row j: + + + -, row k: + - + +.
-constexpr unsigned kNeg = (1u << 1) | (1u << 2) | (1u << 3) | (1u << 6) | (1u << 11) | (1u << 13);
-// Bit 4*p + q is set when the separable form (eq. 7) subtracts W_q (*) x_q
-// from output component p: S[p][q] = -1.  Row r: + - - -, row i: + + + -,
-// row j: + - + +, row k: + + - +.
-constexpr unsigned kSepNeg = (1u << 1) | (1u << 2) | (1u << 3) | (1u << 7) | (1u << 9) | (1u << 14);
-
 constexpr int kThreads = 256;
-constexpr int kTileO = 64;   // output channels per work-group
-constexpr int kTileC = 64;   // input channels per work-group
-constexpr int kChunk = 32;   // pixels per staged chunk
-// LDS rows of a staged chunk: bf16 rows are 64 elements (128 bytes) with the
+constexpr int kChunk = 32;   // pixels per staged chunk (64 where four waves split the K steps)
+// LDS rows of a staged chunk: bf16 rows of 64 channels (128 bytes) have the
 // 16-byte chunks of rows 2..3 mod 4 XOR-swizzled by 4, so that neither the
 // row-wise 16-byte stores nor the transposing 8-byte reads (four rows of
-// one 64-byte column group per 16 lanes) meet in a bank; fp32 rows are
-// padded to 80 elements.
-constexpr int kRowBf16 = 64, kRowF32 = 80;
-__device__ __forceinline__ int chunk_swz(int row) { return 4 * ((row >> 1) & 1); }
+// one 64-byte column group per 16 lanes) meet in a bank; rows of 32 channels
+// (64 bytes) need no swizzle; fp32 rows are padded by 16 elements.
+template <typename T>
+constexpr int row_elems(int tile)
+{
+    return sizeof(T) == 2 ? tile : tile + 16;
+}
+template <int TILE>
+__device__ __forceinline__ int chunk_swz(int row)
+{
+    return TILE == 64 ? 4 * ((row >> 1) & 1) : 0;
+}
 
 struct WArgs {
     const void *x, *dy;
@@ -121,30 +119,32 @@ __device__ __forceinline__ u32x4 load16(const void *base, unsigned bytes, unsign
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
 
-// NC: components per pixel row as the kernel sees it.  4: the Hamilton
-// form above.  1 (layers of at most 16 channels): the whole pixel row is one
-// component of 4*C channels (a.c_out, a.c_in are then 4*C), and the kernel
-// computes the dense product G[(p,o)][(q,c)] = sum_pix dY[pix][p][o]
-// X[pix+tap][q][c] of which the reduction forms every dW_m; on a 64 x 64
-// tile this does the useful work once instead of sixteen times.
-// SEP (NC = 4): the separable form's gradients (eqs. 8-10), dW_q = sum_p
+// SEP: the separable form's gradients (eqs. 8-10), dW_q = sum_p
 // S[p][q] dY_p X_q: the same sixteen component pairs, each added into the
 // accumulator of its input component q with eq. 7's sign.
-template <typename T, bool VEC, int NC, bool SEP = false>
+// WO x WC x WK: waves over (output, input) channel blocks of 32 and over the
+// K steps of a chunk.
+template <typename T, bool VEC, bool SEP, int WO, int WC, int WK>
 __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
 {
-    static_assert(NC == 4 || NC == 1, "four components or one dense row");
-    constexpr int NM = NC == 4 ? 4 : 1;        // accumulator sets: dW_m, or G
+    static_assert(WO * WC * WK == 4, "four waves");
+    constexpr int NC = 4;                      // components per pixel row
+    constexpr int NM = 4;                      // accumulator sets: dW_m
     constexpr int ES = int(sizeof(T));
-    constexpr int kRow = ES == 2 ? kRowBf16 : kRowF32;
     constexpr int EPC = 16 / ES;               // elements per 16-byte chunk
-    constexpr int CPR = kTileO / EPC;          // chunks per (component, pixel) row of the tile
-    constexpr int PXT = kThreads / CPR;        // pixels one pass of the threads covers
-    constexpr int PASSES = kChunk / PXT;
-    constexpr int COMP = kChunk * kRow;        // elements per component block of a tensor in LDS
-    constexpr int TENSOR = NC * COMP;
-    constexpr int BUF = 2 * TENSOR;            // dY then X
-    static_assert(kTileO == kTileC && PXT * PASSES == kChunk, "tile geometry");
+    constexpr int CH = WK == 4 && ES == 2 ? 2 * kChunk : kChunk;  // pixels per chunk
+    constexpr int TW[2] = {32 * WO, 32 * WC};  // channels of the tile: dY, X
+    constexpr int CPR[2] = {TW[0] / EPC, TW[1] / EPC};  // chunks per (component, pixel) row
+    constexpr int ROW[2] = {row_elems<T>(TW[0]), row_elems<T>(TW[1])};
+    constexpr int COMP[2] = {CH * ROW[0], CH * ROW[1]};  // elements per component block in LDS
+    constexpr int XOFF = NC * COMP[0];         // X behind dY
+    constexpr int BUF = XOFF + NC * COMP[1];
+    // The 256 threads move PXT pixel rows of QT components at a time.
+    constexpr int PXT[2] = {kThreads / CPR[0] < CH ? kThreads / CPR[0] : CH, kThreads / CPR[1] < CH ? kThreads / CPR[1] : CH};
+    constexpr int QT[2] = {kThreads / (CPR[0] * PXT[0]), kThreads / (CPR[1] * PXT[1])};
+    constexpr int PASSES[2] = {CH / PXT[0], CH / PXT[1]};
+    constexpr int NQ[2] = {NC / QT[0], NC / QT[1]};
+    static_assert(PXT[0] * PASSES[0] == CH && PXT[1] * PASSES[1] == CH && QT[0] <= NC && QT[1] <= NC, "tile geometry");
     __shared__ __attribute__((aligned(16))) T lds[2 * BUF];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -160,20 +160,22 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
     const int ct = b % a.c_tiles;
     const int split = b / a.c_tiles;
     const int ky = tap / a.k_w, kx = tap - (tap / a.k_w) * a.k_w;
-    const int o0 = ot * kTileO, c0 = ct * kTileC;
+    const int o0 = ot * TW[0], c0 = ct * TW[1];
     const int64_t pix0 = int64_t(split) * a.per_split;
     int64_t pix1 = pix0 + a.per_split;
     if (pix1 > a.pixels)
         pix1 = a.pixels;
-    const int chunks = pix0 < pix1 ? int((pix1 - pix0 + kChunk - 1) / kChunk) : 0;
+    const int chunks = pix0 < pix1 ? int((pix1 - pix0 + CH - 1) / CH) : 0;
     const T *dy = static_cast<const T *>(a.dy);
     const T *x = static_cast<const T *>(a.x);
     const int hw_out = a.h_out * a.w_out;
 
-    // ---- staging: thread t moves chunk t % CPR of pixel rows t / CPR + PXT * i
-    const int cc = tid % CPR, pr = tid / CPR;
+    // ---- staging: of each tensor thread t moves chunk t % CPR of pixel row
+    // t / CPR % PXT (+ PXT per pass), components t / CPR / PXT + QT * i
+    const int cy = tid % CPR[0], py = tid / CPR[0] % PXT[0], qy = tid / CPR[0] / PXT[0];
+    const int cx = tid % CPR[1], px = tid / CPR[1] % PXT[1], qx = tid / CPR[1] / PXT[1];
     struct Staged {
-        u32x4 v[2][PASSES][NC];  // [tensor][pass][component]
+        u32x4 y[PASSES[0]][NQ[0]], x[PASSES[1]][NQ[1]];
     };
     // VEC: 16-byte buffer loads at 32-bit offsets from the slice's first
     // pixel (dY) and first image (X), zeros past a buffer's end; each pass
@@ -186,11 +188,11 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
     const unsigned dy_bytes = unsigned(int64_t(span) * NC * a.c_out * ES);
     const int64_t x_left = (int64_t(a.n) - img0) * a.h * a.w * NC * a.c_in * ES;
     const unsigned x_bytes = unsigned(x_left < 0x7fffffffLL ? x_left : 0x7fffffffLL);
-    const bool o_in = o0 + cc * EPC < a.c_out, c_in_ok = c0 + cc * EPC < a.c_in;
-    int cur_img[PASSES], cur_oy[PASSES], cur_ox[PASSES];
+    const bool o_in = o0 + cy * EPC < a.c_out, c_in_ok = c0 + cx * EPC < a.c_in;
+    int cur_img[PASSES[1]], cur_oy[PASSES[1]], cur_ox[PASSES[1]];
 #pragma unroll
-    for (int i = 0; i < PASSES; ++i) {
-        const int64_t pix = pix0 + pr + PXT * i;
+    for (int i = 0; i < PASSES[1]; ++i) {
+        const int64_t pix = pix0 + px + PXT[1] * i;
         const int64_t img = pix / hw_out;
         const int rr = int(pix - img * hw_out);
         cur_img[i] = int(img - img0);
@@ -199,33 +201,43 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
     }
     auto fetch = [&](int k, Staged &st) {
 #pragma unroll
-        for (int i = 0; i < PASSES; ++i) {
-            const int rel = k * kChunk + pr + PXT * i;  // pixel - pix0
+        for (int i = 0; i < PASSES[0]; ++i) {
+            const int rel = k * CH + py + PXT[0] * i;  // pixel - pix0
             const bool yok = rel < span;
-            const int iy = cur_oy[i] * a.s_h - a.p_h + ky * a.d_h, ix = cur_ox[i] * a.s_w - a.p_w + kx * a.d_w;
             if constexpr (VEC) {
-                const bool xok = yok && c_in_ok && unsigned(iy) < unsigned(a.h) && unsigned(ix) < unsigned(a.w);
-                const unsigned yoff = yok && o_in ? unsigned((rel * NC * a.c_out + o0 + cc * EPC) * ES) : 0x80000000u;
+                const unsigned yoff = yok && o_in ? unsigned((rel * NC * a.c_out + o0 + cy * EPC) * ES) : 0x80000000u;
+#pragma unroll
+                for (int q = 0; q < NQ[0]; ++q)
+                    st.y[i][q] = load16(dy_s, dy_bytes, yoff + unsigned((qy + QT[0] * q) * a.c_out * ES));
+            } else {
+                const T *yrow = dy_s + int64_t(yok ? rel : 0) * NC * a.c_out;
+#pragma unroll
+                for (int q = 0; q < NQ[0]; ++q)
+                    st.y[i][q] = load_chunk<T, VEC>(yrow + (qy + QT[0] * q) * a.c_out + o0, yok, cy * EPC, a.c_out - o0, dy);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < PASSES[1]; ++i) {
+            const int rel = k * CH + px + PXT[1] * i;
+            const bool in = rel < span;
+            const int iy = cur_oy[i] * a.s_h - a.p_h + ky * a.d_h, ix = cur_ox[i] * a.s_w - a.p_w + kx * a.d_w;
+            const bool xok = in && unsigned(iy) < unsigned(a.h) && unsigned(ix) < unsigned(a.w);
+            if constexpr (VEC) {
                 const unsigned xoff =
-                    xok ? unsigned((((cur_img[i] * a.h + iy) * a.w + ix) * NC * a.c_in + c0 + cc * EPC) * ES)
+                    xok && c_in_ok
+                        ? unsigned((((cur_img[i] * a.h + iy) * a.w + ix) * NC * a.c_in + c0 + cx * EPC) * ES)
                         : 0x80000000u;
 #pragma unroll
-                for (int q = 0; q < NC; ++q) {
-                    st.v[0][i][q] = load16(dy_s, dy_bytes, yoff + unsigned(q * a.c_out * ES));
-                    st.v[1][i][q] = load16(x_s, x_bytes, xoff + unsigned(q * a.c_in * ES));
-                }
+                for (int q = 0; q < NQ[1]; ++q)
+                    st.x[i][q] = load16(x_s, x_bytes, xoff + unsigned((qx + QT[1] * q) * a.c_in * ES));
             } else {
-                const bool xok = yok && iy >= 0 && iy < a.h && ix >= 0 && ix < a.w;
-                const T *yrow = dy_s + int64_t(yok ? rel : 0) * NC * a.c_out;
                 const T *xrow = x_s + ((int64_t(cur_img[i]) * a.h + (xok ? iy : 0)) * a.w + (xok ? ix : 0)) * NC * a.c_in;
 #pragma unroll
-                for (int q = 0; q < NC; ++q) {
-                    st.v[0][i][q] = load_chunk<T, VEC>(yrow + q * a.c_out + o0, yok, cc * EPC, a.c_out - o0, dy);
-                    st.v[1][i][q] = load_chunk<T, VEC>(xrow + q * a.c_in + c0, xok, cc * EPC, a.c_in - c0, x);
-                }
+                for (int q = 0; q < NQ[1]; ++q)
+                    st.x[i][q] = load_chunk<T, VEC>(xrow + (qx + QT[1] * q) * a.c_in + c0, xok, cx * EPC, a.c_in - c0, x);
             }
-            // next chunk: kChunk pixels on
-            int ox = cur_ox[i] + kChunk, oy = cur_oy[i], im = cur_img[i];
+            // next chunk: CH pixels on
+            int ox = cur_ox[i] + CH, oy = cur_oy[i], im = cur_img[i];
             while (ox >= a.w_out) {
                 ox -= a.w_out;
                 if (++oy == a.h_out) {
@@ -241,18 +253,25 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
     auto store = [&](int buf, const Staged &st) {
         T *base = lds + buf * BUF;
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int i = 0; i < PASSES[0]; ++i)
 #pragma unroll
-            for (int i = 0; i < PASSES; ++i)
+            for (int q = 0; q < NQ[0]; ++q) {
+                const int row = py + PXT[0] * i;
+                *reinterpret_cast<u32x4 *>(base + (qy + QT[0] * q) * COMP[0] + row * ROW[0] +
+                                           (ES == 2 ? (cy ^ chunk_swz<TW[0]>(row)) : cy) * EPC) = st.y[i][q];
+            }
 #pragma unroll
-                for (int q = 0; q < NC; ++q)
-                    *reinterpret_cast<u32x4 *>(base + t * TENSOR + q * COMP + (pr + PXT * i) * kRow +
-                                               (ES == 2 ? (cc ^ chunk_swz(pr + PXT * i)) : cc) * EPC) =
-                        st.v[t][i][q];
+        for (int i = 0; i < PASSES[1]; ++i)
+#pragma unroll
+            for (int q = 0; q < NQ[1]; ++q) {
+                const int row = px + PXT[1] * i;
+                *reinterpret_cast<u32x4 *>(base + XOFF + (qx + QT[1] * q) * COMP[1] + row * ROW[1] +
+                                           (ES == 2 ? (cx ^ chunk_swz<TW[1]>(row)) : cx) * EPC) = st.x[i][q];
+            }
     };
 
-    // ---- compute: wave w owns o-block w / 2 and c-block w % 2
-    const int ob = (wave >> 1) * 32, cb = (wave & 1) * 32;
+    // ---- compute: wave (wo, wc) owns an o-block and a c-block, K steps wk, wk + WK, ..
+    const int wk = wave % WK, ob = wave / (WK * WC) * 32, cb = wave / WK % WC * 32;
     f32x16 acc[NM];
 #pragma unroll
     for (int m = 0; m < NM; ++m)
@@ -263,7 +282,8 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
     // Fragment of component block `comp` of tensor t (0 dY, 1 X), channel
     // block col0, k-step ks: lane l gets channel col0 + l%32 at the pixels
     // the MFMA's operand layout assigns it.
-    auto frag = [&](const T *base, int comp, int col0, int ks) {
+    auto frag = [&](auto tile, const T *base, int comp, int col0, int ks) {
+        constexpr int TILE = decltype(tile)::value, R = row_elems<T>(TILE);
         typename Frag<T>::type f;
         if constexpr (ES == 2) {
             // two transposing reads of rows 16ks + 8(g/2) + 4r + j, columns
@@ -271,30 +291,30 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
             const int g = lane >> 4, aa = lane & 3, j = (lane & 15) >> 2;
             const int row = 16 * ks + 8 * (g >> 1) + j, col = col0 + 16 * (g & 1) + 4 * aa;
             // rows row and row + 4 share the swizzle
-            const T *p0 = base + comp * COMP + row * kRow + (((col >> 3) ^ chunk_swz(row)) << 3) + (col & 7);
+            const T *p0 = base + comp * CH * R + row * R + (((col >> 3) ^ chunk_swz<TILE>(row)) << 3) + (col & 7);
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                 (__attribute__((address_space(3))) s16x4 *)(p0));
             const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (__attribute__((address_space(3))) s16x4 *)(p0 + 4 * kRow));
+                (__attribute__((address_space(3))) s16x4 *)(p0 + 4 * R));
             s16x4 both[2] = {lo, hi};
             __builtin_memcpy(&f, both, 16);
         } else {
             // one pixel per lane: row 2ks + l/32, column col0 + l%32
-            f = base[comp * COMP + (2 * ks + (lane >> 5)) * kRow + col0 + (lane & 31)];
+            f = base[comp * CH * R + (2 * ks + (lane >> 5)) * R + col0 + (lane & 31)];
         }
         return f;
     };
-    constexpr int KSTEPS = ES == 2 ? kChunk / 16 : kChunk / 2;
+    constexpr int KSTEPS = (ES == 2 ? CH / 16 : CH / 2) / WK;  // of one wave
     typedef typename Frag<T>::type F;
     struct KFrags {
         F fy[NC], fx[NC];
     };
     auto read_k = [&](int buf, int ks, KFrags &f) {
-        const T *yb = lds + buf * BUF, *xb = yb + TENSOR;
+        const T *yb = lds + buf * BUF, *xb = yb + XOFF;
 #pragma unroll
         for (int q = 0; q < NC; ++q) {
-            f.fy[q] = frag(yb, q, ob, ks);
-            f.fx[q] = frag(xb, q, cb, ks);
+            f.fy[q] = frag(std::integral_constant<int, TW[0]>{}, yb, q, ob, ks * WK + wk);
+            f.fx[q] = frag(std::integral_constant<int, TW[1]>{}, xb, q, cb, ks * WK + wk);
         }
     };
     // sign flip of a fragment: the sign bit of every element
@@ -308,25 +328,18 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
         }
     };
     auto mfmas = [&](const KFrags &f) {
-        if constexpr (NC == 1) {
-            if constexpr (ES == 2)
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.fy[0], f.fx[0], acc[0], 0, 0, 0);
-            else
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.fy[0], f.fx[0], acc[0], 0, 0, 0);
-        } else {
 #pragma unroll
-            for (int p = 0; p < NC; ++p) {
-                const F pos = f.fy[p], neg = negate(f.fy[p]);
+        for (int p = 0; p < NC; ++p) {
+            const F pos = f.fy[p], neg = negate(f.fy[p]);
 #pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const int q = p ^ m;
-                    const int d = SEP ? q : m;  // the gradient this pair adds into
-                    const bool minus = ((SEP ? kSepNeg : kNeg) >> (4 * p + q)) & 1u;
-                    if constexpr (ES == 2)
-                        acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(minus ? neg : pos, f.fx[q], acc[d], 0, 0, 0);
-                    else
-                        acc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(minus ? neg : pos, f.fx[q], acc[d], 0, 0, 0);
-                }
+            for (int m = 0; m < 4; ++m) {
+                const int q = p ^ m;
+                const int d = SEP ? q : m;  // the gradient this pair adds into
+                const bool minus = ((SEP ? kWgradSepNeg : kWgradNeg) >> (4 * p + q)) & 1u;
+                if constexpr (ES == 2)
+                    acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(minus ? neg : pos, f.fx[q], acc[d], 0, 0, 0);
+                else
+                    acc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(minus ? neg : pos, f.fx[q], acc[d], 0, 0, 0);
             }
         }
     };
@@ -334,8 +347,6 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
     // sign flips first, then each MFMA followed by one fragment read.
     constexpr int NRD = ES == 2 ? 16 : 8;  // LDS reads of one k-step
     auto sched = [&]() {
-        if constexpr (NC == 1)
-            return;  // one MFMA per k-step: nothing to interleave
         __builtin_amdgcn_sched_group_barrier(0x002, ES == 2 ? 16 : 4, 0);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -395,6 +406,30 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
             iteration(k, sb, sa);
     }
 
+    // ---- the WK waves of a block added in wave order (through LDS)
+    if constexpr (WK > 1) {
+        float *const red = reinterpret_cast<float *>(lds);  // [wave][register][lane]
+        static_assert(sizeof(lds) >= 4 * 16 * 64 * sizeof(float), "the sums fit the LDS");
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            if (wk > 0) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    red[(wave * 16 + e) * 64 + lane] = acc[m][e];
+            }
+            __syncthreads();
+            if (wk == 0) {
+#pragma unroll
+                for (int k = 1; k < WK; ++k)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        acc[m][e] += red[((wave + k) * 16 + e) * 64 + lane];
+            }
+            __syncthreads();
+        }
+        if (wk > 0)
+            return;
+    }
     // ---- partial sums: register 4g + e of lane l is (o, c) = (ob + 8g +
     // 4(l/32) + e, cb + l%32) of the wave's block
     const int c = c0 + cb + (lane & 31);
@@ -410,61 +445,118 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
     }
 }
 
-// dW_m[o][c][ky][kx] = sum over slices of the partials, in slice order, fp64.
-// Consecutive threads take consecutive (o, c) of one (m, tap), so every
-// slice's partials are read contiguously.
-__global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce(const float *__restrict__ part, int splits, int taps,
-                                                                 int c_out, int c_in, float *__restrict__ dw0,
+// dW_m[o][c][ky][kx] = sum over slices of the partials in fp64.  A slice is
+// one run of [tap][m][o][c]; SG threads share four consecutive outputs, thread
+// s taking slices s, s + SG, ... in order (eight 16-byte loads in flight), and
+// are added in order through LDS: deterministic.
+// Bound by reading the partials.  One thread per output walking every slice
+// (the former form) kept too few loads in flight: 33.6 MB of partials (64 x
+// 64 channels, 9 taps, 57 slices) took 17.4 us, and 21.3 us for 57 slices of
+// a 16-channel layer; the latter now takes 4.0.
+template <int SG>
+__global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce(const float *__restrict__ part, int slices, int taps,
+                                                                 int oc_n, float *__restrict__ dw0,
                                                                  float *__restrict__ dw1, float *__restrict__ dw2,
                                                                  float *__restrict__ dw3)
 {
-    const int64_t oc_n = int64_t(c_out) * c_in;
-    const int64_t idx = int64_t(blockIdx.x) * kThreads + threadIdx.x;  // over [m][tap][o][c]
-    if (idx >= 4 * taps * oc_n)
-        return;
-    const int64_t oc = idx % oc_n;  // o * c_in + c
-    const int mt = int(idx / oc_n);
-    const int m = mt / taps, tap = mt - (mt / taps) * taps;
-    double s = 0.0;
-    for (int sp = 0; sp < splits; ++sp)
-        s += double(part[((int64_t(sp) * taps + tap) * 4 + m) * c_out * c_in + oc]);
-    float *dw = m == 0 ? dw0 : m == 1 ? dw1 : m == 2 ? dw2 : dw3;
-    dw[oc * taps + tap] = float(s);
+    constexpr int QUADS = kThreads / SG;  // output quads per block
+    constexpr int U = 8;
+    __shared__ double red[SG > 1 ? SG : 1][QUADS * 4];
+    const int ql = threadIdx.x % QUADS, sg = threadIdx.x / QUADS;
+    const int64_t n = int64_t(4) * taps * oc_n;  // a multiple of 4
+    const int64_t f0 = (int64_t(blockIdx.x) * QUADS + ql) * 4;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    if (f0 < n) {
+        for (int sp = sg; sp < slices; sp += SG * U) {
+            float4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int at = sp + u * SG;
+                v[u] = *reinterpret_cast<const float4 *>(part + int64_t(at < slices ? at : sp) * n + f0);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (sp + u * SG < slices) {
+                    s[0] += double(v[u].x);
+                    s[1] += double(v[u].y);
+                    s[2] += double(v[u].z);
+                    s[3] += double(v[u].w);
+                }
+        }
+    }
+    if constexpr (SG > 1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            red[sg][ql * 4 + e] = s[e];
+        __syncthreads();
+        for (int j = threadIdx.x; j < QUADS * 4; j += kThreads) {
+            double t = 0.0;
+#pragma unroll
+            for (int k = 0; k < SG; ++k)
+                t += red[k][j];
+            const int64_t f = int64_t(blockIdx.x) * QUADS * 4 + j;
+            if (f < n) {
+                const int mt = int(f / oc_n), m = mt & 3, tap = mt >> 2;
+                float *dw = m == 0 ? dw0 : m == 1 ? dw1 : m == 2 ? dw2 : dw3;
+                dw[(f - int64_t(mt) * oc_n) * taps + tap] = float(t);
+            }
+        }
+    } else if (f0 < n) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t f = f0 + e;
+            const int mt = int(f / oc_n), m = mt & 3, tap = mt >> 2;
+            float *dw = m == 0 ? dw0 : m == 1 ? dw1 : m == 2 ? dw2 : dw3;
+            dw[(f - int64_t(mt) * oc_n) * taps + tap] = float(s[e]);
+        }
+    }
 }
 
-// Layers of at most 16 channels (the kernel's NC = 1 form): the partials
-// are G[(p,o)][(q,c)] per slice and tap ([splits][taps][4*c_out][4*c_in]), and
-// dW_m[o][c][tap] = sum over slices, then over p in order, of
-// s(p, p xor m) G[(p,o)][(p xor m, c)] (eq. 6's signs), in fp64; with sep
-// (the separable form) dW_m = sum of S[p][m] G[(p,o)][(m,c)] (eq. 7's signs).
-__global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce_dense(const float *__restrict__ part, int splits,
+// Dense partials G[(p,o)][(q,c)] per slice and tap ([slices][taps][4*c_out]
+// [4*c_in]): dW_m[o][c][tap] = sum over slices and p of s(p, p xor m)
+// G[(p,o)][(p xor m, c)] (eq. 6's signs), in fp64; with sep (the separable
+// form) of S[p][m] G[(p,o)][(m,c)] (eq. 7's signs).  Sixteen threads share
+// an output, as above.
+__global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce_dense(const float *__restrict__ part, int slices,
                                                                        int taps, int c_out, int c_in, int sep,
                                                                        float *__restrict__ dw0,
                                                                        float *__restrict__ dw1,
                                                                        float *__restrict__ dw2,
                                                                        float *__restrict__ dw3)
 {
+    constexpr int SG = 16, OUTS = kThreads / SG;
+    __shared__ double red[SG][OUTS];
+    const int ol = threadIdx.x % OUTS, sg = threadIdx.x / OUTS;
     const int64_t oc_n = int64_t(c_out) * c_in;
-    const int64_t idx = int64_t(blockIdx.x) * kThreads + threadIdx.x;  // over [m][tap][o][c]
-    if (idx >= 4 * taps * oc_n)
-        return;
-    const int64_t oc = idx % oc_n;
+    const int64_t idx = int64_t(blockIdx.x) * OUTS + ol;  // over [tap][m][o][c]
+    const bool live = idx < 4 * taps * oc_n;
+    const int64_t at = live ? idx : 0;
+    const int64_t oc = at % oc_n;
     const int o = int(oc / c_in), c = int(oc - int64_t(o) * c_in);
-    const int mt = int(idx / oc_n);
-    const int m = mt / taps, tap = mt - (mt / taps) * taps;
+    const int mt = int(at / oc_n);
+    const int m = mt & 3, tap = mt >> 2;
     const int64_t g_n = int64_t(4 * c_out) * (4 * c_in);  // one slice's G of one tap
     double s = 0.0;
-    for (int sp = 0; sp < splits; ++sp) {
+#pragma unroll 2
+    for (int sp = sg; sp < slices; sp += SG) {
         const float *g = part + (int64_t(sp) * taps + tap) * g_n;
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
             const int q = sep ? m : p ^ m;
             const double v = double(g[int64_t(p * c_out + o) * (4 * c_in) + q * c_in + c]);
-            s += (((sep ? kSepNeg : kNeg) >> (4 * p + q)) & 1u) ? -v : v;
+            s += (((sep ? kWgradSepNeg : kWgradNeg) >> (4 * p + q)) & 1u) ? -v : v;
         }
     }
-    float *dw = m == 0 ? dw0 : m == 1 ? dw1 : m == 2 ? dw2 : dw3;
-    dw[oc * taps + tap] = float(s);
+    red[sg][ol] = s;
+    __syncthreads();
+    if (threadIdx.x < OUTS && live) {
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < SG; ++k)
+            t += red[k][ol];
+        float *dw = m == 0 ? dw0 : m == 1 ? dw1 : m == 2 ? dw2 : dw3;
+        dw[oc * taps + tap] = float(t);
+    }
 }
 
 // Bias gradient: column sums of the [pixels][cols = 4 * c_out] rows of dY.
@@ -568,45 +660,47 @@ __global__ __launch_bounds__(kThreads) void colsum_final(const float *__restrict
 constexpr int kBiasBlocks = 512;
 
 struct WPlan {
+    int wo, wc;  // channel blocks of 32 per tile
     int o_tiles, c_tiles, taps, splits;
     int64_t per_split;
 };
 
-// Layers whose whole pixel rows (4 * C reals) fit one tile take the dense
-// (NC = 1) form of the kernel.
-bool wgrad_dense(const ConvGeom &g)
-{
-    return 4 * g.c_out <= kTileO && 4 * g.c_in <= kTileC;
-}
-
 WPlan wgrad_plan(const ConvGeom &g)
 {
     WPlan p;
-    const int nc = wgrad_dense(g) ? 4 : 1;  // channels per kernel-side row, in units of C
-    p.o_tiles = (nc * g.c_out + kTileO - 1) / kTileO;
-    p.c_tiles = (nc * g.c_in + kTileC - 1) / kTileC;
+    // A tile of 64 channels a side, or 32 where 64 would leave a block idle
+    // (two or four waves then split a chunk's K steps): 32 -> 64 channels on
+    // 16 x 160 x 160, stride 2: 108.8 -> 65 us with half the MFMAs of the
+    // 64-wide tile gone; 32 -> 32 in fp32 on 16 x 28 x 28: 138 -> 39 us.
+    p.wo = g.c_out <= 32 || (g.c_out > 64 && g.c_out <= 96) ? 1 : 2;
+    p.wc = g.c_in <= 32 || (g.c_in > 64 && g.c_in <= 96) ? 1 : 2;
+    p.o_tiles = (g.c_out + 32 * p.wo - 1) / (32 * p.wo);
+    p.c_tiles = (g.c_in + 32 * p.wc - 1) / (32 * p.wc);
     p.taps = g.k_h * g.k_w;
     const int64_t pixels = g.m();
     const int64_t per_split_pass = int64_t(p.o_tiles) * p.c_tiles * p.taps;
     // about two work-groups per compute unit, each at least a few chunks long
     int64_t splits = (512 + per_split_pass - 1) / per_split_pass;
-    const int64_t max_splits = (pixels + 8 * kChunk - 1) / (8 * kChunk);
+    const int64_t max_splits = (pixels + 2 * kChunk - 1) / (2 * kChunk);
     if (splits > max_splits)
         splits = max_splits;
     if (splits < 1)
         splits = 1;
     p.per_split = (pixels + splits - 1) / splits;
-    p.per_split = (p.per_split + kChunk - 1) / kChunk * kChunk;
+    const int chunk = p.wo * p.wc == 1 ? 2 * kChunk : kChunk;
+    p.per_split = (p.per_split + chunk - 1) / chunk * chunk;
     p.splits = int((pixels + p.per_split - 1) / p.per_split);
     return p;
 }
 
 }  // namespace
 
-size_t qconv2d_wgrad_work_bytes(const ConvGeom &g)
+size_t qconv2d_wgrad_work_bytes(const ConvGeom &g, DType dt)
 {
-    const WPlan p = wgrad_plan(g);
-    const size_t dw_part = size_t(p.splits) * p.taps * (wgrad_dense(g) ? 16 : 4) * g.c_out * g.c_in * sizeof(float);
+    const WgradRows r = qconv2d_wgrad_rows_plan(g, dt);
+    const size_t slices = r.takes ? r.splits * r.segs : wgrad_plan(g).splits;
+    const size_t dw_part =
+        slices * g.k_h * g.k_w * (r.takes && !r.fold ? 16 : 4) * g.c_out * g.c_in * sizeof(float);
     const size_t b_part = size_t(kBiasBlocks) * 4 * g.c_out * sizeof(float);
     return dw_part > b_part ? dw_part : b_part;
 }
@@ -615,77 +709,94 @@ hipError_t qconv2d_backward_weight_run(const ConvGeom &g, DType dt, const void *
                                        float *dw_i, float *dw_j, float *dw_k, float *db, void *work,
                                        hipStream_t stream, bool sep)
 {
-    const WPlan p = wgrad_plan(g);
-    const bool dense = wgrad_dense(g);
-    WArgs a;
-    a.x = x;
-    a.dy = dy;
-    a.part = static_cast<float *>(work);
-    a.n = g.n;
-    a.c_in = dense ? 4 * g.c_in : g.c_in;  // channels of the kernel's one component
-    a.h = g.h;
-    a.w = g.w;
-    a.c_out = dense ? 4 * g.c_out : g.c_out;
-    a.k_h = g.k_h;
-    a.k_w = g.k_w;
-    a.s_h = g.s_h;
-    a.s_w = g.s_w;
-    a.p_h = g.p_h;
-    a.p_w = g.p_w;
-    a.d_h = g.d_h;
-    a.d_w = g.d_w;
-    a.h_out = g.h_out;
-    a.w_out = g.w_out;
-    a.pixels = g.m();
-    a.per_split = p.per_split;
-    a.o_tiles = p.o_tiles;
-    a.c_tiles = p.c_tiles;
-    a.taps = p.taps;
-    a.groups = p.splits * p.c_tiles * p.o_tiles;
-    const unsigned blocks = unsigned(int64_t(8) * p.taps * ((a.groups + 7) / 8));
-    const int epc = dt == DType::BF16 ? 8 : 4, es = dt == DType::BF16 ? 2 : 4;
-    // the 16-byte buffer loads take 32-bit offsets within a slice's pixels
-    // of dY and the images of X it touches
-    const int64_t hw_out = int64_t(g.h_out) * g.w_out;
-    const int64_t dy_span = p.per_split * 4 * g.c_out * es;
-    const int64_t x_span = ((p.per_split + hw_out - 1) / hw_out + 1) * g.h * g.w * 4 * g.c_in * es;
-    const bool vec = a.c_in % epc == 0 && a.c_out % epc == 0 && dy_span < 0x7fffffffLL && x_span < 0x7fffffffLL;
-    auto launch = [&](auto t, auto v, auto nc) {
-        using T = decltype(t);
-        constexpr int NC = decltype(nc)::value;
-        if (sep && NC == 4)
-            hipLaunchKernelGGL((qconv2d_wgrad<T, decltype(v)::value, NC, NC == 4>), dim3(blocks), dim3(kThreads), 0,
-                               stream, a);
-        else
-            hipLaunchKernelGGL((qconv2d_wgrad<T, decltype(v)::value, NC>), dim3(blocks), dim3(kThreads), 0, stream,
-                               a);
-    };
-    using VT = std::true_type;
-    using VF = std::false_type;
-    using N4 = std::integral_constant<int, 4>;
-    using N1 = std::integral_constant<int, 1>;
-    if (dt == DType::BF16) {
-        if (dense)
-            vec ? launch(__bf16{}, VT{}, N1{}) : launch(__bf16{}, VF{}, N1{});
-        else
-            vec ? launch(__bf16{}, VT{}, N4{}) : launch(__bf16{}, VF{}, N4{});
+    float *const part = static_cast<float *>(work);
+    const int taps = g.k_h * g.k_w;
+    const WgradRows r = qconv2d_wgrad_rows_plan(g, dt);
+    int slices = r.splits * r.segs;
+    hipError_t e;
+    if (r.takes) {
+        e = qconv2d_wgrad_rows_run(r, g, dt, x, dy, part, stream, sep);
     } else {
-        if (dense)
-            vec ? launch(float{}, VT{}, N1{}) : launch(float{}, VF{}, N1{});
+        const WPlan p = wgrad_plan(g);
+        slices = p.splits;
+        WArgs a;
+        a.x = x;
+        a.dy = dy;
+        a.part = part;
+        a.n = g.n;
+        a.c_in = g.c_in;
+        a.h = g.h;
+        a.w = g.w;
+        a.c_out = g.c_out;
+        a.k_h = g.k_h;
+        a.k_w = g.k_w;
+        a.s_h = g.s_h;
+        a.s_w = g.s_w;
+        a.p_h = g.p_h;
+        a.p_w = g.p_w;
+        a.d_h = g.d_h;
+        a.d_w = g.d_w;
+        a.h_out = g.h_out;
+        a.w_out = g.w_out;
+        a.pixels = g.m();
+        a.per_split = p.per_split;
+        a.o_tiles = p.o_tiles;
+        a.c_tiles = p.c_tiles;
+        a.taps = p.taps;
+        a.groups = p.splits * p.c_tiles * p.o_tiles;
+        const unsigned blocks = unsigned(int64_t(8) * p.taps * ((a.groups + 7) / 8));
+        const int epc = dt == DType::BF16 ? 8 : 4, es = dt == DType::BF16 ? 2 : 4;
+        // the 16-byte buffer loads take 32-bit offsets within a slice's pixels
+        // of dY and the images of X it touches
+        const int64_t hw_out = int64_t(g.h_out) * g.w_out;
+        const int64_t dy_span = p.per_split * 4 * g.c_out * es;
+        const int64_t x_span = ((p.per_split + hw_out - 1) / hw_out + 1) * g.h * g.w * 4 * g.c_in * es;
+        const bool vec = a.c_in % epc == 0 && a.c_out % epc == 0 && dy_span < 0x7fffffffLL && x_span < 0x7fffffffLL;
+        auto launch = [&](auto t, auto v, auto sp) {
+            auto tile = [&](auto wo, auto wc) {
+                constexpr int WO = decltype(wo)::value, WC = decltype(wc)::value;
+                hipLaunchKernelGGL((qconv2d_wgrad<decltype(t), decltype(v)::value, decltype(sp)::value, WO, WC,
+                                                  4 / (WO * WC)>),
+                                   dim3(blocks), dim3(kThreads), 0, stream, a);
+            };
+            using One = std::integral_constant<int, 1>;
+            using Two = std::integral_constant<int, 2>;
+            if (p.wo == 1)
+                p.wc == 1 ? tile(One{}, One{}) : tile(One{}, Two{});
+            else
+                p.wc == 1 ? tile(Two{}, One{}) : tile(Two{}, Two{});
+        };
+        using Yes = std::true_type;
+        using No = std::false_type;
+        auto form = [&](auto t, auto v) { sep ? launch(t, v, Yes{}) : launch(t, v, No{}); };
+        if (dt == DType::BF16)
+            vec ? form(__bf16{}, Yes{}) : form(__bf16{}, No{});
         else
-            vec ? launch(float{}, VT{}, N4{}) : launch(float{}, VF{}, N4{});
+            vec ? form(float{}, Yes{}) : form(float{}, No{});
+        e = hipGetLastError();
     }
-    hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    const int64_t outs = int64_t(4) * g.c_out * g.c_in * p.taps;
-    const dim3 rgrid(unsigned((outs + kThreads - 1) / kThreads));
-    if (dense)
-        hipLaunchKernelGGL(qconv2d_wgrad_reduce_dense, rgrid, dim3(kThreads), 0, stream, (const float *)a.part,
-                           p.splits, p.taps, g.c_out, g.c_in, sep ? 1 : 0, dw_r, dw_i, dw_j, dw_k);
-    else
-        hipLaunchKernelGGL(qconv2d_wgrad_reduce, rgrid, dim3(kThreads), 0, stream, (const float *)a.part, p.splits,
-                           p.taps, g.c_out, g.c_in, dw_r, dw_i, dw_j, dw_k);
+    const int64_t outs = int64_t(4) * g.c_out * g.c_in * taps;
+    if (r.takes && !r.fold) {
+        hipLaunchKernelGGL(qconv2d_wgrad_reduce_dense, dim3(unsigned((outs + 15) / 16)), dim3(kThreads), 0, stream,
+                           (const float *)part, slices, taps, g.c_out, g.c_in, sep ? 1 : 0, dw_r, dw_i, dw_j, dw_k);
+    } else {
+        // as many threads to an output as the slices keep busy
+        auto reduce = [&](auto sgc) {
+            constexpr int SG = decltype(sgc)::value;
+            const int64_t per_block = kThreads / SG * 4;
+            hipLaunchKernelGGL((qconv2d_wgrad_reduce<SG>), dim3(unsigned((outs + per_block - 1) / per_block)),
+                               dim3(kThreads), 0, stream, (const float *)part, slices, taps, g.c_out * g.c_in, dw_r,
+                               dw_i, dw_j, dw_k);
+        };
+        if (slices >= 12)
+            reduce(std::integral_constant<int, 16>{});
+        else if (slices >= 3)
+            reduce(std::integral_constant<int, 4>{});
+        else
+            reduce(std::integral_constant<int, 1>{});
+    }
     e = hipGetLastError();
     if (e != hipSuccess || db == nullptr)
         return e;
@@ -701,20 +812,20 @@ hipError_t qconv2d_backward_weight_run(const ConvGeom &g, DType dt, const void *
     if (dt == DType::BF16) {
         if (vw == 8)
             hipLaunchKernelGGL((colsum_partial<__bf16, 8>), grid, dim3(kThreads), 0, stream, (const __bf16 *)dy,
-                               pixels, cols, rpb, a.part);
+                               pixels, cols, rpb, part);
         else
             hipLaunchKernelGGL((colsum_partial<__bf16, 1>), grid, dim3(kThreads), 0, stream, (const __bf16 *)dy,
-                               pixels, cols, rpb, a.part);
+                               pixels, cols, rpb, part);
     } else {
         if (vw == 4)
             hipLaunchKernelGGL((colsum_partial<float, 4>), grid, dim3(kThreads), 0, stream, (const float *)dy,
-                               pixels, cols, rpb, a.part);
+                               pixels, cols, rpb, part);
         else
             hipLaunchKernelGGL((colsum_partial<float, 1>), grid, dim3(kThreads), 0, stream, (const float *)dy,
-                               pixels, cols, rpb, a.part);
+                               pixels, cols, rpb, part);
     }
     hipLaunchKernelGGL(colsum_final, dim3((cols + kThreads / 64 - 1) / (kThreads / 64)), dim3(kThreads), 0, stream,
-                       (const float *)a.part, nb, cols, db);
+                       (const float *)part, nb, cols, db);
     return hipGetLastError();
 }
 

@@ -788,7 +788,7 @@ int backward_weight(const char *name, bool sep, const void *x, const void *dy, i
         }
     }
     void *work = nullptr;
-    if (int rc = workspace(stream, kWgrad, quan::qconv2d_wgrad_work_bytes(g), &work))
+    if (int rc = workspace(stream, kWgrad, quan::qconv2d_wgrad_work_bytes(g, to_dt(dtype)), &work))
         return rc;
     const hipError_t e = quan::qconv2d_backward_weight_run(g, to_dt(dtype), x, dy, dw_r, dw_i, dw_j, dw_k, db, work,
                                                            static_cast<hipStream_t>(stream), sep);

@@ -143,10 +143,10 @@ hipError_t qconv2d_backward_data_run(const ConvGeom &g, DType dt, const void *dy
 // Weight and bias gradients of the Hamilton convolution for dL/dY = dy:
 // dw_r..dw_k [c_out][c_in][k_h][k_w] and db [4][c_out] (NULL: skipped), all
 // fp32; x [n][h][w][4][c_in], dy [n][h_out][w_out][4][c_out].  `work` must
-// hold qconv2d_wgrad_work_bytes(g) bytes.
+// hold qconv2d_wgrad_work_bytes(g, dt) bytes.
 // With sep, the gradients of the separable form instead (eqs. 8-10):
 // dW_q = sum_p S[p][q] sum_pix dY_p X_q (S the sign matrix of eq. 7).
-size_t qconv2d_wgrad_work_bytes(const ConvGeom &g);
+size_t qconv2d_wgrad_work_bytes(const ConvGeom &g, DType dt);
 hipError_t qconv2d_backward_weight_run(const ConvGeom &g, DType dt, const void *x, const void *dy, float *dw_r,
                                        float *dw_i, float *dw_j, float *dw_k, float *db, void *work,
                                        hipStream_t stream, bool sep = false);
