@@ -44,7 +44,16 @@ constexpr int kMaxBlocks = 512;  // partial-statistics blocks per column group (
 // blocks per column group of the element-wise passes (normalization and the
 // input gradient), which keep no partials: four work-groups per compute unit
 constexpr int kStreamBlocks = 1024;
-constexpr int kMinRowsPerThread = 24;
+// Rows per thread that a tensor is split down to: one round of the four loads
+// in flight, so that small tensors still spread over the compute units
+// (measured against 24 rows: the input-gradient pass of 131072 rows of 64 bf16
+// columns, 171 -> 1024 blocks, 19.9 -> 12.9 us, of 12544 x 128 fp32, 66 -> 392
+// blocks, 15.2 -> 6.4; the gradient reductions 15.2 -> 12.7 and 9.8 -> 5.8).  A pass that keeps partials goes
+// below kPartialRowsPerThread only while they stay under kPartialBytes, so
+// wide rows need no more scratch than they do at that many rows.
+constexpr int kMinRowsPerThread = 4;
+constexpr int kPartialRowsPerThread = 24;
+constexpr int64_t kPartialBytes = int64_t(2) << 20;
 
 template <typename T, int VW>
 struct alignas(sizeof(T) * VW) Vec {
@@ -79,7 +88,9 @@ struct Layout {
     int64_t rows_per_block;  // contiguous rows of one block
 };
 
-Layout make_layout(int64_t pixels, int c, int vw, int cap = kMaxBlocks)
+// Layout of a pass that writes partials, or (partials false) of an
+// element-wise one.
+Layout make_layout(int64_t pixels, int c, int vw, bool partials = true)
 {
     Layout l;
     l.pixels = pixels;
@@ -89,13 +100,20 @@ Layout make_layout(int64_t pixels, int c, int vw, int cap = kMaxBlocks)
     l.cg = l.chunks < kThreads ? l.chunks : kThreads;
     l.rpi = kThreads / l.cg;
     l.col_groups = (l.chunks + l.cg - 1) / l.cg;
-    const int64_t rows_per_iter_block = int64_t(l.rpi) * kMinRowsPerThread;
-    int64_t want = (pixels + rows_per_iter_block - 1) / rows_per_iter_block;
-    int max_blocks = cap;  // per column group
-    if (max_blocks < 1)
-        max_blocks = 1;
-    if (want > max_blocks)
-        want = max_blocks;
+    auto blocks_of = [&](int rows_per_thread) {
+        const int64_t rows = int64_t(l.rpi) * rows_per_thread;
+        return (pixels + rows - 1) / rows;
+    };
+    int64_t want = blocks_of(kMinRowsPerThread);
+    if (partials) {
+        const int64_t room = kPartialBytes / (int64_t(2) * l.row_len * sizeof(float));
+        const int64_t few = blocks_of(kPartialRowsPerThread);
+        want = want < room ? want : room;
+        want = want > few ? want : few;
+    }
+    const int64_t cap = partials ? kMaxBlocks : kStreamBlocks;  // per column group
+    if (want > cap)
+        want = cap;
     if (want < 1)
         want = 1;
     l.rows_per_block = (pixels + want - 1) / want;
@@ -169,6 +187,24 @@ int vec_width(int c, DType dt)
     return (4 * c) % epc == 0 ? epc : 1;
 }
 
+// Adds the threads' sums red[2][kThreads][VW] over a block's rpi row slots,
+// column by column in slot order, and hands each column's total to
+// put(sum index, column within the block, total).  One thread per (sum,
+// column), so a wave reads consecutive words and the chain is rpi reads.
+template <int VW, typename Put>
+__device__ __forceinline__ void reduce_rows(const float (&red)[2][kThreads][VW], const Layout &l, Put put)
+{
+    const int cols = l.cg * VW;
+    for (int i = threadIdx.x; i < 2 * cols; i += kThreads) {
+        const int s = i >= cols ? 1 : 0, c = i - s * cols;
+        const float *src = &red[s][0][0] + c;
+        float t = 0.0f;
+        for (int j = 0; j < l.rpi; ++j)
+            t += src[j * cols];
+        put(s, c, t);
+    }
+}
+
 template <typename T, int VW>
 __global__ __launch_bounds__(kThreads) void iqbn_stats(const T *__restrict__ x, Layout l,
                                                        float *__restrict__ part, float *__restrict__ kout)
@@ -228,37 +264,22 @@ __global__ __launch_bounds__(kThreads) void iqbn_stats(const T *__restrict__ x, 
         red[1][tid][e] = s2[e];
     }
     __syncthreads();
-    if (rl == 0 && col < l.chunks) {
-        float t1[VW], t2[VW];
+    // Partials are column-major, [2][L][blocks], for iqbn_finalize (it reads
+    // one column's partials with consecutive lanes), or, with kout given,
+    // block-major, [2][blocks][L], for iqbn_merge_affine (consecutive lanes
+    // take consecutive columns).
+    reduce_rows<VW>(red, l, [&](int s, int c, float t) {
+        const int real = blockIdx.y * l.cg * VW + c;
+        if (real < l.row_len)
+            part[size_t(s) * l.row_len * l.blocks +
+                 (kout != nullptr ? size_t(blockIdx.x) * l.row_len + real : size_t(real) * l.blocks + blockIdx.x)] = t;
+    });
+    // the shifts K, for a finalize that cannot read x's row 0 (the merged
+    // pass normalises in place)
+    if (kout != nullptr && blockIdx.x == 0 && rl == 0 && col < l.chunks)
 #pragma unroll
         for (int e = 0; e < VW; ++e)
-            t1[e] = t2[e] = 0.0f;
-        for (int j = 0; j < l.rpi; ++j) {
-#pragma unroll
-            for (int e = 0; e < VW; ++e) {
-                t1[e] += red[0][j * l.cg + cl][e];
-                t2[e] += red[1][j * l.cg + cl][e];
-            }
-        }
-        // Partials are column-major, [2][L][blocks], for iqbn_finalize (it
-        // reads one column's partials with consecutive lanes), or, with
-        // kout given, block-major, [2][blocks][L], for iqbn_merge_affine
-        // (consecutive lanes take consecutive columns).
-        const size_t stride2 = size_t(l.row_len) * l.blocks;
-#pragma unroll
-        for (int e = 0; e < VW; ++e) {
-            const size_t idx = kout != nullptr ? size_t(blockIdx.x) * l.row_len + col * VW + e
-                                               : size_t(col * VW + e) * l.blocks + blockIdx.x;
-            part[idx] = t1[e];
-            part[stride2 + idx] = t2[e];
-        }
-        // the shifts K, for a finalize that cannot read x's row 0 (the
-        // merged pass normalises in place)
-        if (kout != nullptr && blockIdx.x == 0)
-#pragma unroll
-            for (int e = 0; e < VW; ++e)
-                kout[col * VW + e] = k[e];
-    }
+            kout[col * VW + e] = k[e];
 }
 
 // One wave per column: lane i adds the partials of blocks i, i+64, ... (all
@@ -1003,6 +1024,183 @@ __global__ __launch_bounds__(kResThreads) void iqbn_resident(ResArgs a)
             emit(NV + k, held[k][t]);
 }
 
+// ---------------------------- small tensors ----------------------------
+// A tensor of few pixels takes one launch, forward or backward: a work-group
+// owns a column group (64 bytes of each row) over every pixel, keeps it in
+// registers, so it is read once, reduces it through LDS in a fixed order
+// (shifted fp32 sums per thread, fp64 across threads) and writes its result.
+// Latency bounds it: one load round, one reduction, one store round, where
+// the three-launch form pays three launches (2 x 16 x 16, 16 fp32 columns:
+// forward 9.8 -> 4.4 us, backward 12.6 -> 4.8; 59 -> 45 us of kernels and 12 ->
+// 8 launches in that layer's training step).
+constexpr int kSmallThreads = 512;
+constexpr int kSmallRows = 8;          // rows per thread at most, held in registers
+constexpr int kSmallColBytes = 64;     // bytes of a row per column group
+
+struct SmallGrid {
+    int pixels, row_len, chunks;
+    int cg, rpi;   // chunks per column group; rows per round
+    int blocks;    // column groups
+};
+
+template <typename T, int VW>
+constexpr int small_cg()
+{
+    return kSmallColBytes / (VW * int(sizeof(T)));
+}
+
+// Pixels that fit the registers of one work-group with full column groups.
+template <typename T, int VW>
+bool small_takes(int64_t pixels)
+{
+    return pixels <= int64_t(kSmallThreads / small_cg<T, VW>()) * kSmallRows;
+}
+
+template <typename T, int VW>
+SmallGrid small_grid(int64_t pixels, int c)
+{
+    SmallGrid g;
+    g.pixels = int(pixels);
+    g.row_len = 4 * c;
+    g.chunks = g.row_len / VW;
+    g.cg = g.chunks < small_cg<T, VW>() ? g.chunks : small_cg<T, VW>();
+    g.rpi = kSmallThreads / g.cg;
+    g.blocks = (g.chunks + g.cg - 1) / g.cg;
+    return g;
+}
+
+// Totals over the work-group's row slots of two per-thread sums per column:
+// in fp64, slices of the slots side by side, then the slices in order.  The
+// totals of column c (within the group) are handed to put(c, s1, s2) by one
+// thread; every thread passes a barrier after it.
+template <typename T, int VW, typename Put>
+__device__ __forceinline__ void small_reduce(const SmallGrid &g, const float (&s1)[VW], const float (&s2)[VW],
+                                             Put put)
+{
+    constexpr int MAXC = small_cg<T, VW>() * VW;  // columns of a group
+    __shared__ float red[2][kSmallThreads * VW];
+    __shared__ double slice[2][kSmallThreads];
+    const int tid = threadIdx.x, cols = g.cg * VW;
+    // thread (rl, cl) = tid / cg, tid % cg: its VW columns follow those of
+    // the thread before it, so slot rl's row of columns starts at rl * cols
+#pragma unroll
+    for (int e = 0; e < VW; ++e) {
+        red[0][tid * VW + e] = s1[e];
+        red[1][tid * VW + e] = s2[e];
+    }
+    __syncthreads();
+    static_assert(MAXC <= 32, "slices of at least 16 slots");
+    const int ns = kSmallThreads / cols;  // slices
+    const int c = tid % cols, sl = tid / cols;
+    double t1 = 0.0, t2 = 0.0;
+    if (sl < ns) {
+        for (int j = sl; j < g.rpi; j += ns) {
+            t1 += double(red[0][j * cols + c]);
+            t2 += double(red[1][j * cols + c]);
+        }
+    }
+    slice[0][tid] = t1;
+    slice[1][tid] = t2;
+    __syncthreads();
+    if (sl == 0) {
+        for (int k = 1; k < ns; ++k) {
+            t1 += slice[0][k * cols + c];
+            t2 += slice[1][k * cols + c];
+        }
+        put(c, t1, t2);
+    }
+    __syncthreads();
+}
+
+struct SmallArgs {
+    const float *gamma, *beta;
+    float eps;
+    float *mean, *var;
+};
+
+template <typename T, int VW, bool RELU>
+__global__ __launch_bounds__(kSmallThreads) void iqbn_small(const T *x, T *out, SmallGrid g, SmallArgs a)
+{
+    __shared__ float coef[3][small_cg<T, VW>() * VW];
+    const int tid = threadIdx.x;
+    const int cl = tid % g.cg, rl = tid / g.cg;
+    const int chunk = blockIdx.x * g.cg + cl;
+    const bool active = rl < g.rpi && chunk < g.chunks;
+    const T *src = x + size_t(chunk) * VW;
+    Vec<T, VW> v[kSmallRows];
+    float k[VW], s1[VW], s2[VW];
+#pragma unroll
+    for (int e = 0; e < VW; ++e)
+        s1[e] = s2[e] = k[e] = 0.0f;
+    if (active) {
+        // the shift of every column: its value in row 0
+        const Vec<T, VW> kv = *reinterpret_cast<const Vec<T, VW> *>(src);
+#pragma unroll
+        for (int u = 0; u < kSmallRows; ++u) {
+            const int r = rl + u * g.rpi;
+            if (r < g.pixels)
+                v[u] = *reinterpret_cast<const Vec<T, VW> *>(src + size_t(r) * g.row_len);
+        }
+#pragma unroll
+        for (int e = 0; e < VW; ++e)
+            k[e] = float(kv.v[e]);
+#pragma unroll
+        for (int u = 0; u < kSmallRows; ++u) {
+            if (rl + u * g.rpi < g.pixels) {
+#pragma unroll
+                for (int e = 0; e < VW; ++e) {
+                    const float d = float(v[u].v[e]) - k[e];
+                    s1[e] += d;
+                    s2[e] = fmaf(d, d, s2[e]);
+                }
+            }
+        }
+    }
+    const int col0 = blockIdx.x * g.cg * VW;
+    // (the barrier inside comes after every load of x: x may be out)
+    small_reduce<T, VW>(g, s1, s2, [&](int c, double t1, double t2) {
+        const int col = col0 + c;
+        if (col >= g.row_len)
+            return;
+        const double n = double(g.pixels);
+        const double d = t1 / n;  // mean - K
+        double vr = t2 / n - d * d;
+        if (vr < 0.0)
+            vr = 0.0;
+        const double mu = double(float(x[col])) + d;
+        coef[0][c] = float(mu);
+        coef[1][c] = float(double(a.gamma[col]) / sqrt(vr + double(a.eps)));
+        coef[2][c] = a.beta[col];
+        a.mean[col] = float(mu);
+        a.var[col] = float(vr);
+    });
+    if (!active)
+        return;
+    float mu[VW], sc[VW], be[VW];
+#pragma unroll
+    for (int e = 0; e < VW; ++e) {
+        mu[e] = coef[0][cl * VW + e];
+        sc[e] = coef[1][cl * VW + e];
+        be[e] = coef[2][cl * VW + e];
+    }
+    T *dst = out + size_t(chunk) * VW;
+#pragma unroll
+    for (int u = 0; u < kSmallRows; ++u) {
+        const int r = rl + u * g.rpi;
+        if (r < g.pixels) {
+            Vec<T, VW> o;
+#pragma unroll
+            for (int e = 0; e < VW; ++e) {
+                float y = fmaf(float(v[u].v[e]) - mu[e], sc[e], be[e]);
+                if (RELU)
+                    y = fmaxf(y, 0.0f);
+                o.v[e] = T(y);
+            }
+            *reinterpret_cast<Vec<T, VW> *>(dst + size_t(r) * g.row_len) = o;
+        }
+    }
+}
+
 // ------------------------------ backward ------------------------------
 // Gradient of training-mode IQBN (eqs. 11, 12) given the saved batch mean
 // and biased variance: per column, with s = sqrt(var + eps), xhat = (x - mean)
@@ -1014,7 +1212,12 @@ __global__ __launch_bounds__(kResThreads) void iqbn_resident(ResArgs a)
 // Pass 1 (iqbn_bwd_reduce) writes per-block partial sums of g and g xhat in
 // the statistics pass's layout, iqbn_bwd_finalize adds them in fp64 in block
 // order (deterministic) and forms the three coefficients, pass 2
-// (iqbn_bwd_apply) writes dx.  x, dout and y read twice, dx written once.
+// (iqbn_bwd_apply) writes dx.  x and dout read twice, dx written once.  Of y
+// only whether it is positive matters: pass 1 reads y and leaves one bit per
+// element (a byte per chunk of eight, `mask`, where one is given) for pass 2,
+// which saves it a third of its reads: the two passes together 72.6 -> 67.3 us
+// on 102400 x 256 bf16, 131 -> 122 on 200704 x 256 (a device copy's 5.1 TB/s
+// over the bytes moved: 47 and 122 us).
 
 template <typename T, int VW>
 __device__ __forceinline__ void load_col_params(const float *__restrict__ mean, const float *__restrict__ var,
@@ -1032,18 +1235,18 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_reduce(const T *__restrict_
                                                             const T *__restrict__ y, Layout l,
                                                             const float *__restrict__ mean,
                                                             const float *__restrict__ var, float eps,
-                                                            float *__restrict__ part)
+                                                            float *__restrict__ part,
+                                                            unsigned char *__restrict__ mask)
 {
+    const bool keep = mask != nullptr;
     __shared__ float red[2][kThreads][VW];
     const int tid = threadIdx.x;
     const int cl = tid % l.cg;
     const int rl = tid / l.cg;
     const int col = blockIdx.y * l.cg + cl;
     const bool active = rl < l.rpi && col < l.chunks;
-    const int64_t r0 = int64_t(blockIdx.x) * l.rows_per_block;
-    int64_t r1 = r0 + l.rows_per_block;
-    if (r1 > l.pixels)
-        r1 = l.pixels;
+    // (rows dealt round-robin over the blocks, as in iqbn_bwd_apply)
+    const int64_t r1 = l.pixels;
     float s1[VW], s2[VW];
 #pragma unroll
     for (int e = 0; e < VW; ++e)
@@ -1051,19 +1254,26 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_reduce(const T *__restrict_
     if (active) {
         float mu[VW], inv[VW];
         load_col_params<T, VW>(mean, var, eps, col, mu, inv);
-        const int64_t step = l.rpi;
-        auto add = [&](const Vec<T, VW> &xv, const Vec<T, VW> &gv, const Vec<T, VW> &yv) {
+        const int64_t step = int64_t(l.rpi) * l.blocks;
+        auto add = [&](const Vec<T, VW> &xv, const Vec<T, VW> &gv, const Vec<T, VW> &yv, int64_t r) {
+            unsigned bits = 0;
 #pragma unroll
             for (int e = 0; e < VW; ++e) {
                 float g = float(gv.v[e]);
-                if (RELU && !(float(yv.v[e]) > 0.0f))
-                    g = 0.0f;
+                if (RELU) {
+                    const bool on = float(yv.v[e]) > 0.0f;
+                    bits |= on ? 1u << e : 0u;
+                    g = on ? g : 0.0f;
+                }
                 const float xh = (float(xv.v[e]) - mu[e]) * inv[e];
                 s1[e] += g;
                 s2[e] = fmaf(g, xh, s2[e]);
             }
+            if constexpr (RELU && VW == 8)
+                if (keep)
+                    mask[r * l.chunks + col] = (unsigned char)bits;
         };
-        int64_t r = r0 + rl;
+        int64_t r = int64_t(blockIdx.x) * l.rpi + rl;
         // four rows in flight per thread
         for (; r + 3 * step < r1; r += 4 * step) {
             Vec<T, VW> xv[4], gv[4], yv[4];
@@ -1077,7 +1287,7 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_reduce(const T *__restrict_
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                add(xv[u], gv[u], yv[u]);
+                add(xv[u], gv[u], yv[u], r + u * step);
         }
         for (; r < r1; r += step) {
             const int64_t off = r * l.row_len + col * VW;
@@ -1085,7 +1295,7 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_reduce(const T *__restrict_
             if (RELU)
                 yv = *reinterpret_cast<const Vec<T, VW> *>(y + off);
             add(*reinterpret_cast<const Vec<T, VW> *>(x + off), *reinterpret_cast<const Vec<T, VW> *>(dout + off),
-                yv);
+                yv, r);
         }
     }
 #pragma unroll
@@ -1094,26 +1304,11 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_reduce(const T *__restrict_
         red[1][tid][e] = s2[e];
     }
     __syncthreads();
-    if (rl == 0 && col < l.chunks) {
-        float t1[VW], t2[VW];
-#pragma unroll
-        for (int e = 0; e < VW; ++e)
-            t1[e] = t2[e] = 0.0f;
-        for (int j = 0; j < l.rpi; ++j) {
-#pragma unroll
-            for (int e = 0; e < VW; ++e) {
-                t1[e] += red[0][j * l.cg + cl][e];
-                t2[e] += red[1][j * l.cg + cl][e];
-            }
-        }
-        const size_t stride2 = size_t(l.row_len) * l.blocks;
-#pragma unroll
-        for (int e = 0; e < VW; ++e) {
-            const size_t idx = size_t(col * VW + e) * l.blocks + blockIdx.x;
-            part[idx] = t1[e];
-            part[stride2 + idx] = t2[e];
-        }
-    }
+    reduce_rows<VW>(red, l, [&](int s, int c, float t) {
+        const int real = blockIdx.y * l.cg * VW + c;
+        if (real < l.row_len)
+            part[size_t(s) * l.row_len * l.blocks + size_t(real) * l.blocks + blockIdx.x] = t;
+    });
 }
 
 // One wave per column: fp64 sums of the partials (fixed order), then
@@ -1163,13 +1358,16 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_finalize(Layout l, const fl
     }
 }
 
-template <typename T, int VW, bool RELU>
+// MASK: the ReLU's sign from pass 1's bits instead of y.
+template <typename T, int VW, bool RELU, bool MASK = false>
 __global__ __launch_bounds__(kThreads) void iqbn_bwd_apply(const T *__restrict__ x, const T *__restrict__ dout,
                                                            const T *__restrict__ y, T *__restrict__ dx, Layout l,
                                                            const float *__restrict__ mean,
                                                            const float *__restrict__ var, float eps,
-                                                           const float *__restrict__ coef)
+                                                           const float *__restrict__ coef,
+                                                           const unsigned char *__restrict__ mask)
 {
+    static_assert(!MASK || (RELU && VW == 8), "one byte of bits per chunk");
     const int tid = threadIdx.x;
     const int cl = tid % l.cg;
     const int rl = tid / l.cg;
@@ -1187,16 +1385,31 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_apply(const T *__restrict__
     // Rows are dealt out round-robin (block b takes rows b*rpi .. b*rpi+rpi-1
     // of every group of blocks*rpi), so at any moment the work-groups read
     // one narrow window of each of the three or four streams: measured 48.4
-    // -> 46.0 us on 200704 x 1024 bf16 against contiguous row ranges per
+    // -> 46.0 us on 200704 x 256 bf16 without ReLU against contiguous row ranges per
     // work-group (which the two-stream passes keep: there round-robin rows
     // were 1-3 us slower).
-    const int64_t r1 = l.pixels;
-    auto grad = [&](const Vec<T, VW> &xv, const Vec<T, VW> &gv, const Vec<T, VW> &yv) {
+    // Taken from the last row down: the reduction has read the last rows most
+    // recently, so more of them are still in the last-level cache (that
+    // size: 70 -> 61 us without the sign bits, 56.5 -> 54.6 with them).
+    const int64_t r1 = l.pixels, last = r1 - 1;
+    struct Sign {
+        Vec<T, VW> y;
+        unsigned bits;
+    };
+    auto load_sign = [&](int64_t r, Sign &s) {
+        if constexpr (MASK)
+            s.bits = mask[r * l.chunks + col];
+        else if constexpr (RELU)
+            s.y = *reinterpret_cast<const Vec<T, VW> *>(y + r * l.row_len + col * VW);
+    };
+    auto grad = [&](const Vec<T, VW> &xv, const Vec<T, VW> &gv, const Sign &s) {
         Vec<T, VW> o;
 #pragma unroll
         for (int e = 0; e < VW; ++e) {
             float g = float(gv.v[e]);
-            if (RELU && !(float(yv.v[e]) > 0.0f))
+            if constexpr (MASK)
+                g = (s.bits >> e) & 1u ? g : 0.0f;
+            else if (RELU && !(float(s.y.v[e]) > 0.0f))
                 g = 0.0f;
             const float xh = (float(xv.v[e]) - mu[e]) * inv[e];
             o.v[e] = T(a[e] * (g - b1[e] - xh * b2[e]));
@@ -1208,56 +1421,154 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_apply(const T *__restrict__
     // four rows in flight per thread; each row's dx is written after its own
     // loads (dx may be dout)
     for (; r + 3 * step < r1; r += 4 * step) {
-        Vec<T, VW> xv[4], gv[4], yv[4];
+        Vec<T, VW> xv[4], gv[4];
+        Sign sv[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int64_t off = (r + u * step) * l.row_len + col * VW;
+            const int64_t off = (last - r - u * step) * l.row_len + col * VW;
             xv[u] = *reinterpret_cast<const Vec<T, VW> *>(x + off);
             gv[u] = *reinterpret_cast<const Vec<T, VW> *>(dout + off);
-            if (RELU)
-                yv[u] = *reinterpret_cast<const Vec<T, VW> *>(y + off);
+            load_sign(last - r - u * step, sv[u]);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            store_stream(reinterpret_cast<Vec<T, VW> *>(dx + (r + u * step) * l.row_len + col * VW), grad(xv[u], gv[u], yv[u]));
+            store_stream(reinterpret_cast<Vec<T, VW> *>(dx + (last - r - u * step) * l.row_len + col * VW), grad(xv[u], gv[u], sv[u]));
     }
     for (; r < r1; r += step) {
-        const int64_t off = r * l.row_len + col * VW;
-        Vec<T, VW> yv;
-        if (RELU)
-            yv = *reinterpret_cast<const Vec<T, VW> *>(y + off);
+        const int64_t off = (last - r) * l.row_len + col * VW;
+        Sign sv;
+        load_sign(last - r, sv);
         *reinterpret_cast<Vec<T, VW> *>(dx + off) =
-            grad(*reinterpret_cast<const Vec<T, VW> *>(x + off), *reinterpret_cast<const Vec<T, VW> *>(dout + off), yv);
+            grad(*reinterpret_cast<const Vec<T, VW> *>(x + off), *reinterpret_cast<const Vec<T, VW> *>(dout + off), sv);
+    }
+}
+
+struct SmallBwdArgs {
+    const float *mean, *var, *gamma;
+    float eps;
+    float *dgamma, *dbeta;
+};
+
+// The gradient of a small tensor in one launch (see iqbn_small).
+template <typename T, int VW, bool RELU>
+__global__ __launch_bounds__(kSmallThreads) void iqbn_bwd_small(const T *__restrict__ x, const T *dout,
+                                                                const T *__restrict__ y, T *dx, SmallGrid g,
+                                                                SmallBwdArgs a)
+{
+    __shared__ float coef[3][small_cg<T, VW>() * VW];
+    const int tid = threadIdx.x;
+    const int cl = tid % g.cg, rl = tid / g.cg;
+    const int chunk = blockIdx.x * g.cg + cl;
+    const bool active = rl < g.rpi && chunk < g.chunks;
+    Vec<T, VW> xv[kSmallRows], gv[kSmallRows];
+    float mu[VW], inv[VW], s1[VW], s2[VW];
+#pragma unroll
+    for (int e = 0; e < VW; ++e)
+        s1[e] = s2[e] = mu[e] = inv[e] = 0.0f;
+    if (active) {
+#pragma unroll
+        for (int u = 0; u < kSmallRows; ++u) {
+            const int r = rl + u * g.rpi;
+            if (r < g.pixels) {
+                const size_t off = size_t(r) * g.row_len + size_t(chunk) * VW;
+                xv[u] = *reinterpret_cast<const Vec<T, VW> *>(x + off);
+                gv[u] = *reinterpret_cast<const Vec<T, VW> *>(dout + off);
+                if constexpr (RELU) {
+                    const Vec<T, VW> yv = *reinterpret_cast<const Vec<T, VW> *>(y + off);
+#pragma unroll
+                    for (int e = 0; e < VW; ++e)
+                        gv[u].v[e] = float(yv.v[e]) > 0.0f ? gv[u].v[e] : T(0.0f);
+                }
+            }
+        }
+        load_col_params<T, VW>(a.mean, a.var, a.eps, chunk, mu, inv);
+#pragma unroll
+        for (int u = 0; u < kSmallRows; ++u) {
+            if (rl + u * g.rpi < g.pixels) {
+#pragma unroll
+                for (int e = 0; e < VW; ++e) {
+                    const float gr = float(gv[u].v[e]);
+                    s1[e] += gr;
+                    s2[e] = fmaf(gr, (float(xv[u].v[e]) - mu[e]) * inv[e], s2[e]);
+                }
+            }
+        }
+    }
+    const int col0 = blockIdx.x * g.cg * VW;
+    small_reduce<T, VW>(g, s1, s2, [&](int c, double t1, double t2) {
+        const int col = col0 + c;
+        if (col >= g.row_len)
+            return;
+        const double n = double(g.pixels);
+        a.dbeta[col] = float(t1);
+        a.dgamma[col] = float(t2);
+        coef[0][c] = float(double(a.gamma[col]) / sqrt(double(a.var[col]) + double(a.eps)));
+        coef[1][c] = float(t1 / n);
+        coef[2][c] = float(t2 / n);
+    });
+    if (!active)
+        return;
+#pragma unroll
+    for (int u = 0; u < kSmallRows; ++u) {
+        const int r = rl + u * g.rpi;
+        if (r < g.pixels) {
+            Vec<T, VW> o;
+#pragma unroll
+            for (int e = 0; e < VW; ++e) {
+                const int c = cl * VW + e;
+                const float xh = (float(xv[u].v[e]) - mu[e]) * inv[e];
+                o.v[e] = T(coef[0][c] * (float(gv[u].v[e]) - coef[1][c] - xh * coef[2][c]));
+            }
+            *reinterpret_cast<Vec<T, VW> *>(dx + size_t(r) * g.row_len + size_t(chunk) * VW) = o;
+        }
     }
 }
 
 template <typename T, int VW>
 hipError_t launch_backward(const void *x, const void *dout, const void *y, const float *mean, const float *var,
                            const float *gamma, float eps, void *dx, float *dgamma, float *dbeta, int64_t pixels,
-                           int c, void *work, hipStream_t stream)
+                           int c, void *work, unsigned char *mask, hipStream_t stream)
 {
+    const T *xt = static_cast<const T *>(x), *gt = static_cast<const T *>(dout), *yt = static_cast<const T *>(y);
+    if (small_takes<T, VW>(pixels)) {
+        const SmallGrid sg = small_grid<T, VW>(pixels, c);
+        const SmallBwdArgs a = {mean, var, gamma, eps, dgamma, dbeta};
+        if (y != nullptr)
+            hipLaunchKernelGGL((iqbn_bwd_small<T, VW, true>), dim3(sg.blocks), dim3(kSmallThreads), 0, stream, xt, gt,
+                               yt, static_cast<T *>(dx), sg, a);
+        else
+            hipLaunchKernelGGL((iqbn_bwd_small<T, VW, false>), dim3(sg.blocks), dim3(kSmallThreads), 0, stream, xt,
+                               gt, yt, static_cast<T *>(dx), sg, a);
+        return hipGetLastError();
+    }
     const Layout l = make_layout(pixels, c, VW);
     float *part = static_cast<float *>(work);
     float *coef = part + size_t(l.blocks) * 2 * l.row_len;
-    const T *xt = static_cast<const T *>(x), *gt = static_cast<const T *>(dout), *yt = static_cast<const T *>(y);
     const dim3 grid(l.blocks, l.col_groups);
     if (y != nullptr)
         hipLaunchKernelGGL((iqbn_bwd_reduce<T, VW, true>), grid, dim3(kThreads), 0, stream, xt, gt, yt, l, mean,
-                           var, eps, part);
+                           var, eps, part, VW == 8 ? mask : nullptr);
     else
         hipLaunchKernelGGL((iqbn_bwd_reduce<T, VW, false>), grid, dim3(kThreads), 0, stream, xt, gt, yt, l,
-                           mean, var, eps, part);
+                           mean, var, eps, part, nullptr);
     const int fin_blocks = (l.row_len + kThreads / 64 - 1) / (kThreads / 64);
     hipLaunchKernelGGL(iqbn_bwd_finalize, dim3(fin_blocks), dim3(kThreads), 0, stream, l, (const float *)part,
                        var, gamma, eps, dgamma, dbeta, coef);
-    const Layout ls = make_layout(pixels, c, VW, kStreamBlocks);
+    const Layout ls = make_layout(pixels, c, VW, false);
     const dim3 sgrid(ls.blocks, ls.col_groups);
+    if constexpr (VW == 8)
+        if (y != nullptr && mask != nullptr) {
+            hipLaunchKernelGGL((iqbn_bwd_apply<T, VW, true, true>), sgrid, dim3(kThreads), 0, stream, xt, gt, yt,
+                               static_cast<T *>(dx), ls, mean, var, eps, (const float *)coef,
+                               (const unsigned char *)mask);
+            return hipGetLastError();
+        }
     if (y != nullptr)
         hipLaunchKernelGGL((iqbn_bwd_apply<T, VW, true>), sgrid, dim3(kThreads), 0, stream, xt, gt, yt,
-                           static_cast<T *>(dx), ls, mean, var, eps, (const float *)coef);
+                           static_cast<T *>(dx), ls, mean, var, eps, (const float *)coef, nullptr);
     else
         hipLaunchKernelGGL((iqbn_bwd_apply<T, VW, false>), sgrid, dim3(kThreads), 0, stream, xt, gt, yt,
-                           static_cast<T *>(dx), ls, mean, var, eps, (const float *)coef);
+                           static_cast<T *>(dx), ls, mean, var, eps, (const float *)coef, nullptr);
     return hipGetLastError();
 }
 
@@ -1369,6 +1680,17 @@ hipError_t launch_all(const void *x, const float *gamma, const float *beta, floa
                       hipStream_t stream)
 {
     const T *xt = static_cast<const T *>(x);
+    if (small_takes<T, VW>(pixels)) {
+        const SmallGrid sg = small_grid<T, VW>(pixels, c);
+        const SmallArgs a = {gamma, beta, eps, mean, var};
+        if (relu)
+            hipLaunchKernelGGL((iqbn_small<T, VW, true>), dim3(sg.blocks), dim3(kSmallThreads), 0, stream, xt,
+                               static_cast<T *>(out), sg, a);
+        else
+            hipLaunchKernelGGL((iqbn_small<T, VW, false>), dim3(sg.blocks), dim3(kSmallThreads), 0, stream, xt,
+                               static_cast<T *>(out), sg, a);
+        return hipGetLastError();
+    }
     float *part = static_cast<float *>(work);
     if (merge_takes(pixels, c, VW, int(sizeof(T)))) {
         // two launches: statistics, then the merged finalize + normalization
@@ -1392,7 +1714,7 @@ hipError_t launch_all(const void *x, const float *gamma, const float *beta, floa
     const int fin_blocks = (l.row_len + kThreads / 64 - 1) / (kThreads / 64);
     hipLaunchKernelGGL((iqbn_finalize<T>), dim3(fin_blocks), dim3(kThreads), 0, stream, xt, l, part,
                        gamma, beta, eps, mean, var, affine);
-    const Layout ls = make_layout(pixels, c, VW, kStreamBlocks);
+    const Layout ls = make_layout(pixels, c, VW, false);
     const dim3 sgrid(ls.blocks, ls.col_groups);
     if (relu)
         hipLaunchKernelGGL((iqbn_affine<T, VW, true>), sgrid, dim3(kThreads), 0, stream, xt,
@@ -1412,7 +1734,7 @@ hipError_t launch_from_tiles(const float *part, int m_tiles, int tile_rows, cons
     hipLaunchKernelGGL(iqbn_finalize_tiles, dim3(l.row_len), dim3(kThreads), 0, stream, part, m_tiles,
                        tile_rows, pixels, l.row_len, gamma, beta, eps, mean, var, affine);
     T *t = static_cast<T *>(io);
-    const Layout ls = make_layout(pixels, c, VW, kStreamBlocks);
+    const Layout ls = make_layout(pixels, c, VW, false);
     const dim3 sgrid(ls.blocks, ls.col_groups);
     if (relu)
         hipLaunchKernelGGL((iqbn_affine<T, VW, true>), sgrid, dim3(kThreads), 0, stream, t, t, ls,
@@ -1484,15 +1806,26 @@ hipError_t iqbn_from_tiles_run(const float *part, int m_tiles, int tile_rows, co
                                        pixels, c, affine, stream);
 }
 
+namespace {
+// Whether the one-launch form of small tensors takes this one.
+bool small_tensor(int64_t pixels, int c, DType dt)
+{
+    const int vw = vec_width(c, dt);
+    if (dt == DType::BF16)
+        return vw == 8 ? small_takes<__bf16, 8>(pixels) : small_takes<__bf16, 1>(pixels);
+    return vw == 4 ? small_takes<float, 4>(pixels) : small_takes<float, 1>(pixels);
+}
+}  // namespace
+
 bool iqbn_merged(int64_t pixels, int c, DType dt)
 {
-    return merge_takes(pixels, c, vec_width(c, dt), dt == DType::BF16 ? 2 : 4);
+    return small_tensor(pixels, c, dt) || merge_takes(pixels, c, vec_width(c, dt), dt == DType::BF16 ? 2 : 4);
 }
 
 bool iqbn_one_launch(int64_t pixels, int c, DType dt)
 {
     ResPlan rp;
-    return !merge_takes(pixels, c, vec_width(c, dt), dt == DType::BF16 ? 2 : 4) && resident_plan(pixels, c, dt, &rp);
+    return !iqbn_merged(pixels, c, dt) && resident_plan(pixels, c, dt, &rp);
 }
 
 size_t iqbn_barrier_bytes()
@@ -1504,7 +1837,9 @@ size_t iqbn_workspace_bytes(int64_t pixels, int c)
 {
     // Largest over the vector widths the dispatcher may pick, and the
     // resident launch where it applies.
-    size_t best = 0;
+    // Never less than the room the partials of small tensors may take, so
+    // that a buffer sized for one tensor serves the smaller ones too.
+    size_t best = size_t(kPartialBytes) + size_t(12) * c * sizeof(float);
     ResPlan rp;
     for (DType dt : {DType::BF16, DType::F32})
         if (resident_plan(pixels, c, dt, &rp) && resident_bytes(rp, c) > best)
@@ -1525,23 +1860,28 @@ size_t iqbn_workspace_bytes(int64_t pixels, int c)
     return best;
 }
 
+size_t iqbn_mask_bytes(int64_t pixels, int c, DType dt)
+{
+    return vec_width(c, dt) == 8 && !small_tensor(pixels, c, dt) ? size_t(pixels) * (size_t(4) * c / 8) : 0;
+}
+
 hipError_t iqbn_backward_run(const void *x, const void *dout, const void *y, const float *mean, const float *var,
                              const float *gamma, float eps, void *dx, float *dgamma, float *dbeta, int64_t pixels,
-                             int c, DType dt, void *work, hipStream_t stream)
+                             int c, DType dt, void *work, unsigned char *mask, hipStream_t stream)
 {
     const int vw = vec_width(c, dt);
     if (dt == DType::BF16) {
         if (vw == 8)
             return launch_backward<__bf16, 8>(x, dout, y, mean, var, gamma, eps, dx, dgamma, dbeta, pixels, c,
-                                              work, stream);
+                                              work, mask, stream);
         return launch_backward<__bf16, 1>(x, dout, y, mean, var, gamma, eps, dx, dgamma, dbeta, pixels, c, work,
-                                          stream);
+                                          mask, stream);
     }
     if (vw == 4)
         return launch_backward<float, 4>(x, dout, y, mean, var, gamma, eps, dx, dgamma, dbeta, pixels, c, work,
-                                         stream);
+                                         mask, stream);
     return launch_backward<float, 1>(x, dout, y, mean, var, gamma, eps, dx, dgamma, dbeta, pixels, c, work,
-                                     stream);
+                                     mask, stream);
 }
 
 hipError_t iqbn_run(const void *x, const float *gamma, const float *beta, float eps, bool relu,
@@ -1550,7 +1890,7 @@ hipError_t iqbn_run(const void *x, const float *gamma, const float *beta, float 
 {
     ResPlan rp;
     const int vw = vec_width(c, dt);
-    const bool merged = merge_takes(pixels, c, vw, dt == DType::BF16 ? 2 : 4);
+    const bool merged = iqbn_merged(pixels, c, dt);
     if (!merged && flags != nullptr && resident_plan(pixels, c, dt, &rp))
         return dt == DType::BF16 ? launch_resident<__bf16>(rp, x, gamma, beta, eps, relu, out, mean, var, pixels,
                                                            c, work, flags, stream)

@@ -55,7 +55,8 @@ enum Purpose {
     kGradStage = 4,
     kWgrad = 5,
     kIqbnBarrier = 6,  // the one-launch IQBN's grid-barrier flags: zeroed once, when allocated
-    kConvClaim = 7     // the convolution's tail-block claims: zeroed once, when allocated
+    kConvClaim = 7,    // the convolution's tail-block claims: zeroed once, when allocated
+    kIqbnMask = 8      // sign bits of the saved ReLU output, IQBN gradient (optional)
 };
 
 // Returns a device buffer of at least `bytes` for (current device, stream,
@@ -97,6 +98,35 @@ int workspace(void *stream, Purpose purpose, size_t bytes, void **out, unsigned 
     if (uses != nullptr)
         *uses = ws.uses++;
     return QUAN_OK;
+}
+
+// A buffer that a call is only faster with: NULL, without an error, where it
+// cannot be had: a stream under capture whose buffer would have to grow, or
+// no memory left.  The caller then takes its form without it.
+void *optional_workspace(void *stream, Purpose purpose, size_t bytes)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess)
+        return nullptr;
+    {
+        std::lock_guard<std::mutex> lock(g_ws_mutex);
+        const auto it = g_ws.find({dev, {stream, int(purpose)}});
+        if (it != g_ws.end() && it->second.bytes >= bytes)
+            return it->second.ptr;
+    }
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capturing) != hipSuccess ||
+        capturing != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    void *p = nullptr;
+    if (workspace(stream, purpose, bytes, &p) != QUAN_OK) {
+        g_last_error.clear();
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return p;
 }
 
 // The grid-barrier flags of the one-launch IQBN on this (device, stream).
@@ -860,10 +890,14 @@ QUAN_API int quan_iqbn_backward(const void *x, const void *dout, const void *y, 
         overlaps(dbeta, sb, gamma, sb))
         return fail(QUAN_ERR_ALIAS, "iqbn_backward: dgamma/dbeta overlap each other or the statistics");
     void *work = nullptr;
+    const quan::DType dt = to_dt(dtype);
     if (int rc = workspace(stream, kIqbnPartials, quan::iqbn_workspace_bytes(pixels, c), &work))
         return rc;
-    const hipError_t e = quan::iqbn_backward_run(x, dout, y, mean, var, gamma, eps, dx, dgamma, dbeta, pixels, c,
-                                                 to_dt(dtype), work, static_cast<hipStream_t>(stream));
+    const size_t mb = y != nullptr ? quan::iqbn_mask_bytes(pixels, c, dt) : 0;
+    void *mask = mb > 0 ? optional_workspace(stream, kIqbnMask, mb) : nullptr;
+    const hipError_t e = quan::iqbn_backward_run(x, dout, y, mean, var, gamma, eps, dx, dgamma, dbeta, pixels, c, dt,
+                                                 work, static_cast<unsigned char *>(mask),
+                                                 static_cast<hipStream_t>(stream));
     if (e != hipSuccess)
         return fail_hip(e, "iqbn backward launch");
     return QUAN_OK;

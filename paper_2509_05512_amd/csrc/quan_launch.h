@@ -170,8 +170,9 @@ size_t iqbn_barrier_bytes();
 // Whether iqbn_run (given flags) normalises this tensor in one launch that
 // reads it once, on the current device.
 bool iqbn_one_launch(int64_t pixels, int c, DType dt);
-// Whether iqbn_run takes two launches with the finalize merged into the
-// normalization (small tensors with wide rows).
+// Whether iqbn_run takes one launch over whole columns (few pixels) or two
+// with the finalize merged into the normalization (small tensors with wide
+// rows).
 bool iqbn_merged(int64_t pixels, int c, DType dt);
 hipError_t iqbn_run(const void *x, const float *gamma, const float *beta, float eps, bool relu,
                     void *out, float *mean, float *var, int64_t pixels, int c, DType dt,
@@ -180,10 +181,13 @@ hipError_t iqbn_run(const void *x, const float *gamma, const float *beta, float 
 // Gradient of training-mode IQBN given the forward's saved mean and biased
 // variance ([4][c] fp32): dx (dtype dt, x's layout), dgamma, dbeta ([4][c]
 // fp32).  y (the forward output after ReLU) masks the gradient where y <= 0;
-// NULL: no ReLU.  `work` must hold iqbn_workspace_bytes(...) bytes.
+// NULL: no ReLU.  `work` must hold iqbn_workspace_bytes(...) bytes, `mask`
+// iqbn_mask_bytes(...) for the sign bits of y that spare the second pass its
+// read (NULL: y is read again).
+size_t iqbn_mask_bytes(int64_t pixels, int c, DType dt);
 hipError_t iqbn_backward_run(const void *x, const void *dout, const void *y, const float *mean, const float *var,
                              const float *gamma, float eps, void *dx, float *dgamma, float *dbeta, int64_t pixels,
-                             int c, DType dt, void *work, hipStream_t stream);
+                             int c, DType dt, void *work, unsigned char *mask, hipStream_t stream);
 
 // IQBN of a convolution output whose per-tile statistics the convolution
 // wrote (qconv2d_run with stats): `part` holds iqbn_tile_stats_bytes(m_tiles,
