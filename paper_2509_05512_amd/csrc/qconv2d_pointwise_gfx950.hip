@@ -444,6 +444,10 @@ bool qconv2d_pointwise_takes(const ConvGeom &g, DType dt)
         return false;
     if ((g.c_in != 32 && g.c_in != 64) || (g.c_out != 32 && g.c_out != 64) || g.m() < 1)
         return false;
+    // every output pixel has an input pixel (an input gradient's phase may
+    // have rows or columns past its input, which are zero)
+    if (int64_t(g.h_out - 1) * g.s_h >= g.h || int64_t(g.w_out - 1) * g.s_w >= g.w)
+        return false;
     const int64_t x_bytes = int64_t(g.n) * g.h * g.w * 8 * g.c_in;
     return x_bytes <= int64_t(0x7fffffef) && g.m() <= int64_t(0x7fffffff) - 64;
 }

@@ -198,6 +198,23 @@ def test_pointwise_backward_data(case):
     assert_close(f64(dx.cpu()), ref, BF16, f"pointwise dX {label}")
 
 
+def test_phase_larger_than_its_input():
+    """3x3 stride 2 without padding on an even width: the last input column
+    meets no window, and the one-tap phase of the input gradient that holds it
+    has one column more than dy.  Its gradient is zero, not the next row's."""
+    say("pointwise phase past its input")
+    N, C, H, W = 1, 64, 13, 10
+    rng = np.random.default_rng(403)
+    w = torch.from_numpy((rng.standard_normal((4, C, C, 3, 3)) / 48).astype(np.float32)).to(BF16)
+    dy = torch.from_numpy(rng.standard_normal((N, 4, C, 6, 4), dtype=np.float32)).to(BF16)
+    dx = quan.quan_qconv2d_backward_data(quan.to_device_layout(dy.cuda()), *[w[q].contiguous().cuda() for q in range(4)],
+                                         (H, W), stride=2)
+    torch.cuda.synchronize()
+    ref, _, _ = oracle.qconv2d_backward(np.zeros((N, 4, C, H, W)), f64(w), f64(dy), 2, 0, 1)
+    assert_close(f64(dx.cpu()), ref, BF16, "dX of a phase past its input")
+    assert not dx[..., W - 1].any()
+
+
 def test_pointwise_two_streams():
     """Two layers launched on two streams at once, each into a NaN-filled
     output, both equal to the oracle."""
