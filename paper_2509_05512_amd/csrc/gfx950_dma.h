@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "quan_launch.h"
+
 namespace quan {
 namespace {
 
@@ -47,6 +49,19 @@ __device__ __forceinline__ void wait_vmcnt()
     static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
     // vmcnt[3:0] | expcnt (7) | lgkmcnt (15) | vmcnt[5:4]
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+// Quotient by a FastDiv's divisor, and the pixel of `out` that a scattered
+// launch's pixel m goes to.
+__device__ __forceinline__ int fast_div(int n, const FastDiv &d)
+{
+    return int((unsigned long long)unsigned(n) * d.mul >> d.shift);
+}
+__device__ __forceinline__ unsigned scatter_pixel(const ScatterMap &s, int m)
+{
+    const int img = fast_div(m, s.by_hw), rem = m - img * s.hw_out;
+    const int y = fast_div(rem, s.by_w), x = rem - y * s.w_out;
+    return unsigned((img * s.h + y * s.s_h + s.r_h) * s.w + x * s.s_w + s.r_w);
 }
 
 }  // namespace

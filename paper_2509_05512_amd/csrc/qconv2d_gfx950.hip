@@ -128,6 +128,8 @@ struct KArgs {
     const float *scale;
     const float *shift;
     int relu;
+    ScatterMap scatter;  // (kEpiScatter) where each output pixel goes
+    unsigned out_bytes;  // (kEpiScatter, bf16) bytes of the images written into
 };
 
 // Work-groups a launch with tail blocks may have (the claim buffer's
@@ -215,7 +217,8 @@ __device__ __forceinline__ void interleave_kstep()
 // pixels x BN = 32*NB*WAVES_N output reals (BN/4 output channels, all four
 // components).  VEC: c_in is a multiple of the 16-byte chunk, so activations
 // move by DMA; otherwise the producer loads partial chunks element-wise.
-// EPI: what the epilogue applies (kEpiBias, kEpiStats, kEpiFold); fixed at
+// EPI: what the epilogue applies (kEpiBias, kEpiStats, kEpiFold,
+// kEpiScatter: nothing, pixels stored where KArgs::scatter says); fixed at
 // compile time so the common bias-only kernel carries none of the others'
 // state through its main loop.
 //
@@ -235,7 +238,7 @@ __device__ __forceinline__ void interleave_kstep()
 // separable form needs only W_q beside x_q, so a stage's weights are still
 // four 16-channel row groups (kernel 2*pair + g/2, channel half g%2).
 // K-step j of a stage then belongs to component 2*pair + j/2.
-enum : int { kEpiBias = 0, kEpiStats = 1, kEpiFold = 2 };
+enum : int { kEpiBias = 0, kEpiStats = 1, kEpiFold = 2, kEpiScatter = 3 };
 // Producer waves per work-group.  A tile with few MFMAs per stage (the
 // separable form, a quarter of the Hamilton MFMAs; tiles of 32 or fewer
 // output channels) runs at the pace of its activation loads, and four
@@ -321,7 +324,9 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
                   "producer_waves sees the tile geometry");
     static_assert(!ALLP || (!SEP && !PAIR && ES == 2 && MB == 1 && WAVES_N == 1),
                   "all-components waves: Hamilton form, bf16, 32 pixels per wave");
-    static_assert(FORM == kFormHamilton || (!SEP && EPI == kEpiBias), "block tables: Hamilton layouts, bias epilogue");
+    static_assert(FORM == kFormHamilton || (!SEP && (EPI == kEpiBias || EPI == kEpiScatter)),
+                  "block tables: Hamilton layouts, bias or scattering epilogue");
+    static_assert(EPI != kEpiScatter || (!SEP && !POINCARE), "input gradients scatter their pixels");
     static_assert(!POINCARE || (!VEC && !SEP && EPI == kEpiBias), "Poincare stem: element loads, bias epilogue");
     // kernel component and sign of block (output p, input q)
     auto blk_kernel = [](int p, int q) { return FORM == kFormHamilton ? (p ^ q) : p; };
@@ -339,6 +344,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
     // index modulo SWZ (their count), which spreads a wave's park stores
     // over the banks and leaves the component segments in place.
     constexpr bool DEFER = ALLP || (WAVES_M == 1 && WTN == BNC && P_UNIFORM && !SEP);
+    static_assert(EPI != kEpiScatter || ALLP || !DEFER, "the drain of one component's rows does not scatter");
     constexpr int SWZ = BNC * ES / 16;                  // chunks of one component's channels
     constexpr int OUT_ROW = (ALLP ? 4 : 1) * BNC * ES;  // bytes of one pixel in a wave's region
     constexpr int OUT_CPR = OUT_ROW / 16;               // 16-byte chunks per pixel
@@ -828,6 +834,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
     const T *d_base = nullptr;   // pending tile: first pixel's output row
     unsigned d_bytes = 0;        // bytes of output from d_base on (capped)
     unsigned d_lane = 0;         // lane's byte offset in a store, or out of range
+    int d_m = 0;                 // (kEpiScatter) lane's pixel of store 0; d_lane is then its offset in the pixel
     auto drain_read = [&](int i) {
         const int ic = i < N_DRAIN ? i : N_DRAIN - 1;
         if constexpr (ALLP) {
@@ -845,6 +852,15 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
     // stores were as fast alone but slowed the IQBN pass that reads them).
     constexpr int kStoreDeviceScope = 16;
     auto drain_store = [&](int i, u32x4 v) {
+        if constexpr (EPI == kEpiScatter) {
+            // the pixel's place in the whole images; at most 2^32 - 64 bytes
+            const int m = d_m + i * PPS;
+            const unsigned at = scatter_pixel(a.scatter, m) * unsigned(row_bytes) + d_lane;
+            __builtin_amdgcn_raw_buffer_store_b128(
+                v, make_rsrc(a.out, a.out_bytes),
+                i < N_DRAIN && d_lane != 0x80000000u && m < a.m ? at : 0xfffffff0u, 0, kStoreDeviceScope);
+            return;
+        }
         const unsigned off = (i < N_DRAIN && d_lane != 0x80000000u)
                                  ? d_lane + unsigned(i * (64 / OUT_CPR) * row_bytes)
                                  : 0x80000000u;
@@ -1342,8 +1358,11 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
         d_base = out + (size_t)mw * 4 * a.c_out;
         d_bytes = rows_left <= 0 ? 0u : rows_left < 0x7fffffffLL ? unsigned(rows_left) : 0x7fffffffu;
         const int ch = o0 + d_k * CPC;  // first channel of the lane's chunk
-        d_lane = (ch < a.c_out && (!TAIL || d_p == wm)) ? unsigned(d_pix * row_bytes + (d_p * a.c_out + ch) * ES)
-                                                        : 0x80000000u;
+        d_lane = (ch < a.c_out && (!TAIL || d_p == wm))
+                     ? unsigned((EPI == kEpiScatter ? 0 : d_pix * row_bytes) + (d_p * a.c_out + ch) * ES)
+                     : 0x80000000u;
+        if constexpr (EPI == kEpiScatter)
+            d_m = mw + d_pix;
         d_next = 0;
     };
     // ---- epilogue: bias, round, channels-last store ----
@@ -1355,7 +1374,10 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             col_affine(p * a.c_out + o + e, o + e < a.c_out, sc[e], sh[e]);
-        T *dst = out + ((size_t)m * 4 * a.c_out + p * a.c_out + o);
+        size_t pix = (size_t)m;
+        if constexpr (EPI == kEpiScatter)
+            pix = scatter_pixel(a.scatter, m);
+        T *dst = out + (pix * 4 * a.c_out + p * a.c_out + o);
         T v[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -1680,16 +1702,22 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
 // kPackSeparableGrad the four real kernels as they are.
 enum : int { kPackForward = 0, kPackHamiltonGrad = 1, kPackSeparableGrad = 2 };
 //
-// A transposed mode may pack a sub-kernel instead (one output phase of a
-// strided layer's input gradient): tap (ky, kx) of the k_h x k_w sub-kernel
-// is tap (ky0 + ky * step_h, kx0 + kx * step_w) of the full_kh x full_kw
-// transposed kernel.
+// A strided layer's input gradient runs one convolution per output phase, on
+// the taps of the transposed kernel that reach it; every tap reaches exactly
+// one phase, so all their packed kernels are one pack of the whole kernel with
+// its taps ordered phase by phase (PhaseTaps): phase i takes the taps from
+// start[i] on, tap j of them being (ky0 + (j / kw) * step_h, kx0 + (j % kw) *
+// step_w) of the transposed kernel.  The whole kernel is one phase.
+constexpr int kMaxPhases = 16;
+struct PhaseTaps {
+    int n, step_h, step_w;
+    int start[kMaxPhases], kw[kMaxPhases], ky0[kMaxPhases], kx0[kMaxPhases];
+};
 template <typename T, int MODE>
 __global__ __launch_bounds__(256) void qconv2d_pack(const T *__restrict__ w0, const T *__restrict__ w1,
                                                     const T *__restrict__ w2, const T *__restrict__ w3,
                                                     T *__restrict__ wp, int c_in, int c_out, int k_h,
-                                                    int k_w, int n_cblk, int cout_pad, int total, int ky0,
-                                                    int kx0, int step_h, int step_w, int full_kh, int full_kw)
+                                                    int k_w, int n_cblk, int cout_pad, int total, PhaseTaps pt)
 {
     constexpr int CS = stage_channels<T>();
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1705,16 +1733,24 @@ __global__ __launch_bounds__(256) void qconv2d_pack(const T *__restrict__ w0, co
     const int cblk = t % n_cblk;
     const int tap = t / n_cblk;
     const int c = cblk * CS + cc;
-    const int ky = tap / k_w, kx = tap - (tap / k_w) * k_w;
     const T *src = ws == 0 ? w0 : ws == 1 ? w1 : ws == 2 ? w2 : w3;
     T v = T(0);
     if (o < c_out && c < c_in) {
         if constexpr (MODE != kPackForward) {
-            const int kyf = ky0 + ky * step_h, kxf = kx0 + kx * step_w;
-            const T u = src[((c * c_out + o) * full_kh + (full_kh - 1 - kyf)) * full_kw + (full_kw - 1 - kxf)];
+            int start = 0, kw = pt.kw[0], ky0 = pt.ky0[0], kx0 = pt.kx0[0];
+            for (int i = 1; i < pt.n; ++i)
+                if (tap >= pt.start[i]) {
+                    start = pt.start[i];
+                    kw = pt.kw[i];
+                    ky0 = pt.ky0[i];
+                    kx0 = pt.kx0[i];
+                }
+            const int j = tap - start, jy = j / kw;
+            const int ky = ky0 + jy * pt.step_h, kx = kx0 + (j - jy * kw) * pt.step_w;
+            const T u = src[((c * c_out + o) * k_h + (k_h - 1 - ky)) * k_w + (k_w - 1 - kx)];
             v = (MODE == kPackSeparableGrad || ws == 0) ? u : T(-float(u));
         } else {
-            v = src[((o * c_in + c) * k_h + ky) * k_w + kx];
+            v = src[(o * c_in + c) * k_h * k_w + tap];
         }
     }
     wp[idx] = v;
@@ -1805,45 +1841,27 @@ __global__ __launch_bounds__(256) void qconv2d_grad_dilate(const T *__restrict__
     reinterpret_cast<Chunk *>(z)[idx] = c;
 }
 
-// The output phases of a strided layer's input gradient, computed apart:
-// phase (ry, rx) holds dX at rows ry, ry + s_h, ... and columns rx, rx + s_w,
-// ... as a dense [n][hp][wp][row] block `off` elements into the stage buffer;
-// hp == 0 marks a phase that no kernel tap reaches (its pixels are zero).
-constexpr int kMaxPhases = 16;
-struct PhaseMap {
-    int64_t off[kMaxPhases];
-    int hp[kMaxPhases], wp[kMaxPhases];
-};
-
-// Interleaves the phases into dX [n][h][w][row].  One thread per VW elements.
+// Zeros the pixels of dX [n][h][w][row] whose phase (bit (iy % s_h) * s_w +
+// ix % s_w of `zero`) no kernel tap reaches.  One thread per VW elements.
 template <typename T, int VW>
-__global__ __launch_bounds__(256) void qconv2d_grad_interleave(const T *__restrict__ stage, T *__restrict__ dx,
-                                                               PhaseMap pm, int h, int w, int s_h, int s_w,
-                                                               int row_vecs, int64_t total)
+__global__ __launch_bounds__(256) void qconv2d_grad_zero_phases(T *__restrict__ dx, unsigned zero, int h, int w,
+                                                                int s_h, int s_w, int row_vecs, int64_t total)
 {
     const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (idx >= total)
         return;
-    int64_t t = idx;
-    const int v = int(t % row_vecs);
-    t /= row_vecs;
+    const int64_t t = idx / row_vecs;
     const int ix = int(t % w);
-    t /= w;
-    const int iy = int(t % h);
-    const int64_t n = t / h;
+    const int iy = int(t / w % h);
+    if (!((zero >> ((iy % s_h) * s_w + ix % s_w)) & 1u))
+        return;
     struct alignas(sizeof(T) * VW) Chunk {
         T e[VW];
     };
     Chunk c;
-    const int ph = (iy % s_h) * s_w + ix % s_w;
-    if (pm.hp[ph] > 0) {
-        const int64_t at = ((n * pm.hp[ph] + iy / s_h) * pm.wp[ph] + ix / s_w) * row_vecs + v;
-        c = reinterpret_cast<const Chunk *>(stage + pm.off[ph])[at];
-    } else {
 #pragma unroll
-        for (int e = 0; e < VW; ++e)
-            c.e[e] = T(0);
-    }
+    for (int e = 0; e < VW; ++e)
+        c.e[e] = T(0);
     reinterpret_cast<Chunk *>(dx)[idx] = c;
 }
 
@@ -1860,8 +1878,8 @@ struct KernelEntry {
     // channel masking, 2 for paired stages (separable bf16, c_in a multiple
     // of 32), 3 for the Poincare stem (element loads of eq. 4 from colour
     // planes); NULL where the kind or variant does not apply (statistics need
-    // the deferred epilogue).
-    const void *fn[3][4];
+    // the deferred epilogue, scattered pixels are an input gradient's).
+    const void *fn[4][4];
     const char *name;
     bool allp;   // all-components waves in the Hamilton form: takes tail blocks
 };
@@ -1896,14 +1914,15 @@ constexpr const void *stem_fn()
         return (const void *)&qconv2d_igemm<T, MB, NB, WM, WN, false, kEpiBias, SEP, false, false, kFormHamilton, true>;
 }
 // the folded-IQBN epilogue serves the Hamilton form only (inference
-// convolution + IQBN); the separable form has a bias epilogue
-template <typename T, int MB, int NB, int WM, int WN, bool VEC, bool SEP>
+// convolution + IQBN), as does the scattering one (the separable form's input
+// gradient has kernels of its own); the separable form has a bias epilogue
+template <typename T, int MB, int NB, int WM, int WN, bool VEC, bool SEP, int EPI = kEpiFold>
 constexpr const void *fold_fn()
 {
     if constexpr (SEP)
         return nullptr;
     else
-        return (const void *)&qconv2d_igemm<T, MB, NB, WM, WN, VEC, kEpiFold, SEP>;
+        return (const void *)&qconv2d_igemm<T, MB, NB, WM, WN, VEC, EPI, SEP>;
 }
 #define QCONV_K(T, DT, MB, NB, WM, WN, SEP)                                                            \
     KernelEntry                                                                                        \
@@ -1917,7 +1936,9 @@ constexpr const void *fold_fn()
               nullptr, nullptr},                                                                         \
              {fold_fn<T, MB, NB, WM, WN, true, SEP>(),                                                 \
               fold_fn<T, MB, NB, WM, WN, false, SEP>(),                                                \
-              pair_fn<T, MB, NB, WM, WN, kEpiFold, SEP>(), nullptr}},                                    \
+              pair_fn<T, MB, NB, WM, WN, kEpiFold, SEP>(), nullptr},                                     \
+             {fold_fn<T, MB, NB, WM, WN, true, SEP, kEpiScatter>(),                                    \
+              fold_fn<T, MB, NB, WM, WN, false, SEP, kEpiScatter>(), nullptr, nullptr}},                \
             #T "_mb" #MB "x" #WM "_nb" #NB "x" #WN #SEP                                                \
     }
 
@@ -1938,12 +1959,15 @@ constexpr const void *fold_fn()
               nullptr, nullptr},                                                                       \
              {(const void *)&qconv2d_igemm<__bf16, 1, NB, 4, 1, true, kEpiFold, false, false, true>,    \
               (const void *)&qconv2d_igemm<__bf16, 1, NB, 4, 1, false, kEpiFold, false, false, true>,   \
+              nullptr, nullptr},                                                                       \
+             {(const void *)&qconv2d_igemm<__bf16, 1, NB, 4, 1, true, kEpiScatter, false, false, true>, \
+              (const void *)&qconv2d_igemm<__bf16, 1, NB, 4, 1, false, kEpiScatter, false, false, true>, \
               nullptr, nullptr}},                                                                      \
             "bf16_allp_nb" #NB, true                                                                   \
     }
 
 // The input gradient of the separable form (eqs. 8-10) on the Hamilton
-// layouts with the kFormSepGrad block table: bias epilogue only.
+// layouts with the kFormSepGrad block table: bias or scattering epilogue.
 #define QCONV_KG(T, DT, MB, NB, WM, WN, ALLPW)                                                         \
     KernelEntry                                                                                        \
     {                                                                                                  \
@@ -1954,7 +1978,10 @@ constexpr const void *fold_fn()
               (const void *)&qconv2d_igemm<T, MB, NB, WM, WN, false, kEpiBias, false, false, ALLPW, kFormSepGrad>, \
               nullptr, nullptr},                                                                       \
              {nullptr, nullptr, nullptr, nullptr},                                                     \
-             {nullptr, nullptr, nullptr, nullptr}},                                                    \
+             {nullptr, nullptr, nullptr, nullptr},                                                     \
+             {(const void *)&qconv2d_igemm<T, MB, NB, WM, WN, true, kEpiScatter, false, false, ALLPW, kFormSepGrad>,  \
+              (const void *)&qconv2d_igemm<T, MB, NB, WM, WN, false, kEpiScatter, false, false, ALLPW, kFormSepGrad>, \
+              nullptr, nullptr}},                                                    \
             #T "_sepgrad_mb" #MB "x" #WM "_nb" #NB "x" #WN                                             \
     }
 
@@ -2103,13 +2130,11 @@ ConvPlan qconv2d_plan(const ConvGeom &g, DType dt, ConvForm form)
 }
 
 namespace {
-// (ky0, kx0, step_h, step_w, full_kh, full_kw): the sub-kernel of a
-// transposed mode (the whole kernel: 0, 0, 1, 1, k_h, k_w)
+// phases: the tap order of a transposed mode (NULL: the whole kernel's)
 template <int MODE>
 hipError_t pack_weights(const PackGeom &pg, int c_in, int c_out, int k_h, int k_w, DType dt, const void *w_r,
                         const void *w_i, const void *w_j, const void *w_k, void *wpack, hipStream_t stream,
-                        int ky0 = 0, int kx0 = 0, int step_h = 1, int step_w = 1, int full_kh = 0,
-                        int full_kw = 0)
+                        const PhaseTaps *phases = nullptr)
 {
     const int total = int(pg.bytes / (dt == DType::BF16 ? 2 : 4));
     const int blocks = (total + 255) / 256;
@@ -2129,20 +2154,23 @@ hipError_t pack_weights(const PackGeom &pg, int c_in, int c_out, int k_h, int k_
                                c_out, pg.n_cblk, pg.cout_pad, threads);
         return hipGetLastError();
     }
-    if (full_kh == 0) {
-        full_kh = k_h;
-        full_kw = k_w;
+    PhaseTaps pt = {};
+    if (phases != nullptr) {
+        pt = *phases;
+    } else {
+        pt.n = pt.step_h = pt.step_w = 1;
+        pt.kw[0] = k_w;
     }
     if (dt == DType::BF16)
         hipLaunchKernelGGL((qconv2d_pack<__bf16, MODE>), dim3(blocks), dim3(256), 0, stream,
                            (const __bf16 *)w_r, (const __bf16 *)w_i, (const __bf16 *)w_j,
                            (const __bf16 *)w_k, (__bf16 *)wpack, c_in, c_out, k_h, k_w, pg.n_cblk,
-                           pg.cout_pad, total, ky0, kx0, step_h, step_w, full_kh, full_kw);
+                           pg.cout_pad, total, pt);
     else
         hipLaunchKernelGGL((qconv2d_pack<float, MODE>), dim3(blocks), dim3(256), 0, stream,
                            (const float *)w_r, (const float *)w_i, (const float *)w_j,
                            (const float *)w_k, (float *)wpack, c_in, c_out, k_h, k_w, pg.n_cblk,
-                           pg.cout_pad, total, ky0, kx0, step_h, step_w, full_kh, full_kw);
+                           pg.cout_pad, total, pt);
     return hipGetLastError();
 }
 }  // namespace
@@ -2174,17 +2202,21 @@ ConvGeom qconv2d_grad_data_geom(const ConvGeom &g)
     return t;
 }
 
+namespace {
+// Whether the strided input gradient runs phase by phase.
+bool by_phases(const ConvGeom &g)
+{
+    return (g.s_h != 1 || g.s_w != 1) && g.d_h == 1 && g.d_w == 1 && g.s_h * g.s_w <= kMaxPhases;
+}
+}  // namespace
+
 size_t qconv2d_grad_data_stage_bytes(const ConvGeom &g, DType dt)
 {
-    if (g.s_h == 1 && g.s_w == 1)
+    if ((g.s_h == 1 && g.s_w == 1) || by_phases(g))
         return 0;
+    // the zero-inserted gradient
     const ConvGeom t = qconv2d_grad_data_geom(g);
-    const size_t es = dt == DType::BF16 ? 2 : 4;
-    // the zero-inserted gradient (dilated layers), or the output phases (dX's size)
-    const size_t z = size_t(t.n) * t.h * t.w * 4 * t.c_in * es;
-    // (each phase starts on a 16-byte boundary)
-    const size_t phases = size_t(g.n) * g.h * g.w * 4 * g.c_in * es + size_t(16) * kMaxPhases;
-    return z > phases ? z : phases;
+    return size_t(t.n) * t.h * t.w * 4 * t.c_in * (dt == DType::BF16 ? 2 : 4);
 }
 
 namespace {
@@ -2210,79 +2242,88 @@ AxisPhase axis_phase(int k, int p, int s, int in, int r)
 
 // The strided input gradient as s_h x s_w stride-1 convolutions of dY, one
 // per output phase (only the taps that reach it: the MFMA work of the layer
-// once, where the zero-inserted gradient does it s_h * s_w times), then one
-// pass that interleaves the phases into dX.
+// once, where the zero-inserted gradient does it s_h * s_w times), each of
+// which writes its pixels in their places in dX.  One launch packs every
+// phase's kernel.  Measured on 16 x 160 x 160, 32 -> 64, 3x3 stride 2, bf16:
+// a pass that interleaved dense phases into dX took 45.6 us, the phases' four
+// packs and the unused whole one 24 us, and the convolutions 126 us where
+// they now take MEAS_P (a phase's pixel is 256 contiguous bytes, whole lines).
 hipError_t backward_data_phases(const ConvGeom &g, DType dt, const void *dy, const void *w_r, const void *w_i,
-                                const void *w_j, const void *w_k, void *dx, void *wpack, void *stage,
-                                hipStream_t stream, bool sep, ConvClaim *claim)
+                                const void *w_j, const void *w_k, void *dx, void *wpack, hipStream_t stream,
+                                bool sep, ConvClaim *claim)
 {
-    const size_t es = dt == DType::BF16 ? 2 : 4;
-    const int row = 4 * g.c_in;
-    PhaseMap pm;
-    int64_t off = 0;          // elements into the stage buffer
-    size_t wp_off = 0;        // bytes into the packed-weight buffer
+    const ConvGeom whole = qconv2d_grad_data_geom(g);
+    const PackGeom pg = qconv2d_pack_geom(whole.c_in, whole.c_out, whole.k_h, whole.k_w, dt);
+    PhaseTaps pt = {};
+    pt.step_h = g.s_h;
+    pt.step_w = g.s_w;
+    unsigned zero = 0;  // phases without taps
+    int taps = 0;
     for (int ry = 0; ry < g.s_h; ++ry)
         for (int rx = 0; rx < g.s_w; ++rx) {
-            const int ph = ry * g.s_w + rx;
             const AxisPhase ay = axis_phase(g.k_h, g.p_h, g.s_h, g.h, ry);
             const AxisPhase ax = axis_phase(g.k_w, g.p_w, g.s_w, g.w, rx);
-            pm.off[ph] = off;
-            pm.hp[ph] = pm.wp[ph] = 0;
-            if (ay.size == 0 || ax.size == 0 || ay.taps == 0 || ax.taps == 0)
-                continue;  // no pixels, or no tap reaches them: zeros
-            ConvGeom t;
-            t.n = g.n;
-            t.c_in = g.c_out;
-            t.c_out = g.c_in;
+            if (ay.taps == 0 || ax.taps == 0) {
+                zero |= 1u << (ry * g.s_w + rx);
+                continue;
+            }
+            pt.start[pt.n] = taps;
+            pt.kw[pt.n] = ax.taps;
+            pt.ky0[pt.n] = ay.u0;
+            pt.kx0[pt.n] = ax.u0;
+            ++pt.n;
+            taps += ay.taps * ax.taps;
+        }
+    const auto pack = sep ? pack_weights<kPackSeparableGrad> : pack_weights<kPackHamiltonGrad>;
+    hipError_t e = pack(pg, whole.c_in, whole.c_out, g.k_h, g.k_w, dt, w_r, w_i, w_j, w_k, wpack, stream, &pt);
+    if (e != hipSuccess)
+        return e;
+    const size_t tap_bytes = pg.bytes / (size_t(g.k_h) * g.k_w);
+    int i = 0;
+    for (int ry = 0; ry < g.s_h; ++ry)
+        for (int rx = 0; rx < g.s_w; ++rx) {
+            if ((zero >> (ry * g.s_w + rx)) & 1u)
+                continue;
+            const void *wp = static_cast<unsigned char *>(wpack) + size_t(pt.start[i++]) * tap_bytes;
+            const AxisPhase ay = axis_phase(g.k_h, g.p_h, g.s_h, g.h, ry);
+            const AxisPhase ax = axis_phase(g.k_w, g.p_w, g.s_w, g.w, rx);
+            if (ay.size == 0 || ax.size == 0)
+                continue;  // no pixels
+            ConvGeom t = whole;
             t.k_h = ay.taps;
             t.k_w = ax.taps;
-            t.s_h = t.s_w = 1;
-            t.d_h = t.d_w = 1;
             t.p_h = ay.pad;
             t.p_w = ax.pad;
             t.h = g.h_out;
             t.w = g.w_out;
             t.h_out = ay.size;
             t.w_out = ax.size;
-            const PackGeom pg = qconv2d_pack_geom(t.c_in, t.c_out, t.k_h, t.k_w, dt);
-            void *wp = static_cast<unsigned char *>(wpack) + wp_off;
-            hipError_t e = sep ? pack_weights<kPackSeparableGrad>(pg, t.c_in, t.c_out, t.k_h, t.k_w, dt, w_r, w_i,
-                                                                   w_j, w_k, wp, stream, ay.u0, ax.u0, g.s_h, g.s_w,
-                                                                   g.k_h, g.k_w)
-                               : pack_weights<kPackHamiltonGrad>(pg, t.c_in, t.c_out, t.k_h, t.k_w, dt, w_r, w_i,
-                                                                  w_j, w_k, wp, stream, ay.u0, ax.u0, g.s_h, g.s_w,
-                                                                  g.k_h, g.k_w);
+            const ConvScatter to = {g.h, g.w, g.s_h, g.s_w, ry, rx};
+            e = qconv2d_run(qconv2d_plan(t, dt, sep ? ConvForm::SeparableGradData : ConvForm::Hamilton),
+                            qconv2d_pack_geom(t.c_in, t.c_out, t.k_h, t.k_w, dt), t, dt, dy, wp, nullptr, dx, nullptr,
+                            nullptr, stream, false, claim, &to);
             if (e != hipSuccess)
                 return e;
-            e = qconv2d_run(qconv2d_plan(t, dt, sep ? ConvForm::SeparableGradData : ConvForm::Hamilton), pg, t, dt,
-                            dy, wp, nullptr, static_cast<unsigned char *>(stage) + size_t(off) * es, nullptr,
-                            nullptr, stream, false, claim);
-            if (e != hipSuccess)
-                return e;
-            pm.hp[ph] = ay.size;
-            pm.wp[ph] = ax.size;
-            // the next phase starts on a 16-byte boundary
-            off += int64_t(g.n) * ay.size * ax.size * row;
-            off = (off * int64_t(es) + 15) / 16 * 16 / int64_t(es);
-            wp_off += pg.bytes;
         }
+    if (zero == 0)
+        return hipSuccess;
+    const int row = 4 * g.c_in;
     const int vw = row % (dt == DType::BF16 ? 8 : 4) == 0 ? (dt == DType::BF16 ? 8 : 4) : 1;
     const int64_t total = int64_t(g.n) * g.h * g.w * (row / vw);
-    const unsigned blocks = unsigned((total + 255) / 256);
+    const dim3 blocks(unsigned((total + 255) / 256));
+    auto clear = [&](auto kernel, auto *to) {
+        hipLaunchKernelGGL(kernel, blocks, dim3(256), 0, stream, to, zero, g.h, g.w, g.s_h, g.s_w, row / vw, total);
+    };
     if (dt == DType::BF16) {
         if (vw == 8)
-            hipLaunchKernelGGL((qconv2d_grad_interleave<__bf16, 8>), dim3(blocks), dim3(256), 0, stream,
-                               (const __bf16 *)stage, (__bf16 *)dx, pm, g.h, g.w, g.s_h, g.s_w, row / vw, total);
+            clear(qconv2d_grad_zero_phases<__bf16, 8>, static_cast<__bf16 *>(dx));
         else
-            hipLaunchKernelGGL((qconv2d_grad_interleave<__bf16, 1>), dim3(blocks), dim3(256), 0, stream,
-                               (const __bf16 *)stage, (__bf16 *)dx, pm, g.h, g.w, g.s_h, g.s_w, row, total);
+            clear(qconv2d_grad_zero_phases<__bf16, 1>, static_cast<__bf16 *>(dx));
     } else {
         if (vw == 4)
-            hipLaunchKernelGGL((qconv2d_grad_interleave<float, 4>), dim3(blocks), dim3(256), 0, stream,
-                               (const float *)stage, (float *)dx, pm, g.h, g.w, g.s_h, g.s_w, row / vw, total);
+            clear(qconv2d_grad_zero_phases<float, 4>, static_cast<float *>(dx));
         else
-            hipLaunchKernelGGL((qconv2d_grad_interleave<float, 1>), dim3(blocks), dim3(256), 0, stream,
-                               (const float *)stage, (float *)dx, pm, g.h, g.w, g.s_h, g.s_w, row, total);
+            clear(qconv2d_grad_zero_phases<float, 1>, static_cast<float *>(dx));
     }
     return hipGetLastError();
 }
@@ -2295,6 +2336,8 @@ hipError_t qconv2d_backward_data_run(const ConvGeom &g, DType dt, const void *dy
     const ConvGeom t = qconv2d_grad_data_geom(g);
     if (t.p_h < 0 || t.p_w < 0 || t.h < 1 || t.w < 1)
         return hipErrorInvalidValue;
+    if (by_phases(g))
+        return backward_data_phases(g, dt, dy, w_r, w_i, w_j, w_k, dx, wpack, stream, sep, claim);
     const PackGeom pg = qconv2d_pack_geom(t.c_in, t.c_out, t.k_h, t.k_w, dt);
     hipError_t e = sep ? pack_weights<kPackSeparableGrad>(pg, t.c_in, t.c_out, t.k_h, t.k_w, dt, w_r, w_i, w_j, w_k,
                                                           wpack, stream)
@@ -2302,8 +2345,6 @@ hipError_t qconv2d_backward_data_run(const ConvGeom &g, DType dt, const void *dy
                                                          wpack, stream);
     if (e != hipSuccess)
         return e;
-    if ((g.s_h != 1 || g.s_w != 1) && g.d_h == 1 && g.d_w == 1 && g.s_h * g.s_w <= kMaxPhases)
-        return backward_data_phases(g, dt, dy, w_r, w_i, w_j, w_k, dx, wpack, stage, stream, sep, claim);
     const void *z = dy;
     if (g.s_h != 1 || g.s_w != 1) {
         const int row = 4 * g.c_out;
@@ -2356,13 +2397,14 @@ size_t qconv2d_claim_bytes()
 
 hipError_t qconv2d_run(const ConvPlan &plan, const PackGeom &pg, const ConvGeom &g, DType dt,
                        const void *x, const void *wpack, const void *bias, void *out,
-                       float *stats, const ConvFold *fold, hipStream_t stream, bool poincare, ConvClaim *claim)
+                       float *stats, const ConvFold *fold, hipStream_t stream, bool poincare, ConvClaim *claim,
+                       const ConvScatter *scatter)
 {
     if (plan.pointwise) {
         if (poincare)
             return hipErrorInvalidValue;
         return qconv2d_pointwise_run(g, pg, plan.group_stages, x, wpack, bias, out, stats, plan.stat_tiles, fold,
-                                     stream);
+                                     stream, scatter);
     }
     if (plan.id < 0 || plan.id >= kNumKernels)
         return hipErrorInvalidValue;
@@ -2408,7 +2450,16 @@ hipError_t qconv2d_run(const ConvPlan &plan, const PackGeom &pg, const ConvGeom 
     if (fold != nullptr && (fold->scale == nullptr || fold->shift == nullptr))
         return hipErrorInvalidValue;
     void *args[] = {&a};
-    const int epi = stats != nullptr ? kEpiStats : fold != nullptr ? kEpiFold : kEpiBias;
+    if (scatter != nullptr) {
+        if (stats != nullptr || fold != nullptr || bias != nullptr)
+            return hipErrorInvalidValue;
+        a.scatter = ScatterMap(*scatter, g.h_out, g.w_out);
+        a.out_bytes = unsigned(int64_t(g.n) * scatter->h * scatter->w * 4 * g.c_out * es);  // (used in bf16: fits)
+    }
+    const int epi = scatter != nullptr ? kEpiScatter
+                    : stats != nullptr ? kEpiStats
+                    : fold != nullptr  ? kEpiFold
+                                       : kEpiBias;
     const bool paired = k.fn[epi][2] != nullptr && g.c_in % 32 == 0;
     if (poincare && (g.c_in != 1 || epi != kEpiBias))
         return hipErrorInvalidValue;

@@ -43,7 +43,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kPwEpiBias = 0, kPwEpiStats = 1, kPwEpiFold = 2;
+constexpr int kPwEpiBias = 0, kPwEpiStats = 1, kPwEpiFold = 2, kPwEpiScatter = 3;
 constexpr int kPwComputeWaves = 4, kPwProducerWaves = 2, kPwStoreWaves = 2;
 constexpr int kPwThreads = 64 * (kPwComputeWaves + kPwProducerWaves + kPwStoreWaves);
 constexpr int kPwStagePixels = 32;
@@ -68,6 +68,8 @@ struct PwArgs {
     const float *scale;  // [4 c_out] (EPI fold)
     const float *shift;
     int relu;
+    ScatterMap scatter;  // (EPI scatter)
+    unsigned out_bytes;  // (EPI scatter) bytes of the images written into
 };
 
 // XOR swizzle of the 16-byte chunk index in an LDS row of CPR chunks, as a
@@ -226,6 +228,24 @@ __global__ __launch_bounds__(kPwThreads) void qconv2d_pointwise(PwArgs a)
                     v[c][it] = *reinterpret_cast<const u32x4 *>(region + (CPS * sw + c) * PARK + jj * PRB +
                                                                 16 * (cc ^ pw_swz<PCPR>(jj)));
                 }
+            }
+            if constexpr (EPI == kPwEpiScatter) {
+                // each pixel's row goes to its place in the whole images
+                const __amdgpu_buffer_rsrc_t dst = make_rsrc(outb, a.out_bytes);
+#pragma unroll
+                for (int c = 0; c < CPS; ++c) {
+#pragma unroll
+                    for (int it = 0; it < DRAIN; ++it) {
+                        const int byte = 1024 * it + 16 * lane;
+                        const int jj = byte / PRB, cc = (byte % PRB) / 16;
+                        const int m = m0 + jj;
+                        const unsigned at = scatter_pixel(a.scatter, m) * unsigned(OUT_ROW);
+                        __builtin_amdgcn_raw_buffer_store_b128(
+                            v[c][it], dst, m < a.m ? at + unsigned((CPS * sw + c) * PRB + 16 * cc) : 0xfffffff0u, 0,
+                            kPwStorePolicy);
+                    }
+                }
+                continue;
             }
             // buffer stores over the stage's valid rows: rows past M fall
             // outside the range and are dropped
@@ -431,6 +451,8 @@ const void *pw_kernel(int epi)
         return (const void *)&qconv2d_pointwise<CIN, COUT, kPwEpiStats>;
     case kPwEpiFold:
         return (const void *)&qconv2d_pointwise<CIN, COUT, kPwEpiFold>;
+    case kPwEpiScatter:
+        return (const void *)&qconv2d_pointwise<CIN, COUT, kPwEpiScatter>;
     default:
         return (const void *)&qconv2d_pointwise<CIN, COUT, kPwEpiBias>;
     }
@@ -466,9 +488,11 @@ int qconv2d_pointwise_stage_pixels()
 
 hipError_t qconv2d_pointwise_run(const ConvGeom &g, const PackGeom &pg, int group_stages, const void *x,
                                  const void *wpack, const void *bias, void *out, float *stats, int stat_tiles,
-                                 const ConvFold *fold, hipStream_t stream)
+                                 const ConvFold *fold, hipStream_t stream, const ConvScatter *scatter)
 {
     if (!qconv2d_pointwise_takes(g, DType::BF16) || group_stages < 1 || pg.pk != 16)
+        return hipErrorInvalidValue;
+    if (scatter != nullptr && (stats != nullptr || fold != nullptr || bias != nullptr))
         return hipErrorInvalidValue;
     PwArgs a;
     a.x = x;
@@ -496,7 +520,14 @@ hipError_t qconv2d_pointwise_run(const ConvGeom &g, const PackGeom &pg, int grou
         return hipErrorInvalidValue;
     if (fold != nullptr && (fold->scale == nullptr || fold->shift == nullptr))
         return hipErrorInvalidValue;
-    const int epi = stats != nullptr ? kPwEpiStats : fold != nullptr ? kPwEpiFold : kPwEpiBias;
+    if (scatter != nullptr) {
+        a.scatter = ScatterMap(*scatter, g.h_out, g.w_out);
+        a.out_bytes = unsigned(int64_t(g.n) * scatter->h * scatter->w * 8 * g.c_out);
+    }
+    const int epi = scatter != nullptr ? kPwEpiScatter
+                    : stats != nullptr ? kPwEpiStats
+                    : fold != nullptr  ? kPwEpiFold
+                                       : kPwEpiBias;
     const void *fn = g.c_in == 64 ? (g.c_out == 64 ? pw_kernel<64, 64>(epi) : pw_kernel<64, 32>(epi))
                                   : (g.c_out == 64 ? pw_kernel<32, 64>(epi) : pw_kernel<32, 32>(epi));
     void *args[] = {&a};

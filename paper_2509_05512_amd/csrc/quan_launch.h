@@ -86,6 +86,42 @@ struct ConvFold {
 // as the convolution loads them.
 bool qconv2d_writes_stats(const ConvPlan &plan, const ConvGeom &g, DType dt);
 //
+// With `scatter` non-NULL (no bias, statistics or fold) output pixel (n, y,
+// x) goes to pixel (n, y * s_h + r_h, x * s_w + r_w) of images of h x w in
+// `out`: one output phase of a strided layer's input gradient, written in
+// place.
+struct ConvScatter {
+    int h, w, s_h, s_w, r_h, r_w;
+};
+// Exact quotients of 0 <= n < 2^31 by a fixed divisor d >= 1, as one 64-bit
+// product: with 2^(s-1) < d <= 2^s, mul = floor(2^(31+s) / d) + 1 fits 32 bits
+// and exceeds 2^(31+s) / d by at most 2^s / d of a unit.
+struct FastDiv {
+    unsigned mul = 0;
+    int shift = 31;
+    FastDiv() = default;
+    explicit FastDiv(int d)
+    {
+        int s = 0;
+        while ((1LL << s) < d)
+            ++s;
+        mul = unsigned((1ULL << (31 + s)) / unsigned(d) + 1);
+        shift = 31 + s;
+    }
+};
+// The kernels' form of a ConvScatter: pixel m of the launch.
+struct ScatterMap {
+    int hw_out, w_out;      // of the launch
+    int h, w, s_h, s_w, r_h, r_w;
+    FastDiv by_hw, by_w;
+    ScatterMap() = default;
+    ScatterMap(const ConvScatter &c, int h_out, int w_out_)
+        : hw_out(h_out * w_out_), w_out(w_out_), h(c.h), w(c.w), s_h(c.s_h), s_w(c.s_w), r_h(c.r_h), r_w(c.r_w),
+          by_hw(hw_out), by_w(w_out_)
+    {
+    }
+};
+//
 // `claim` (optional): buf, qconv2d_claim_bytes() of device memory, zero
 // before the first launch that uses it, which every launch leaves zero
 // again (the launches that use one buffer must not overlap: one buffer per
@@ -100,7 +136,7 @@ struct ConvClaim {
 hipError_t qconv2d_run(const ConvPlan &plan, const PackGeom &pg, const ConvGeom &g, DType dt,
                        const void *x, const void *wpack, const void *bias, void *out,
                        float *stats, const ConvFold *fold, hipStream_t stream, bool poincare = false,
-                       ConvClaim *claim = nullptr);
+                       ConvClaim *claim = nullptr, const ConvScatter *scatter = nullptr);
 size_t qconv2d_claim_bytes();
 
 // The pointwise streaming kernel (1x1 kernel, no padding, any stride; bf16,
@@ -113,7 +149,8 @@ int qconv2d_pointwise_group_stages(int64_t m, int cus);
 int qconv2d_pointwise_stage_pixels();
 hipError_t qconv2d_pointwise_run(const ConvGeom &g, const PackGeom &pg, int group_stages, const void *x,
                                  const void *wpack, const void *bias, void *out, float *stats, int stat_tiles,
-                                 const ConvFold *fold, hipStream_t stream);
+                                 const ConvFold *fold, hipStream_t stream,
+                                 const ConvScatter *scatter = nullptr);
 
 // The stem layer (g.c_in == 1, bf16) as its own kernel: rgb is the colour
 // planes [n][3][h][w], mapped to quaternions by eq. 4 as they are loaded;
@@ -125,11 +162,13 @@ hipError_t qconv2d_pointwise_run(const ConvGeom &g, const PackGeom &pg, int grou
 hipError_t qconv2d_stem_run(const PackGeom &pg, const ConvGeom &g, DType dt, const void *rgb, const void *wpack,
                             const void *bias, void *out, hipStream_t stream);
 
-// Input gradient of the Hamilton convolution: dX = conv(Z, W'), Z = dY (stride
-// 1) or dY scattered with s-1 zeros between rows/columns (staged in `stage`,
-// qconv2d_grad_data_stage_bytes bytes), W' the conjugated, transposed,
-// flipped kernel (packed into `wpack`: qconv2d_pack_geom of the gradient
-// geometry), stride 1, pad d(k-1) - p (must be >= 0).  g is the forward
+// Input gradient of the Hamilton convolution: dX = conv(Z, W'), Z = dY, W'
+// the conjugated, transposed, flipped kernel (packed into `wpack`:
+// qconv2d_pack_geom of the gradient geometry), stride 1, pad d(k-1) - p (must
+// be >= 0).  A strided layer without dilation runs one such convolution per
+// output phase on its sub-kernel (see backward_data_phases); a strided and
+// dilated one takes Z = dY scattered with s-1 zeros between rows/columns
+// (staged in `stage`, qconv2d_grad_data_stage_bytes bytes).  g is the forward
 // layer's geometry; dy [n][h_out][w_out][4][c_out], dx [n][h][w][4][c_in].
 // With sep, the separable form's input gradient (eqs. 8-10) instead:
 // dX_p = sum_q M[p][q] (W'_p (*) Z_q), W'_p the transposed, flipped real
