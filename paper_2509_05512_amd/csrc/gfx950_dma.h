@@ -1,4 +1,5 @@
-// Global -> LDS DMA helpers shared by the convolution kernels (gfx950).
+// Device helpers shared by the kernels (gfx950): global -> LDS DMA, the folded
+// normalisation's map, scattered pixels.
 // Device-only; included inside no namespace.
 #pragma once
 
@@ -49,6 +50,16 @@ __device__ __forceinline__ void wait_vmcnt()
     static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
     // vmcnt[3:0] | expcnt (7) | lgkmcnt (15) | vmcnt[5:4]
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+// The map of a folded inference IQBN, in fp64: scale = gamma / sqrt(var +
+// eps), shift = (bias - mean) * scale + beta.
+__device__ __forceinline__ void fold_map(float mean, float var, float gamma, float beta, float bias, float eps,
+                                         float &scale, float &shift)
+{
+    const double sc = double(gamma) / sqrt(double(var) + double(eps));
+    scale = float(sc);
+    shift = float((double(bias) - double(mean)) * sc + double(beta));
 }
 
 // Quotient by a FastDiv's divisor, and the pixel of `out` that a scattered

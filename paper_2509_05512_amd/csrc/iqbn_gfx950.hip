@@ -34,6 +34,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "gfx950_dma.h"
 #include "quan_launch.h"
 
 namespace quan {
@@ -1758,10 +1759,8 @@ __global__ __launch_bounds__(kThreads) void iqbn_fold(const float *__restrict__ 
     const int col = blockIdx.x * kThreads + threadIdx.x;
     if (col >= cols)
         return;
-    const double sc = double(gamma[col]) / sqrt(double(var[col]) + double(eps));
-    const double b = bias != nullptr ? double(float(bias[col])) : 0.0;
-    scale[col] = float(sc);
-    shift[col] = float((b - double(mean[col])) * sc + double(beta[col]));
+    fold_map(mean[col], var[col], gamma[col], beta[col], bias != nullptr ? float(bias[col]) : 0.0f, eps, scale[col],
+             shift[col]);
 }
 
 }  // namespace

@@ -130,6 +130,8 @@ struct KArgs {
     int relu;
     ScatterMap scatter;  // (kEpiScatter) where each output pixel goes
     unsigned out_bytes;  // (kEpiScatter, bf16) bytes of the images written into
+    float *part;         // (kEpiPartial) partial tiles
+    int splits;          // (kEpiPartial) work-groups per tile
 };
 
 // Work-groups a launch with tail blocks may have (the claim buffer's
@@ -218,7 +220,9 @@ __device__ __forceinline__ void interleave_kstep()
 // components).  VEC: c_in is a multiple of the 16-byte chunk, so activations
 // move by DMA; otherwise the producer loads partial chunks element-wise.
 // EPI: what the epilogue applies (kEpiBias, kEpiStats, kEpiFold,
-// kEpiScatter: nothing, pixels stored where KArgs::scatter says); fixed at
+// kEpiScatter: nothing, pixels stored where KArgs::scatter says, kEpiPartial:
+// one of a.splits runs of the tile's stages, accumulators stored as they are
+// for qconv2d_add_splits); fixed at
 // compile time so the common bias-only kernel carries none of the others'
 // state through its main loop.
 //
@@ -238,7 +242,7 @@ __device__ __forceinline__ void interleave_kstep()
 // separable form needs only W_q beside x_q, so a stage's weights are still
 // four 16-channel row groups (kernel 2*pair + g/2, channel half g%2).
 // K-step j of a stage then belongs to component 2*pair + j/2.
-enum : int { kEpiBias = 0, kEpiStats = 1, kEpiFold = 2, kEpiScatter = 3 };
+enum : int { kEpiBias = 0, kEpiStats = 1, kEpiFold = 2, kEpiScatter = 3, kEpiPartial = 4 };
 // Producer waves per work-group.  A tile with few MFMAs per stage (the
 // separable form, a quarter of the Hamilton MFMAs; tiles of 32 or fewer
 // output channels) runs at the pace of its activation loads, and four
@@ -312,7 +316,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
     // weight region) to the region's upper half, which the A instructions
     // of rows 64..127 load instead.  A producer issues as many instructions
     // per step as for a tile, and a tail block takes ceil(S / 2) steps.
-    constexpr bool TAIL2 = ALLP && FORM == kFormHamilton && VEC && !POINCARE && NPROD == 2 &&
+    constexpr bool TAIL2 = ALLP && EPI != kEpiPartial && FORM == kFormHamilton && VEC && !POINCARE && NPROD == 2 &&
                            A_INSTR == 2 * B_INSTR && A_BYTES == 2 * B_BYTES;
     constexpr bool P_UNIFORM = BNC >= 32;       // a 32-wide N block lies in one output component
     static_assert(CPQ == 2 && CS * 4 * ES == 128, "stage row is 128 bytes");
@@ -343,7 +347,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
     // chunks of one component's BNC values are XOR-swizzled with the pixel
     // index modulo SWZ (their count), which spreads a wave's park stores
     // over the banks and leaves the component segments in place.
-    constexpr bool DEFER = ALLP || (WAVES_M == 1 && WTN == BNC && P_UNIFORM && !SEP);
+    constexpr bool DEFER = EPI != kEpiPartial && (ALLP || (WAVES_M == 1 && WTN == BNC && P_UNIFORM && !SEP));
     static_assert(EPI != kEpiScatter || ALLP || !DEFER, "the drain of one component's rows does not scatter");
     constexpr int SWZ = BNC * ES / 16;                  // chunks of one component's channels
     constexpr int OUT_ROW = (ALLP ? 4 : 1) * BNC * ES;  // bytes of one pixel in a wave's region
@@ -377,16 +381,25 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
     const int tiles = a.full_tiles;
     const int x_lo = int((long long)tiles * before_x / n_wg);
     const int x_hi = int((long long)tiles * (before_x + cnt_x) / n_wg);
-    const int n_mine = x_hi - x_lo > xslot ? (x_hi - x_lo - xslot + cnt_x - 1) / cnt_x : 0;
+    // (partial tiles: work-group (m-tile, split, n-tile), one run of stages)
+    const int n_mine = EPI == kEpiPartial ? 1
+                       : x_hi - x_lo > xslot ? (x_hi - x_lo - xslot + cnt_x - 1) / cnt_x : 0;
     // (with tail blocks every work-group has at least one tile, so none
     // leaves here and every one takes part in the claims)
     if (n_mine == 0)
         return;  // the whole work-group leaves: no barrier is pending
-    auto tile_of = [&](int k) { return x_lo + xslot + k * cnt_x; };
+    const int split = EPI == kEpiPartial ? bid / a.n_tiles % a.splits : 0;
+    auto tile_of = [&](int k) {
+        if constexpr (EPI == kEpiPartial)
+            return bid / (a.n_tiles * a.splits) * a.n_tiles + bid % a.n_tiles;
+        return x_lo + xslot + k * cnt_x;
+    };
     const bool tails = TAIL2 && a.tail_blocks > 0;
     // first pixel of tail block c
     auto tail_m0 = [&](int c) { return ((BM / WTM) * a.full_tiles + c) * WTM; };
-    const int S = a.stages;
+    // first stage of the work-group's run and its stages
+    const int s_lo = EPI == kEpiPartial ? int((long long)a.stages * split / a.splits) : 0;
+    const int S = EPI == kEpiPartial ? int((long long)a.stages * (split + 1) / a.splits) - s_lo : a.stages;
     const int ST = TAIL2 ? (S + 1) / 2 : S;  // steps of a tail block
 
     if (wave >= NCW) {
@@ -402,6 +415,11 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
         // Issue cursor: tile k (of this work-group), stage t of that tile at
         // tap (ky, kx) and channel block cblk, and the tile's DMA plan.
         int k = 0, ky = 0, kx = 0, cblk = 0;
+        if constexpr (EPI == kEpiPartial) {
+            cblk = s_lo % a.n_cblk;
+            ky = s_lo / a.n_cblk / a.k_w;
+            kx = s_lo / a.n_cblk - ky * a.k_w;
+        }
         int n_items = n_mine;  // items known so far: the tiles, then each claimed tail block
         const T *xt = nullptr;
         unsigned x_bytes = 0;  // bytes of x from xt on (capped at 2^31 - 1)
@@ -1427,6 +1445,28 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
             ph = (ph + S) & 3;
         }
 
+        if constexpr (EPI == kEpiPartial) {
+            // fragment f of (split, tile): four accumulator registers of one
+            // block, 64 lanes x 16 bytes, so every store is 1 KB contiguous
+            constexpr int FRAGS = QS * NB * MB * 4;  // per wave
+            f32x4 *dst = reinterpret_cast<f32x4 *>(a.part) +
+                         ((size_t(split) * a.full_tiles + tile) * NCW + wave) * FRAGS * 64 + lane;
+#pragma unroll
+            for (int qs = 0; qs < QS; ++qs)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            f32x4 v;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                v[e] = acc[qs][nb][mb][4 * g + e];
+                            dst[(((qs * NB + nb) * MB + mb) * 4 + g) * 64] = v;
+                        }
+            return;
+        }
         if (defer) {
             // finish the previous tile's stores before its region is reused
             for (; d_next < N_DRAIN; ++d_next)
@@ -1691,6 +1731,110 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
     }
 }
 
+// Adds the partial tiles of a split convolution and applies its epilogue: one
+// block of 256 threads per 32 x 32 accumulator block of a tile (the four
+// registers of group g = thread / 64, lane thread % 64, as the partial kernel
+// holds them), splits added in order.  Bound by reading the partials, which
+// the partial launch has just written (they are in the last-level cache).
+// Measured with it, bf16 3x3, 256 -> 256 channels, one 14 x 14 image (16 tiles
+// of 144 stages, 9 splits): 49.8 us + 4.7 for the folded map -> 15.0 + 4.0; 6 to
+// 12 splits measure the same, 18 and 24 are 4-5 us slower, and non-temporal or
+// device-scope stores of the partials gain nothing (18.4 against 18.9).
+struct SplitArgs {
+    const float *part;
+    int splits, tiles, n_tiles, bm, bnc, m, c_out;
+    void *out;
+    const void *bias;  // EPI bias (NULL: none)
+    const float *mean, *var, *gamma, *beta;  // EPI fold
+    float eps;
+    int relu;
+    int scattered;
+    ScatterMap scatter;
+};
+
+// ALLP: a wave's blocks are (component, 32-channel block) of 32 pixels; else
+// the 64-pixel tile of 2 x 2 waves, whose 32 columns of wave n are component-
+// major over the tile's bnc channels.
+template <typename T, bool ALLP, bool FOLD>
+__global__ __launch_bounds__(256) void qconv2d_add_splits(SplitArgs a)
+{
+    __shared__ float sc[32], sh[32];
+    const int tid = threadIdx.x, lane = tid & 63, g = tid >> 6;
+    const int waves = 4, frags = ALLP ? 4 * (a.bnc / 32) : 1;  // blocks per wave
+    const int blk = blockIdx.x % frags, wave = blockIdx.x / frags % waves, tile = blockIdx.x / (frags * waves);
+    const int m0 = tile / a.n_tiles * a.bm, o0 = tile % a.n_tiles * a.bnc;
+    const int pix0 = m0 + (ALLP ? wave : wave % 2) * 32;
+    // column i of the block: component p(i), channel o(i)
+    auto column = [&](int i, int &p, int &o) {
+        if constexpr (ALLP) {
+            p = blk / (a.bnc / 32);
+            o = o0 + blk % (a.bnc / 32) * 32 + i;
+        } else {
+            const int tn = wave / 2 * 32 + i;
+            p = tn / a.bnc;
+            o = o0 + tn % a.bnc;
+        }
+    };
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(a.part) + size_t(blockIdx.x) * 256 + tid;
+    const size_t step = size_t(a.tiles) * waves * frags * 256;
+    f32x4 sum = src[0];
+    int s = 1;
+    for (; s + 3 < a.splits; s += 4) {
+        f32x4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] = src[(s + u) * step];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            sum += v[u];
+    }
+    for (; s < a.splits; ++s)
+        sum += src[s * step];
+    if (tid < 32) {
+        int p, o;
+        column(tid, p, o);
+        float fs = 1.0f, fh = 0.0f;
+        if (o < a.c_out) {
+            const int col = p * a.c_out + o;
+            const T *bias = static_cast<const T *>(a.bias);
+            const float b = bias != nullptr ? float(bias[col]) : 0.0f;
+            if constexpr (FOLD)
+                fold_map(a.mean[col], a.var[col], a.gamma[col], a.beta[col], b, a.eps, fs, fh);
+            else
+                fh = b;
+        }
+        sc[tid] = fs;
+        sh[tid] = fh;
+    }
+    __syncthreads();
+    const int m = pix0 + (lane & 31), i0 = 8 * g + 4 * (lane >> 5);
+    int p, o;
+    column(i0, p, o);
+    if (m >= a.m || o >= a.c_out)
+        return;
+    const size_t pix = a.scattered ? size_t(scatter_pixel(a.scatter, m)) : size_t(m);
+    T *dst = static_cast<T *>(a.out) + (pix * 4 + p) * a.c_out + o;
+    T v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float y = fmaf(sum[e], sc[i0 + e], sh[i0 + e]);
+        if (FOLD && a.relu)
+            y = fmaxf(y, 0.0f);
+        v[e] = T(y);
+    }
+    if ((a.c_out & 3) == 0) {
+        struct alignas(4 * sizeof(T)) Quad {
+            T e[4];
+        };
+        *reinterpret_cast<Quad *>(dst) = Quad{{v[0], v[1], v[2], v[3]}};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (o + e < a.c_out)
+                dst[e] = v[e];
+    }
+}
+
 // Packs W_r, W_i, W_j, W_k (each OIHW) into [tap][cblk][kernel][cout_pad][CS]
 // so that one stage of one N-tile is four contiguous runs; padding is zero.
 // c_in, c_out are the packed convolution's.  The transposed modes pack the
@@ -1878,8 +2022,9 @@ struct KernelEntry {
     // channel masking, 2 for paired stages (separable bf16, c_in a multiple
     // of 32), 3 for the Poincare stem (element loads of eq. 4 from colour
     // planes); NULL where the kind or variant does not apply (statistics need
-    // the deferred epilogue, scattered pixels are an input gradient's).
-    const void *fn[4][4];
+    // the deferred epilogue, scattered pixels are an input gradient's, partial
+    // tiles the Hamilton form's).
+    const void *fn[5][4];
     const char *name;
     bool allp;   // all-components waves in the Hamilton form: takes tail blocks
 };
@@ -1915,7 +2060,8 @@ constexpr const void *stem_fn()
 }
 // the folded-IQBN epilogue serves the Hamilton form only (inference
 // convolution + IQBN), as does the scattering one (the separable form's input
-// gradient has kernels of its own); the separable form has a bias epilogue
+// gradient has kernels of its own) and the partial one; the separable form has
+// a bias epilogue
 template <typename T, int MB, int NB, int WM, int WN, bool VEC, bool SEP, int EPI = kEpiFold>
 constexpr const void *fold_fn()
 {
@@ -1938,7 +2084,9 @@ constexpr const void *fold_fn()
               fold_fn<T, MB, NB, WM, WN, false, SEP>(),                                                \
               pair_fn<T, MB, NB, WM, WN, kEpiFold, SEP>(), nullptr},                                     \
              {fold_fn<T, MB, NB, WM, WN, true, SEP, kEpiScatter>(),                                    \
-              fold_fn<T, MB, NB, WM, WN, false, SEP, kEpiScatter>(), nullptr, nullptr}},                \
+              fold_fn<T, MB, NB, WM, WN, false, SEP, kEpiScatter>(), nullptr, nullptr},                 \
+             {fold_fn<T, MB, NB, WM, WN, true, SEP, kEpiPartial>(),                                    \
+              fold_fn<T, MB, NB, WM, WN, false, SEP, kEpiPartial>(), nullptr, nullptr}},                \
             #T "_mb" #MB "x" #WM "_nb" #NB "x" #WN #SEP                                                \
     }
 
@@ -1962,6 +2110,9 @@ constexpr const void *fold_fn()
               nullptr, nullptr},                                                                       \
              {(const void *)&qconv2d_igemm<__bf16, 1, NB, 4, 1, true, kEpiScatter, false, false, true>, \
               (const void *)&qconv2d_igemm<__bf16, 1, NB, 4, 1, false, kEpiScatter, false, false, true>, \
+              nullptr, nullptr},                                                                       \
+             {(const void *)&qconv2d_igemm<__bf16, 1, NB, 4, 1, true, kEpiPartial, false, false, true>, \
+              (const void *)&qconv2d_igemm<__bf16, 1, NB, 4, 1, false, kEpiPartial, false, false, true>, \
               nullptr, nullptr}},                                                                      \
             "bf16_allp_nb" #NB, true                                                                   \
     }
@@ -1981,7 +2132,8 @@ constexpr const void *fold_fn()
              {nullptr, nullptr, nullptr, nullptr},                                                     \
              {(const void *)&qconv2d_igemm<T, MB, NB, WM, WN, true, kEpiScatter, false, false, ALLPW, kFormSepGrad>,  \
               (const void *)&qconv2d_igemm<T, MB, NB, WM, WN, false, kEpiScatter, false, false, ALLPW, kFormSepGrad>, \
-              nullptr, nullptr}},                                                    \
+              nullptr, nullptr},                                                                       \
+             {nullptr, nullptr, nullptr, nullptr}},                                                    \
             #T "_sepgrad_mb" #MB "x" #WM "_nb" #NB "x" #WN                                             \
     }
 
@@ -2062,6 +2214,38 @@ double plan_cost(const KernelEntry &k, int64_t m, int c_out, int stages, int cus
     return double(rounds) * tile;
 }
 
+// How many work-groups share a tile's K loop.  A layer of few tiles leaves
+// compute units idle while each work-group walks all stages at the pace of
+// its loads: kSplitStageUs a stage (measured: 0.35 us on the 32-channel bf16
+// tile, 144 stages in 50 us on 16 work-groups; 0.7 on the 64-channel one; 0.4
+// on the fp32 tile).  Splitting it `n` ways costs the second launch and the
+// partials' way to memory and back (at half of the 8 TB/s that they see in
+// the last-level cache) and is taken where it saves a fifth.  At most one
+// work-group per compute unit and at least four stages each, so the pipeline
+// fills.
+struct SplitCost {
+    int splits;
+    double us;
+};
+constexpr double kSplitLaunchUs = 4.0, kSplitGain = 0.8, kSplitBytesPerUs = 4e6;
+constexpr int kSplitMinStages = 4, kSplitMax = 32;
+
+SplitCost split_cost(const KernelEntry &k, int64_t m, int c_out, int stages, int cus)
+{
+    const int64_t tiles = (m + k.bm - 1) / k.bm * ((c_out + k.bnc - 1) / k.bnc);
+    const double stage_us = k.dt == DType::F32 ? 0.4 : 0.35 * k.nb;
+    const int64_t rounds = (tiles + cus - 1) / cus;
+    const double whole = double(rounds) * (stages * stage_us + 4.0);
+    SplitCost best = {1, whole};
+    for (int n = 2; n <= kSplitMax && stages / n >= kSplitMinStages && tiles * n <= cus; ++n) {
+        const double bytes = 2.0 * n * double(tiles) * k.bm * 4.0 * k.bnc * sizeof(float);
+        const double us = (stages + n - 1) / n * stage_us + 4.0 + kSplitLaunchUs + bytes / kSplitBytesPerUs;
+        if (us < best.us && us < kSplitGain * whole)
+            best = {n, us};
+    }
+    return best;
+}
+
 }  // namespace
 
 PackGeom qconv2d_pack_geom(int c_in, int c_out, int k_h, int k_w, DType dt)
@@ -2075,7 +2259,7 @@ PackGeom qconv2d_pack_geom(int c_in, int c_out, int k_h, int k_w, DType dt)
     return pg;
 }
 
-ConvPlan qconv2d_plan(const ConvGeom &g, DType dt, ConvForm form)
+ConvPlan qconv2d_plan(const ConvGeom &g, DType dt, ConvForm form, bool split)
 {
     const bool sep = form != ConvForm::Hamilton;
     const int64_t m = g.m();
@@ -2092,6 +2276,8 @@ ConvPlan qconv2d_plan(const ConvGeom &g, DType dt, ConvForm form)
         p.stat_rows = p.bm * p.group_stages;
         p.stat_tiles = int((m + p.stat_rows - 1) / p.stat_rows);
         p.name = "bf16_pointwise";
+        p.splits = 1;
+        p.part = nullptr;
         return p;
     }
     const int pk = dt == DType::BF16 ? 16 : 8;
@@ -2114,6 +2300,23 @@ ConvPlan qconv2d_plan(const ConvGeom &g, DType dt, ConvForm form)
             id = i;
         }
     }
+    // a split of the tile above or of the other one, whichever is faster
+    int splits = 1;
+    if (split && form == ConvForm::Hamilton) {
+        double us = split_cost(kKernels[id], m, g.c_out, stages, cus).us;
+        splits = split_cost(kKernels[id], m, g.c_out, stages, cus).splits;
+        for (int i = 0; i < kNumKernels; ++i) {
+            const KernelEntry &k = kKernels[i];
+            if (k.dt != dt || k.form != int(form) || (k.bnc == 64 && g.c_out <= 32))
+                continue;
+            const SplitCost c = split_cost(k, m, g.c_out, stages, cus);
+            if (c.splits > 1 && c.us < us) {
+                us = c.us;
+                splits = c.splits;
+                id = i;
+            }
+        }
+    }
     const KernelEntry &k = kKernels[id];
     ConvPlan p;
     p.id = id;
@@ -2126,7 +2329,21 @@ ConvPlan qconv2d_plan(const ConvGeom &g, DType dt, ConvForm form)
     p.stat_rows = k.stat_rows;
     p.stat_tiles = int((m + k.stat_rows - 1) / k.stat_rows);
     p.name = k.name;
+    p.splits = splits;
+    p.part = nullptr;
     return p;
+}
+
+size_t qconv2d_split_bytes(const ConvPlan &plan)
+{
+    if (plan.splits <= 1)
+        return 0;
+    return size_t(plan.splits) * plan.m_tiles * plan.n_tiles * plan.bm * 4 * plan.bnc * sizeof(float);
+}
+
+bool qconv2d_folds(const ConvPlan &plan)
+{
+    return plan.pointwise || plan.splits > 1;
 }
 
 namespace {
@@ -2240,6 +2457,32 @@ AxisPhase axis_phase(int k, int p, int s, int in, int r)
     return a;
 }
 
+// The convolution of one output phase.
+ConvGeom phase_geom(const ConvGeom &g, const AxisPhase &ay, const AxisPhase &ax)
+{
+    ConvGeom t = qconv2d_grad_data_geom(g);
+    t.k_h = ay.taps;
+    t.k_w = ax.taps;
+    t.p_h = ay.pad;
+    t.p_w = ax.pad;
+    t.h = g.h_out;
+    t.w = g.w_out;
+    t.h_out = ay.size;
+    t.w_out = ax.size;
+    return t;
+}
+
+// The plan of a gradient convolution, split where its partials fit.
+ConvPlan grad_plan(const ConvGeom &t, DType dt, bool sep, void *part, size_t part_bytes)
+{
+    const ConvForm form = sep ? ConvForm::SeparableGradData : ConvForm::Hamilton;
+    ConvPlan p = qconv2d_plan(t, dt, form, true);
+    if (p.splits > 1 && (part == nullptr || qconv2d_split_bytes(p) > part_bytes))
+        return qconv2d_plan(t, dt, form);
+    p.part = static_cast<float *>(part);
+    return p;
+}
+
 // The strided input gradient as s_h x s_w stride-1 convolutions of dY, one
 // per output phase (only the taps that reach it: the MFMA work of the layer
 // once, where the zero-inserted gradient does it s_h * s_w times), each of
@@ -2247,10 +2490,10 @@ AxisPhase axis_phase(int k, int p, int s, int in, int r)
 // phase's kernel.  Measured on 16 x 160 x 160, 32 -> 64, 3x3 stride 2, bf16:
 // a pass that interleaved dense phases into dX took 45.6 us, the phases' four
 // packs and the unused whole one 24 us, and the convolutions 126 us where
-// they now take MEAS_P (a phase's pixel is 256 contiguous bytes, whole lines).
+// they now take 134 (a phase's pixel is 256 contiguous bytes, whole lines).
 hipError_t backward_data_phases(const ConvGeom &g, DType dt, const void *dy, const void *w_r, const void *w_i,
                                 const void *w_j, const void *w_k, void *dx, void *wpack, hipStream_t stream,
-                                bool sep, ConvClaim *claim)
+                                bool sep, ConvClaim *claim, void *part, size_t part_bytes)
 {
     const ConvGeom whole = qconv2d_grad_data_geom(g);
     const PackGeom pg = qconv2d_pack_geom(whole.c_in, whole.c_out, whole.k_h, whole.k_w, dt);
@@ -2289,17 +2532,9 @@ hipError_t backward_data_phases(const ConvGeom &g, DType dt, const void *dy, con
             const AxisPhase ax = axis_phase(g.k_w, g.p_w, g.s_w, g.w, rx);
             if (ay.size == 0 || ax.size == 0)
                 continue;  // no pixels
-            ConvGeom t = whole;
-            t.k_h = ay.taps;
-            t.k_w = ax.taps;
-            t.p_h = ay.pad;
-            t.p_w = ax.pad;
-            t.h = g.h_out;
-            t.w = g.w_out;
-            t.h_out = ay.size;
-            t.w_out = ax.size;
+            const ConvGeom t = phase_geom(g, ay, ax);
             const ConvScatter to = {g.h, g.w, g.s_h, g.s_w, ry, rx};
-            e = qconv2d_run(qconv2d_plan(t, dt, sep ? ConvForm::SeparableGradData : ConvForm::Hamilton),
+            e = qconv2d_run(grad_plan(t, dt, sep, part, part_bytes),
                             qconv2d_pack_geom(t.c_in, t.c_out, t.k_h, t.k_w, dt), t, dt, dy, wp, nullptr, dx, nullptr,
                             nullptr, stream, false, claim, &to);
             if (e != hipSuccess)
@@ -2329,15 +2564,33 @@ hipError_t backward_data_phases(const ConvGeom &g, DType dt, const void *dy, con
 }
 }  // namespace
 
+size_t qconv2d_grad_data_split_bytes(const ConvGeom &g, DType dt, bool sep)
+{
+    const ConvForm form = sep ? ConvForm::SeparableGradData : ConvForm::Hamilton;
+    if (!by_phases(g))
+        return qconv2d_split_bytes(qconv2d_plan(qconv2d_grad_data_geom(g), dt, form, true));
+    size_t best = 0;
+    for (int ry = 0; ry < g.s_h; ++ry)
+        for (int rx = 0; rx < g.s_w; ++rx) {
+            const AxisPhase ay = axis_phase(g.k_h, g.p_h, g.s_h, g.h, ry);
+            const AxisPhase ax = axis_phase(g.k_w, g.p_w, g.s_w, g.w, rx);
+            if (ay.taps == 0 || ax.taps == 0 || ay.size == 0 || ax.size == 0)
+                continue;
+            const size_t b = qconv2d_split_bytes(qconv2d_plan(phase_geom(g, ay, ax), dt, form, true));
+            best = b > best ? b : best;
+        }
+    return best;
+}
+
 hipError_t qconv2d_backward_data_run(const ConvGeom &g, DType dt, const void *dy, const void *w_r, const void *w_i,
                                      const void *w_j, const void *w_k, void *dx, void *wpack, void *stage,
-                                     hipStream_t stream, bool sep, ConvClaim *claim)
+                                     hipStream_t stream, bool sep, ConvClaim *claim, void *part, size_t part_bytes)
 {
     const ConvGeom t = qconv2d_grad_data_geom(g);
     if (t.p_h < 0 || t.p_w < 0 || t.h < 1 || t.w < 1)
         return hipErrorInvalidValue;
     if (by_phases(g))
-        return backward_data_phases(g, dt, dy, w_r, w_i, w_j, w_k, dx, wpack, stream, sep, claim);
+        return backward_data_phases(g, dt, dy, w_r, w_i, w_j, w_k, dx, wpack, stream, sep, claim, part, part_bytes);
     const PackGeom pg = qconv2d_pack_geom(t.c_in, t.c_out, t.k_h, t.k_w, dt);
     hipError_t e = sep ? pack_weights<kPackSeparableGrad>(pg, t.c_in, t.c_out, t.k_h, t.k_w, dt, w_r, w_i, w_j, w_k,
                                                           wpack, stream)
@@ -2375,7 +2628,7 @@ hipError_t qconv2d_backward_data_run(const ConvGeom &g, DType dt, const void *dy
             return e;
         z = stage;
     }
-    return qconv2d_run(qconv2d_plan(t, dt, sep ? ConvForm::SeparableGradData : ConvForm::Hamilton), pg, t, dt, z,
+    return qconv2d_run(grad_plan(t, dt, sep, part, part_bytes), pg, t, dt, z,
                        wpack, nullptr, dx, nullptr, nullptr, stream, false, claim);
 }
 
@@ -2387,7 +2640,7 @@ bool qconv2d_writes_stats(const ConvPlan &plan, const ConvGeom &g, DType dt)
         return false;
     const KernelEntry &k = kKernels[plan.id];
     // deferred epilogue and whole 16-byte output chunks
-    return k.defer && g.c_out % (dt == DType::BF16 ? 8 : 4) == 0;
+    return plan.splits == 1 && k.defer && g.c_out % (dt == DType::BF16 ? 8 : 4) == 0;
 }
 
 size_t qconv2d_claim_bytes()
@@ -2413,7 +2666,7 @@ hipError_t qconv2d_run(const ConvPlan &plan, const PackGeom &pg, const ConvGeom 
     const int es = dt == DType::BF16 ? 2 : 4;
     if (128 / (4 * es) != pg.pk || kPackCoutAlign % k.bnc != 0 || k.dt != dt || pg.bytes > 0x7fffffffu)
         return hipErrorInvalidValue;
-    KArgs a;
+    KArgs a{};
     a.x = x;
     a.wpack = wpack;
     a.bias = bias;
@@ -2447,7 +2700,7 @@ hipError_t qconv2d_run(const ConvPlan &plan, const PackGeom &pg, const ConvGeom 
     a.relu = fold != nullptr && fold->relu ? 1 : 0;
     if (stats != nullptr && !qconv2d_writes_stats(plan, g, dt))
         return hipErrorInvalidValue;
-    if (fold != nullptr && (fold->scale == nullptr || fold->shift == nullptr))
+    if (fold != nullptr && plan.splits == 1 && (fold->scale == nullptr || fold->shift == nullptr))
         return hipErrorInvalidValue;
     void *args[] = {&a};
     if (scatter != nullptr) {
@@ -2466,6 +2719,58 @@ hipError_t qconv2d_run(const ConvPlan &plan, const PackGeom &pg, const ConvGeom 
     const void *fn = k.fn[epi][poincare ? 3 : (g.c_in % epc) != 0 ? 1 : paired ? 2 : 0];
     if (fn == nullptr)
         return hipErrorInvalidValue;
+    a.part = plan.part;
+    a.splits = plan.splits;
+    if (plan.splits > 1) {
+        const void *pfn = k.fn[kEpiPartial][(g.c_in % epc) != 0 ? 1 : 0];
+        if (poincare || stats != nullptr || plan.part == nullptr || pfn == nullptr)
+            return hipErrorInvalidValue;
+        a.full_tiles = plan.m_tiles * plan.n_tiles;
+        a.tail_blocks = 0;
+        a.claim = nullptr;
+        a.epoch = 0;
+        hipError_t e = hipLaunchKernel(pfn, dim3(unsigned(a.full_tiles) * unsigned(plan.splits)), dim3(k.threads), args,
+                                       0, stream);
+        if (e != hipSuccess)
+            return e;
+        SplitArgs r;
+        r.part = plan.part;
+        r.splits = plan.splits;
+        r.tiles = a.full_tiles;
+        r.n_tiles = plan.n_tiles;
+        r.bm = plan.bm;
+        r.bnc = plan.bnc;
+        r.m = a.m;
+        r.c_out = g.c_out;
+        r.out = out;
+        r.bias = fold != nullptr ? fold->bias : bias;
+        r.mean = r.var = r.gamma = r.beta = nullptr;
+        r.eps = 0.0f;
+        r.relu = 0;
+        if (fold != nullptr) {
+            r.mean = fold->mean;
+            r.var = fold->var;
+            r.gamma = fold->gamma;
+            r.beta = fold->beta;
+            r.eps = fold->eps;
+            r.relu = fold->relu ? 1 : 0;
+        }
+        r.scattered = scatter != nullptr ? 1 : 0;
+        r.scatter = a.scatter;
+        const dim3 blocks(unsigned(a.full_tiles) * 4u * unsigned(k.allp ? 4 * (k.bnc / 32) : 1));
+        if (dt == DType::BF16) {
+            if (fold != nullptr)
+                hipLaunchKernelGGL((qconv2d_add_splits<__bf16, true, true>), blocks, dim3(256), 0, stream, r);
+            else
+                hipLaunchKernelGGL((qconv2d_add_splits<__bf16, true, false>), blocks, dim3(256), 0, stream, r);
+        } else {
+            if (fold != nullptr)
+                hipLaunchKernelGGL((qconv2d_add_splits<float, false, true>), blocks, dim3(256), 0, stream, r);
+            else
+                hipLaunchKernelGGL((qconv2d_add_splits<float, false, false>), blocks, dim3(256), 0, stream, r);
+        }
+        return hipGetLastError();
+    }
     // Persistent grid: as many work-groups as fit on the device at once, at
     // most one per tile.
     const long long tiles = (long long)plan.m_tiles * plan.n_tiles;

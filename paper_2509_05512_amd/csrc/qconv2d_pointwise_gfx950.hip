@@ -65,8 +65,8 @@ struct PwArgs {
     unsigned x_bytes;
     float *stats;       // [2][4 c_out][stat_tiles] (EPI statistics)
     int stat_tiles;
-    const float *scale;  // [4 c_out] (EPI fold)
-    const float *shift;
+    const float *mean, *var, *gamma, *beta;  // [4 c_out] (EPI fold)
+    float eps;
     int relu;
     ScatterMap scatter;  // (EPI scatter)
     unsigned out_bytes;  // (EPI scatter) bytes of the images written into
@@ -355,8 +355,11 @@ __global__ __launch_bounds__(kPwThreads) void qconv2d_pointwise(PwArgs a)
         const int col = threadIdx.x;  // 0..255 covers 4 * COUT
         if (col < 4 * COUT) {
             if constexpr (EPI == kPwEpiFold) {
-                cmap[col] = a.scale[col];
-                cmap[4 * COUT + col] = a.shift[col];
+                // formed here, 4 COUT columns per work-group, while the first
+                // stages are on their way: a launch of its own took 4.8 us
+                const float b = a.bias != nullptr ? float(static_cast<const __bf16 *>(a.bias)[col]) : 0.0f;
+                fold_map(a.mean[col], a.var[col], a.gamma[col], a.beta[col], b, a.eps, cmap[col],
+                         cmap[4 * COUT + col]);
             } else {
                 cmap[col] = a.bias != nullptr ? float(static_cast<const __bf16 *>(a.bias)[col]) : 0.0f;
             }
@@ -512,13 +515,19 @@ hipError_t qconv2d_pointwise_run(const ConvGeom &g, const PackGeom &pg, int grou
     a.x_bytes = unsigned(int64_t(g.n) * g.h * g.w * 8 * g.c_in);
     a.stats = stats;
     a.stat_tiles = stat_tiles;
-    a.scale = fold != nullptr ? fold->scale : nullptr;
-    a.shift = fold != nullptr ? fold->shift : nullptr;
+    a.mean = a.var = a.gamma = a.beta = nullptr;
+    a.eps = 0.0f;
+    if (fold != nullptr) {
+        a.bias = fold->bias;
+        a.mean = fold->mean;
+        a.var = fold->var;
+        a.gamma = fold->gamma;
+        a.beta = fold->beta;
+        a.eps = fold->eps;
+    }
     a.relu = fold != nullptr && fold->relu ? 1 : 0;
     const int blocks = (a.stages + group_stages - 1) / group_stages;
     if (stats != nullptr && (fold != nullptr || stat_tiles != blocks))
-        return hipErrorInvalidValue;
-    if (fold != nullptr && (fold->scale == nullptr || fold->shift == nullptr))
         return hipErrorInvalidValue;
     if (scatter != nullptr) {
         a.scatter = ScatterMap(*scatter, g.h_out, g.w_out);

@@ -56,7 +56,8 @@ enum Purpose {
     kWgrad = 5,
     kIqbnBarrier = 6,  // the one-launch IQBN's grid-barrier flags: zeroed once, when allocated
     kConvClaim = 7,    // the convolution's tail-block claims: zeroed once, when allocated
-    kIqbnMask = 8      // sign bits of the saved ReLU output, IQBN gradient (optional)
+    kIqbnMask = 8,     // sign bits of the saved ReLU output, IQBN gradient (optional)
+    kConvSplit = 9     // partial tiles of a convolution that splits K (optional)
 };
 
 // Returns a device buffer of at least `bytes` for (current device, stream,
@@ -152,6 +153,19 @@ int conv_claim(void *stream, quan::ConvClaim *out)
     // take tags from a range of their own
     out->epoch = uses * 17u;
     return QUAN_OK;
+}
+
+// The plan of a convolution on this stream, split over K where that pays and
+// the partial tiles can be had.
+quan::ConvPlan plan_conv(void *stream, const quan::ConvGeom &g, quan::DType dt, quan::ConvForm form)
+{
+    quan::ConvPlan plan = quan::qconv2d_plan(g, dt, form, true);
+    if (plan.splits > 1) {
+        plan.part = static_cast<float *>(optional_workspace(stream, kConvSplit, quan::qconv2d_split_bytes(plan)));
+        if (plan.part == nullptr)
+            plan = quan::qconv2d_plan(g, dt, form);
+    }
+    return plan;
 }
 
 constexpr int64_t kMaxElems = (int64_t(1) << 31) - 1;
@@ -352,7 +366,8 @@ int conv_packed(const char *name, bool sep, const void *x, const void *packed, c
         return fail(QUAN_ERR_ALIAS, "%s: out overlaps the packed weights", name);
     const quan::DType dt = to_dt(dtype);
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
-    const quan::ConvPlan plan = quan::qconv2d_plan(g, dt, sep ? quan::ConvForm::Separable : quan::ConvForm::Hamilton);
+    const quan::ConvPlan plan =
+        plan_conv(stream, g, dt, sep ? quan::ConvForm::Separable : quan::ConvForm::Hamilton);
     quan::ConvClaim claim{};
     if (int rc = conv_claim(stream, &claim))
         return rc;
@@ -403,8 +418,8 @@ int conv_unpacked(const char *name, bool sep, const void *x, const void *w_r, co
     quan::ConvClaim claim{};
     if (int rc = conv_claim(stream, &claim))
         return rc;
-    e = quan::qconv2d_run(quan::qconv2d_plan(g, dt, sep ? quan::ConvForm::Separable : quan::ConvForm::Hamilton), pg,
-                          g, dt, x, wpack, bias, out, nullptr, nullptr, s, false, &claim);
+    e = quan::qconv2d_run(plan_conv(stream, g, dt, sep ? quan::ConvForm::Separable : quan::ConvForm::Hamilton), pg, g,
+                          dt, x, wpack, bias, out, nullptr, nullptr, s, false, &claim);
     if (e != hipSuccess)
         return fail_hip(e, "qconv2d launch");
     return QUAN_OK;
@@ -541,7 +556,7 @@ QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const 
 
     const quan::DType dt = to_dt(dtype);
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
-    const quan::ConvPlan plan = quan::qconv2d_plan(g, dt, quan::ConvForm::Hamilton);
+    const quan::ConvPlan plan = plan_conv(stream, g, dt, quan::ConvForm::Hamilton);
     const int64_t pixels = g.m();
     hipStream_t s = static_cast<hipStream_t>(stream);
     void *work = nullptr;
@@ -625,20 +640,24 @@ QUAN_API int quan_qconv2d_iqbn_inference(const void *x, const void *packed, cons
     const quan::DType dt = to_dt(dtype);
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    void *work = nullptr;
-    if (int rc = workspace(stream, kIqbnFold, 2 * sbytes, &work))
-        return rc;
-    float *scale = static_cast<float *>(work), *shift = scale + size_t(4) * c_out;
-    hipError_t e = quan::iqbn_fold_run(running_mean, running_var, gamma, beta, bias, eps, c_out, dt, scale,
-                                       shift, s);
-    if (e != hipSuccess)
-        return fail_hip(e, "iqbn fold launch");
-    const quan::ConvFold fold{scale, shift, relu != 0};
+    const quan::ConvPlan plan = plan_conv(stream, g, dt, quan::ConvForm::Hamilton);
+    quan::ConvFold fold{nullptr, nullptr, relu != 0, running_mean, running_var, gamma, beta, bias, eps};
+    hipError_t e;
+    if (!quan::qconv2d_folds(plan)) {
+        void *work = nullptr;
+        if (int rc = workspace(stream, kIqbnFold, 2 * sbytes, &work))
+            return rc;
+        float *scale = static_cast<float *>(work), *shift = scale + size_t(4) * c_out;
+        e = quan::iqbn_fold_run(running_mean, running_var, gamma, beta, bias, eps, c_out, dt, scale, shift, s);
+        if (e != hipSuccess)
+            return fail_hip(e, "iqbn fold launch");
+        fold.scale = scale;
+        fold.shift = shift;
+    }
     quan::ConvClaim claim{};
     if (int rc = conv_claim(stream, &claim))
         return rc;
-    e = quan::qconv2d_run(quan::qconv2d_plan(g, dt, quan::ConvForm::Hamilton), pg, g, dt, x, packed, bias, out,
-                          nullptr, &fold, s, false, &claim);
+    e = quan::qconv2d_run(plan, pg, g, dt, x, packed, bias, out, nullptr, &fold, s, false, &claim);
     if (e != hipSuccess)
         return fail_hip(e, "qconv2d launch");
     return QUAN_OK;
@@ -755,8 +774,12 @@ int backward_data(const char *name, bool sep, const void *dy, const void *w_r, c
     quan::ConvClaim claim{};
     if (int rc = conv_claim(stream, &claim))
         return rc;
+    size_t pb = quan::qconv2d_grad_data_split_bytes(g, dt, sep);
+    void *part = pb > 0 ? optional_workspace(stream, kConvSplit, pb) : nullptr;
+    if (part == nullptr)
+        pb = 0;
     const hipError_t e = quan::qconv2d_backward_data_run(g, dt, dy, w_r, w_i, w_j, w_k, dx, wpack, stage,
-                                                         static_cast<hipStream_t>(stream), sep, &claim);
+                                                         static_cast<hipStream_t>(stream), sep, &claim, part, pb);
     if (e != hipSuccess)
         return fail_hip(e, "backward data launch");
     return QUAN_OK;

@@ -50,15 +50,23 @@ struct ConvPlan {
     // implicit-GEMM kernel table: group_stages 32-pixel stages per work-group
     bool pointwise;
     int group_stages;
+    // A layer with too few tiles for the chip splits each tile's K loop over
+    // `splits` work-groups (1: none), whose fp32 partial tiles go to `part`
+    // (qconv2d_split_bytes(plan) bytes, set by the caller) and are added, in
+    // split order, by a second launch that applies the epilogue.
+    int splits;
+    float *part;
 };
+size_t qconv2d_split_bytes(const ConvPlan &plan);
 
 // What a convolution launch computes: the Hamilton product (eq. 5), the
 // separable form (eq. 7), or the separable form's input gradient (eqs.
 // 8-10: block (p, q) of the 4x4 block weight is M[p][q] W'_p).
 enum class ConvForm : int { Hamilton = 0, Separable = 1, SeparableGradData = 2 };
 
-// Pick a tile configuration for the convolution.
-ConvPlan qconv2d_plan(const ConvGeom &g, DType dt, ConvForm form);
+// Pick a tile configuration for the convolution (split: it may split K, for
+// a caller that has the memory).
+ConvPlan qconv2d_plan(const ConvGeom &g, DType dt, ConvForm form, bool split = false);
 
 // Pack W_r..W_k (OIHW) into the PackGeom layout, zero padded.
 hipError_t qconv2d_pack_weights(const PackGeom &pg, int c_in, int c_out, int k_h, int k_w, DType dt,
@@ -74,12 +82,19 @@ hipError_t qconv2d_pack_weights(const PackGeom &pg, int c_in, int c_out, int k_h
 //
 // With `fold` non-NULL the epilogue applies out = scale[col] * acc +
 // shift[col] (fp32, [4][c_out] each, col = p * c_out + o) and max(0, .) when
-// relu is set, instead of adding the bias (inference IQBN folded in).
+// relu is set, instead of adding the bias (inference IQBN folded in).  The map
+// is formed in fp64 from the statistics and parameters (fold_map), by the
+// launch itself where qconv2d_folds(plan) holds, else beforehand by
+// iqbn_fold_run into scale and shift; the launch then takes `bias` from here.
 struct ConvFold {
     const float *scale;
     const float *shift;
     bool relu;
+    const float *mean, *var, *gamma, *beta;  // [4][c_out]
+    const void *bias;                        // [4][c_out] of the run's type, or NULL
+    float eps;
 };
+bool qconv2d_folds(const ConvPlan &plan);
 //
 // With `poincare` (a stem layer: g.c_in == 1, bias epilogue) x is the colour
 // planes [n][3][h][w] of the input images, mapped to quaternions by eq. 4
@@ -175,9 +190,13 @@ hipError_t qconv2d_stem_run(const PackGeom &pg, const ConvGeom &g, DType dt, con
 // kernel and M the backward mixing matrix, accumulated in fp32.
 ConvGeom qconv2d_grad_data_geom(const ConvGeom &g);
 size_t qconv2d_grad_data_stage_bytes(const ConvGeom &g, DType dt);
+// Bytes with which every convolution of the call may split K (`part`, of
+// part_bytes, may be smaller or NULL: those that do not fit then don't).
+size_t qconv2d_grad_data_split_bytes(const ConvGeom &g, DType dt, bool sep);
 hipError_t qconv2d_backward_data_run(const ConvGeom &g, DType dt, const void *dy, const void *w_r, const void *w_i,
                                      const void *w_j, const void *w_k, void *dx, void *wpack, void *stage,
-                                     hipStream_t stream, bool sep = false, ConvClaim *claim = nullptr);
+                                     hipStream_t stream, bool sep = false, ConvClaim *claim = nullptr,
+                                     void *part = nullptr, size_t part_bytes = 0);
 
 // Weight and bias gradients of the Hamilton convolution for dL/dY = dy:
 // dw_r..dw_k [c_out][c_in][k_h][k_w] and db [4][c_out] (NULL: skipped), all
