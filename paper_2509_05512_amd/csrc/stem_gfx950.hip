@@ -5,10 +5,16 @@
 // 3x3 stem) against a few dozen output reals per pixel.  The implicit-GEMM
 // kernel would stage 16 input channels per step with 15 of them zero; this
 // kernel builds each MFMA's K = 16 slice (two taps x four components) of
-// one output pixel per lane straight from the colour planes, with the map
-// of eq. 4 evaluated in fp32 (one division per tap) and rounded once to
-// bf16.  The layer is bound
-// by writing its output (4 * c_out reals per pixel against 3 inputs).
+// one output pixel per lane from the colour planes, with the map of eq. 4
+// evaluated in fp32 and rounded once to bf16.  The layer is bound by writing its output (4 * c_out reals per pixel
+// against 3 inputs).
+//
+// A work-group takes bands of consecutive output rows of one image.  It maps
+// the band's input rows once per pixel into LDS (8 bytes a quaternion, zeros
+// outside the image), where every tap of every output pixel then finds them:
+// the map costs a load of three planes and a division per input pixel, which
+// per tap was 2.25 (stride 2) to 9 times as much.  A band whose input rows do
+// not fit (wide or strongly dilated layers) maps per tap from memory.
 //
 // Per wave: 32 consecutive output pixels at a time, D = W^T X^T with
 //   A (32 output reals x 16 k): the signed Hamilton block weight of eq. 6,
@@ -18,10 +24,16 @@
 //       fragment each);
 //   B (16 k x 32 pixels): lane l holds pixel l % 32, k = 16m + 8(l/32) + e,
 //       i.e. taps 4m + 2(l/32) and 4m + 2(l/32) + 1, all four components;
-//   D: lane l holds rows 8j + 4(l/32) + i (i, j < 4) of its pixel, so each
-//       group of four rows goes out as one 8-byte store of bf16.
+//   D: lane l holds rows 8j + 4(l/32) + i (i, j < 4) of its pixel.  The wave
+//       parks 64 of them at a time in LDS (rows padded by 8 bytes, so the 32
+//       pixels' 8-byte pieces fall on different banks) and stores 16 bytes a
+//       lane, whole lines, where 8-byte stores from D touched 32 lines each.
+// 64 x 224 x 224 RGB, 3x3 stride 2 to 16 channels: 54.6 -> 33.1 us (122 MB;
+// a device copy of as much takes 24).  Bands of two rows or one work-group a
+// band instead of three work-groups a compute unit: 33.9, 35.0.
 #include <hip/hip_runtime.h>
 
+#include "gfx950_dma.h"
 #include "quan_launch.h"
 
 namespace quan {
@@ -31,28 +43,70 @@ typedef __bf16 stem_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float stem_f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kStemThreads = 256;
+constexpr int kStemWaves = kStemThreads / 64;
 constexpr int kStemMaxFrags = 32;  // NBLK x KM weight fragments held in LDS (1 KB each)
+constexpr int kStemMaxBand = 8;    // output rows of a band at most
+// LDS of a work-group: three fit a compute unit (160 KB), and no launch needs
+// more than the 64 KB that a kernel gets without asking.
+constexpr size_t kStemLds = 52 * 1024, kStemMaxLds = 64 * 1024;
 
 struct StemArgs {
     const __bf16 *rgb;   // [n][3][h][w]
     const __bf16 *wpack; // packed weights: W_m[o][tap] at ((tap * 4 + m) * cout_pad + o) * pk
     const __bf16 *bias;  // [4][c_out] or NULL
     __bf16 *out;         // [n][h_out][w_out][4][c_out]
-    int n, h, w, c_out, k_h, k_w, s_h, s_w, p_h, p_w, d_h, d_w, h_out, w_out;
+    int h, w, c_out, k_h, k_w, s_h, s_w, p_h, p_w, d_h, d_w, h_out, w_out;
     int cout_pad, pk;
     int km;              // K slices of 16: ceil(taps / 4)
-    int64_t m;           // output pixels
-    int64_t groups;      // ceil(m / 32)
+    int band;            // output rows of a band
+    int img_bands;       // bands per image
+    int bands;           // of all images
+    int patch_w;         // staged columns: input columns -p_w .. patch_w - p_w - 1
+    int patch;           // staged pixels of a band (the zero pixel follows); 0: not staged
+    FastDiv by_w_out, by_patch_w, by_last;  // by_last: pieces of the last parked slice of a pixel
 };
 
-template <int NBLK>
+// The quaternion of an RGB pixel (eq. 4) in bf16.
+__device__ __forceinline__ uint2 stem_quaternion(const __bf16 *px, int hw)
+{
+    const float r = float(px[0]), g = float(px[hw]), bl = float(px[2 * hw]);
+    const float n2 = r * r + g * g + bl * bl;
+    const float inv = 1.0f / (1.0f + n2);
+    const __bf16 q[4] = {__bf16((1.0f - n2) * inv), __bf16((2.0f * r) * inv), __bf16((2.0f * g) * inv),
+                         __bf16((2.0f * bl) * inv)};
+    uint2 v;
+    __builtin_memcpy(&v, q, 8);
+    return v;
+}
+
+// Bytes of one parked pixel (a slice of up to two blocks of 32 reals), and of
+// a work-group's LDS.
+__host__ __device__ constexpr int stem_park_row(int nblk)
+{
+    return 64 * (nblk < 2 ? nblk : 2) + 8;
+}
+__host__ __device__ constexpr size_t stem_lds_bytes(int nblk, int km, int patch)
+{
+    return size_t(nblk) * km * 1024 + size_t(32) * nblk * 4 + size_t(kStemWaves) * 32 * stem_park_row(nblk) +
+           size_t(4 * km) * 4 + (patch > 0 ? (size_t(patch) + 1) * 8 : 0);
+}
+static_assert(stem_lds_bytes(8, kStemMaxFrags / 8, 0) <= kStemLds && stem_lds_bytes(1, kStemMaxFrags, 0) <= kStemLds,
+              "every kernel fits without a patch");
+
+template <int NBLK, bool STAGED>
 __global__ __launch_bounds__(kStemThreads) void qconv2d_stem(StemArgs a)
 {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     // A fragments of the signed block weight, fragment (b, m) for lane l:
-    // rows 32b + l%32, k = 16m + 8(l/32) .. +7; and the bias of every row
-    __shared__ stem_bf16x8 wtab[kStemMaxFrags][64];
-    __shared__ float btab[32 * NBLK];
-    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    // rows 32b + l%32, k = 16m + 8(l/32) .. +7; the bias of every row; the
+    // waves' parked output; each tap's offset in the patch; the patch
+    stem_bf16x8(*const wtab)[64] = reinterpret_cast<stem_bf16x8(*)[64]>(lds);
+    float *const btab = reinterpret_cast<float *>(lds + size_t(NBLK) * a.km * 1024);
+    unsigned char *const parks = reinterpret_cast<unsigned char *>(btab + 32 * NBLK);
+    constexpr int prow = stem_park_row(NBLK);
+    uint2 *const patch = reinterpret_cast<uint2 *>(parks + kStemWaves * 32 * prow);
+    int *const taps_at = reinterpret_cast<int *>(patch + (STAGED ? a.patch + 1 : 0));
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, l32 = lane & 31;
     const int taps = a.k_h * a.k_w;
     const int rows = 4 * a.c_out;
     for (int idx = threadIdx.x; idx < NBLK * a.km * 64; idx += kStemThreads) {
@@ -75,90 +129,166 @@ __global__ __launch_bounds__(kStemThreads) void qconv2d_stem(StemArgs a)
     }
     for (int r = threadIdx.x; r < 32 * NBLK; r += kStemThreads)
         btab[r] = (a.bias != nullptr && r < rows) ? float(a.bias[r]) : 0.0f;
-    __syncthreads();
+    if constexpr (STAGED) {
+        // taps past the kernel (zero weights) read the zero pixel; -1 marks
+        // them, as their address does not move with the output pixel
+        for (int t = threadIdx.x; t < 4 * a.km; t += kStemThreads)
+            taps_at[t] = t < taps ? t / a.k_w * a.d_h * a.patch_w + t % a.k_w * a.d_w : -1;
+        if (threadIdx.x == 0)
+            patch[a.patch] = uint2{0u, 0u};
+    }
 
-    const int hw = a.h * a.w, hw_out = a.h_out * a.w_out;
-    const int64_t waves = int64_t(gridDim.x) * (kStemThreads / 64);
-    const int64_t wid = int64_t(blockIdx.x) * (kStemThreads / 64) + (threadIdx.x >> 6);
-    for (int64_t grp = wid; grp < a.groups; grp += waves) {
-        const int64_t pix = grp * 32 + l32;
-        const bool live = pix < a.m;
-        int img = 0, oy = 0, ox = 0;
-        if (live) {
-            img = int(pix / hw_out);
-            const int rr = int(pix - int64_t(img) * hw_out);
-            oy = rr / a.w_out;
-            ox = rr - oy * a.w_out;
-        }
+    const int hw = a.h * a.w;
+    unsigned char *const park = parks + wave * 32 * prow;
+    for (int bd = blockIdx.x; bd < a.bands; bd += gridDim.x) {
+        const int img = bd / a.img_bands, y0 = (bd - img * a.img_bands) * a.band;
+        const int nrows = a.h_out - y0 < a.band ? a.h_out - y0 : a.band;
         const __bf16 *plane = a.rgb + size_t(img) * 3 * hw;
-        // accumulators start at the bias of the lane's rows 32b + 8j + 4*half + i
-        stem_f32x16 acc[NBLK];
+        const int iy0 = y0 * a.s_h - a.p_h;
+        if constexpr (STAGED) {
+            __syncthreads();  // the previous band's patch is read
+            const int need = ((nrows - 1) * a.s_h + (a.k_h - 1) * a.d_h + 1) * a.patch_w;
+            // four pixels' loads in flight per thread
+            for (int i = threadIdx.x; i < need; i += 4 * kStemThreads) {
+                const __bf16 *px[4];
+                bool in[4];
+                uint2 v[4];
 #pragma unroll
-        for (int b = 0; b < NBLK; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                acc[b][i] = btab[32 * b + 8 * (i >> 2) + 4 * half + (i & 3)];
-        for (int m = 0; m < a.km; ++m) {
-            // the pixel's quaternions (eq. 4) at taps 4m + 2*half and 4m + 2*half + 1
-            stem_bf16x8 xq;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int tap = 4 * m + 2 * half + u;
-                float q0 = 0.0f, q1 = 0.0f, q2 = 0.0f, q3 = 0.0f;
-                if (live && tap < taps) {
-                    const int ky = tap / a.k_w, kx = tap - ky * a.k_w;
-                    const int iy = oy * a.s_h - a.p_h + ky * a.d_h, ix = ox * a.s_w - a.p_w + kx * a.d_w;
-                    if ((unsigned)iy < (unsigned)a.h && (unsigned)ix < (unsigned)a.w) {
-                        const __bf16 *px = plane + iy * a.w + ix;
-                        const float r = float(px[0]), g = float(px[hw]), bl = float(px[2 * hw]);
-                        const float n2 = r * r + g * g + bl * bl;
-                        const float inv = 1.0f / (1.0f + n2);
-                        q0 = (1.0f - n2) * inv;
-                        q1 = (2.0f * r) * inv;
-                        q2 = (2.0f * g) * inv;
-                        q3 = (2.0f * bl) * inv;
-                    }
+                for (int u = 0; u < 4; ++u) {
+                    const int j = i + u * kStemThreads;
+                    const int yy = fast_div(j, a.by_patch_w);
+                    const int iy = iy0 + yy, ix = j - yy * a.patch_w - a.p_w;
+                    in[u] = j < need && (unsigned)iy < (unsigned)a.h && (unsigned)ix < (unsigned)a.w;
+                    px[u] = plane + (in[u] ? iy * a.w + ix : 0);
                 }
-                xq[4 * u + 0] = __bf16(q0);
-                xq[4 * u + 1] = __bf16(q1);
-                xq[4 * u + 2] = __bf16(q2);
-                xq[4 * u + 3] = __bf16(q3);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    v[u] = stem_quaternion(px[u], hw);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (i + u * kStemThreads < need)
+                        patch[i + u * kStemThreads] = in[u] ? v[u] : uint2{0u, 0u};
             }
+        }
+        __syncthreads();
+        const int pixels = nrows * a.w_out;
+        __bf16 *const oband = a.out + (size_t(img) * a.h_out + y0) * a.w_out * rows;
+        for (int p0 = 32 * wave; p0 < pixels; p0 += 32 * kStemWaves) {
+            const int n_live = pixels - p0 < 32 ? pixels - p0 : 32;
+            // (pixels past the band repeat its last one and are not stored)
+            const int pix = p0 + (l32 < n_live ? l32 : n_live - 1);
+            const int oy = fast_div(pix, a.by_w_out), ox = pix - oy * a.w_out;
+            // accumulators start at the bias of the lane's rows 32b + 8j + 4*half + i
+            stem_f32x16 acc[NBLK];
 #pragma unroll
             for (int b = 0; b < NBLK; ++b)
-                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wtab[b * a.km + m][lane], xq, acc[b], 0, 0, 0);
-        }
-        if (!live)
-            continue;
-        __bf16 *orow = a.out + pix * rows;
 #pragma unroll
-        for (int b = 0; b < NBLK; ++b)
+                for (int i = 0; i < 16; ++i)
+                    acc[b][i] = btab[32 * b + 8 * (i >> 2) + 4 * half + (i & 3)];
+            const int at = oy * a.s_h * a.patch_w + ox * a.s_w;
+            for (int m = 0; m < a.km; ++m) {
+                // the pixel's quaternions at taps 4m + 2*half and 4m + 2*half + 1
+                uint2 q[2];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r0 = 32 * b + 8 * j + 4 * half;
-                if (r0 < rows) {
-                    __bf16 v[4];
+                for (int u = 0; u < 2; ++u) {
+                    const int tap = 4 * m + 2 * half + u;
+                    if constexpr (STAGED) {
+                        const int t = taps_at[tap];
+                        q[u] = patch[t >= 0 ? at + t : a.patch];
+                    } else {
+                        q[u] = uint2{0u, 0u};
+                        const int ky = tap / a.k_w, kx = tap - ky * a.k_w;
+                        const int iy = iy0 + oy * a.s_h + ky * a.d_h, ix = ox * a.s_w - a.p_w + kx * a.d_w;
+                        if (tap < taps && (unsigned)iy < (unsigned)a.h && (unsigned)ix < (unsigned)a.w)
+                            q[u] = stem_quaternion(plane + iy * a.w + ix, hw);
+                    }
+                }
+                stem_bf16x8 xq;
+                __builtin_memcpy(&xq, q, 16);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        v[i] = __bf16(acc[b][4 * j + i]);
-                    unsigned long long bits;
-                    __builtin_memcpy(&bits, v, 8);
-                    *reinterpret_cast<unsigned long long *>(orow + r0) = bits;
+                for (int b = 0; b < NBLK; ++b)
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wtab[b * a.km + m][lane], xq, acc[b], 0, 0, 0);
+            }
+            __bf16 *const orun = oband + size_t(p0) * rows;
+            constexpr int SB = NBLK < 2 ? NBLK : 2;  // blocks of a slice
+            const bool direct = (a.c_out & 1) != 0;  // 8-byte pieces only
+#pragma unroll
+            for (int b0 = 0; b0 < NBLK; b0 += SB) {
+#pragma unroll
+                for (int b = b0; b < b0 + SB; ++b)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int r0 = 32 * b + 8 * j + 4 * half;
+                        if (r0 < rows) {
+                            __bf16 v[4];
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                v[i] = __bf16(acc[b][4 * j + i]);
+                            uint2 bits;
+                            __builtin_memcpy(&bits, v, 8);
+                            if (!direct)
+                                *reinterpret_cast<uint2 *>(park + l32 * prow + 2 * (r0 - 32 * b0)) = bits;
+                            else if (l32 < n_live)
+                                *reinterpret_cast<uint2 *>(orun + l32 * rows + r0) = bits;
+                        }
+                    }
+                const int left = rows - 32 * b0;
+                if (!direct && left > 0) {
+                    // (a wave's LDS accesses are in order: no barrier)
+                    __builtin_amdgcn_wave_barrier();
+                    const bool whole = left >= 32 * SB;
+                    const int chunks = whole ? 4 * SB : left / 8;
+                    for (int i = lane; i < n_live * chunks; i += 64) {
+                        const int pl = whole ? i / (4 * SB) : fast_div(i, a.by_last), c = i - pl * chunks;
+                        const unsigned char *src = park + pl * prow + 16 * c;
+                        const uint2 lo = *reinterpret_cast<const uint2 *>(src);
+                        const uint2 hi = *reinterpret_cast<const uint2 *>(src + 8);
+                        *reinterpret_cast<uint4 *>(orun + pl * rows + 32 * b0 + 8 * c) =
+                            uint4{lo.x, lo.y, hi.x, hi.y};
+                    }
+                    __builtin_amdgcn_wave_barrier();
                 }
             }
+        }
     }
 }
 
 template <int NBLK>
-hipError_t launch_stem(const StemArgs &a, hipStream_t stream)
+hipError_t launch_stem(StemArgs a, int64_t n, hipStream_t stream)
 {
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess)
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    const int64_t wgs_needed = (a.groups + kStemThreads / 64 - 1) / (kStemThreads / 64);
-    const int64_t cap = int64_t(cus) * 8;
-    const int wgs = int(wgs_needed < cap ? wgs_needed : cap);
-    hipLaunchKernelGGL((qconv2d_stem<NBLK>), dim3(wgs), dim3(kStemThreads), 0, stream, a);
+    // The band: as many rows as leave three work-groups a compute unit, both
+    // in LDS and in number, since a taller band shares more input rows.
+    const int64_t span_h = int64_t(a.k_h - 1) * a.d_h + 1, span_w = int64_t(a.k_w - 1) * a.d_w + 1;
+    const int64_t cols = int64_t(a.w_out - 1) * a.s_w + span_w;
+    auto patch_of = [&](int band) { return (int64_t(band - 1) * a.s_h + span_h) * cols; };
+    a.band = 1;
+    const size_t fixed = stem_lds_bytes(NBLK, a.km, 0);
+    auto fits = [&](int band, size_t lds) {
+        const int64_t px = patch_of(band);
+        return px < int64_t(lds / 8) && fixed + size_t(px + 1) * 8 <= lds;
+    };
+    const bool staged = fits(1, kStemMaxLds);
+    while (a.band < kStemMaxBand && 2 * a.band <= a.h_out && (!staged || fits(2 * a.band, kStemLds)) &&
+           n * ((a.h_out + 2 * a.band - 1) / (2 * a.band)) >= 3LL * cus)
+        a.band *= 2;
+    a.img_bands = (a.h_out + a.band - 1) / a.band;
+    a.bands = int(n * a.img_bands);
+    a.patch_w = staged ? int(cols) : 1;
+    a.patch = staged ? int(patch_of(a.band)) : 0;
+    a.by_w_out = FastDiv(a.w_out);
+    a.by_patch_w = FastDiv(a.patch_w);
+    const int last = 4 * a.c_out % (NBLK < 2 ? 32 : 64) / 8;
+    a.by_last = FastDiv(last > 0 ? last : 1);
+    const size_t lds = stem_lds_bytes(NBLK, a.km, a.patch);
+    const int64_t cap = 3LL * cus;
+    const dim3 wgs(unsigned(a.bands < cap ? a.bands : cap));
+    if (staged)
+        hipLaunchKernelGGL((qconv2d_stem<NBLK, true>), wgs, dim3(kStemThreads), lds, stream, a);
+    else
+        hipLaunchKernelGGL((qconv2d_stem<NBLK, false>), wgs, dim3(kStemThreads), lds, stream, a);
     return hipGetLastError();
 }
 
@@ -179,7 +309,6 @@ hipError_t qconv2d_stem_run(const PackGeom &pg, const ConvGeom &g, DType dt, con
     a.wpack = static_cast<const __bf16 *>(wpack);
     a.bias = static_cast<const __bf16 *>(bias);
     a.out = static_cast<__bf16 *>(out);
-    a.n = g.n;
     a.h = g.h;
     a.w = g.w;
     a.c_out = g.c_out;
@@ -196,15 +325,13 @@ hipError_t qconv2d_stem_run(const PackGeom &pg, const ConvGeom &g, DType dt, con
     a.cout_pad = pg.cout_pad;
     a.pk = pg.pk;
     a.km = km;
-    a.m = g.m();
-    a.groups = (a.m + 31) / 32;
     if (nblk == 1)
-        return launch_stem<1>(a, stream);
+        return launch_stem<1>(a, g.n, stream);
     if (nblk == 2)
-        return launch_stem<2>(a, stream);
+        return launch_stem<2>(a, g.n, stream);
     if (nblk <= 4)
-        return launch_stem<4>(a, stream);
-    return launch_stem<8>(a, stream);
+        return launch_stem<4>(a, g.n, stream);
+    return launch_stem<8>(a, g.n, stream);
 }
 
 }  // namespace quan
