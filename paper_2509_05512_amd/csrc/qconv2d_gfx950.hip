@@ -1955,6 +1955,48 @@ __global__ __launch_bounds__(64) void qconv2d_pack_octets(const __bf16 *__restri
     }
 }
 
+// x [pixels][4][c] with every component's channels padded by zeros to cp, a
+// whole number of 16-byte chunks: what the DMA loads take.  One thread per
+// chunk, source pieces of P elements (P divides c).  The element loads that it
+// spares cost a memory latency per stage: 8 x 75 x 77, 3x3 bf16, 12 -> 20
+// channels 40.2 -> 17.3 + 3.7 us for the pad, its input gradient 66.9 -> 22.4 +
+// 6.4.
+// (Single-word DMA of the partial chunks instead: 123 and 202 us.)
+template <typename T, int P>
+__global__ __launch_bounds__(256) void qconv2d_pad_channels(const T *__restrict__ x, T *__restrict__ out, int c,
+                                                            int cp, int64_t total)
+{
+    constexpr int EPC = Elem<T>::per_chunk;
+    const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (idx >= total)
+        return;
+    const int per = cp / EPC;
+    const int64_t row = idx / per;  // pixel and component
+    const int c0 = int(idx - row * per) * EPC;
+    struct alignas(P * sizeof(T)) Piece {
+        T e[P];
+    };
+    struct alignas(16) Chunk {
+        T e[EPC];
+    };
+    Chunk v;
+#pragma unroll
+    for (int i = 0; i < EPC; i += P) {
+        Piece p;
+        if (c0 + i < c) {
+            p = *reinterpret_cast<const Piece *>(x + row * c + c0 + i);
+        } else {
+#pragma unroll
+            for (int e = 0; e < P; ++e)
+                p.e[e] = T(0);
+        }
+#pragma unroll
+        for (int e = 0; e < P; ++e)
+            v.e[i + e] = p.e[e];
+    }
+    reinterpret_cast<Chunk *>(out)[idx] = v;
+}
+
 template <typename T, int VW>
 __global__ __launch_bounds__(256) void qconv2d_grad_dilate(const T *__restrict__ dy, T *__restrict__ z, int ho,
                                                            int wo, int hz, int wz, int s_h, int s_w, int row_vecs,
@@ -2278,6 +2320,7 @@ ConvPlan qconv2d_plan(const ConvGeom &g, DType dt, ConvForm form, bool split)
         p.name = "bf16_pointwise";
         p.splits = 1;
         p.part = nullptr;
+        p.pad = nullptr;
         return p;
     }
     const int pk = dt == DType::BF16 ? 16 : 8;
@@ -2331,7 +2374,64 @@ ConvPlan qconv2d_plan(const ConvGeom &g, DType dt, ConvForm form, bool split)
     p.name = k.name;
     p.splits = splits;
     p.part = nullptr;
+    p.pad = nullptr;
     return p;
+}
+
+namespace {
+int padded_channels(int c, DType dt)
+{
+    const int epc = dt == DType::BF16 ? 8 : 4;
+    return (c + epc - 1) / epc * epc;
+}
+
+hipError_t pad_channels(const ConvGeom &g, DType dt, const void *x, void *pad, hipStream_t stream)
+{
+    const int cp = padded_channels(g.c_in, dt);
+    const int64_t total = int64_t(g.n) * g.h * g.w * 4 * (cp / (dt == DType::BF16 ? 8 : 4));
+    auto go = [&](auto kernel, auto *src) {
+        using T = std::remove_const_t<std::remove_pointer_t<decltype(src)>>;
+        hipLaunchKernelGGL(kernel, dim3(unsigned((total + 255) / 256)), dim3(256), 0, stream, src,
+                           static_cast<T *>(pad), g.c_in, cp, total);
+    };
+    const __bf16 *xb = static_cast<const __bf16 *>(x);
+    const float *xf = static_cast<const float *>(x);
+    if (dt == DType::BF16) {
+        if (g.c_in % 4 == 0)
+            go(qconv2d_pad_channels<__bf16, 4>, xb);
+        else if (g.c_in % 2 == 0)
+            go(qconv2d_pad_channels<__bf16, 2>, xb);
+        else
+            go(qconv2d_pad_channels<__bf16, 1>, xb);
+    } else {
+        if (g.c_in % 2 == 0)
+            go(qconv2d_pad_channels<float, 2>, xf);
+        else
+            go(qconv2d_pad_channels<float, 1>, xf);
+    }
+    return hipGetLastError();
+}
+}  // namespace
+
+// The pad costs a launch and one pass over x; a stage of element loads costs
+// about 1.8 us more than one of DMA (2.2 against 0.4), so it pays from about
+// four stages per work-group on.  The padded tensor keeps to the limits that
+// the entry points set for x.
+size_t qconv2d_pad_bytes(const ConvGeom &g, DType dt)
+{
+    const int cp = padded_channels(g.c_in, dt);
+    if (cp == g.c_in)
+        return 0;
+    const int pk = dt == DType::BF16 ? 16 : 8;
+    const int64_t stages = int64_t(g.k_h) * g.k_w * ((g.c_in + pk - 1) / pk);
+    const int64_t rounds = (g.m() / 128 + device_cus() - 1) / device_cus();
+    if (stages * (rounds > 0 ? rounds : 1) < 4)
+        return 0;
+    const int64_t es = dt == DType::BF16 ? 2 : 4, limit = (int64_t(1) << 31) - 1;
+    const int64_t img = int64_t(g.h) * g.w * 4 * cp;
+    if (img * g.n > limit || img * es * (256 / (int64_t(g.h_out) * g.w_out) + 2) > limit)
+        return 0;
+    return size_t(img) * g.n * es;
 }
 
 size_t qconv2d_split_bytes(const ConvPlan &plan)
@@ -2493,7 +2593,7 @@ ConvPlan grad_plan(const ConvGeom &t, DType dt, bool sep, void *part, size_t par
 // they now take 134 (a phase's pixel is 256 contiguous bytes, whole lines).
 hipError_t backward_data_phases(const ConvGeom &g, DType dt, const void *dy, const void *w_r, const void *w_i,
                                 const void *w_j, const void *w_k, void *dx, void *wpack, hipStream_t stream,
-                                bool sep, ConvClaim *claim, void *part, size_t part_bytes)
+                                bool sep, ConvClaim *claim, void *part, size_t part_bytes, int dy_channels)
 {
     const ConvGeom whole = qconv2d_grad_data_geom(g);
     const PackGeom pg = qconv2d_pack_geom(whole.c_in, whole.c_out, whole.k_h, whole.k_w, dt);
@@ -2532,7 +2632,8 @@ hipError_t backward_data_phases(const ConvGeom &g, DType dt, const void *dy, con
             const AxisPhase ax = axis_phase(g.k_w, g.p_w, g.s_w, g.w, rx);
             if (ay.size == 0 || ax.size == 0)
                 continue;  // no pixels
-            const ConvGeom t = phase_geom(g, ay, ax);
+            ConvGeom t = phase_geom(g, ay, ax);
+            t.c_in = dy_channels;  // as they lie in dy (zero kernels past the layer's)
             const ConvScatter to = {g.h, g.w, g.s_h, g.s_w, ry, rx};
             e = qconv2d_run(grad_plan(t, dt, sep, part, part_bytes),
                             qconv2d_pack_geom(t.c_in, t.c_out, t.k_h, t.k_w, dt), t, dt, dy, wp, nullptr, dx, nullptr,
@@ -2564,6 +2665,18 @@ hipError_t backward_data_phases(const ConvGeom &g, DType dt, const void *dy, con
 }
 }  // namespace
 
+size_t qconv2d_grad_data_pad_bytes(const ConvGeom &g, DType dt)
+{
+    // dy, or its zero-inserted form (staged with the padded channels: only
+    // dy itself is padded where it is not staged)
+    if ((g.s_h != 1 || g.s_w != 1) && !by_phases(g))
+        return 0;
+    ConvGeom t = qconv2d_grad_data_geom(g);
+    t.h = g.h_out;
+    t.w = g.w_out;
+    return qconv2d_pad_bytes(t, dt);
+}
+
 size_t qconv2d_grad_data_split_bytes(const ConvGeom &g, DType dt, bool sep)
 {
     const ConvForm form = sep ? ConvForm::SeparableGradData : ConvForm::Hamilton;
@@ -2584,13 +2697,26 @@ size_t qconv2d_grad_data_split_bytes(const ConvGeom &g, DType dt, bool sep)
 
 hipError_t qconv2d_backward_data_run(const ConvGeom &g, DType dt, const void *dy, const void *w_r, const void *w_i,
                                      const void *w_j, const void *w_k, void *dx, void *wpack, void *stage,
-                                     hipStream_t stream, bool sep, ConvClaim *claim, void *part, size_t part_bytes)
+                                     hipStream_t stream, bool sep, ConvClaim *claim, void *part, size_t part_bytes,
+                                     void *pad)
 {
-    const ConvGeom t = qconv2d_grad_data_geom(g);
+    ConvGeom t = qconv2d_grad_data_geom(g);
     if (t.p_h < 0 || t.p_w < 0 || t.h < 1 || t.w < 1)
         return hipErrorInvalidValue;
+    int channels = g.c_out;  // of dy as the convolutions read it
+    if (pad != nullptr && qconv2d_grad_data_pad_bytes(g, dt) > 0) {
+        ConvGeom d = t;  // dy's own geometry
+        d.h = g.h_out;
+        d.w = g.w_out;
+        const hipError_t e = pad_channels(d, dt, dy, pad, stream);
+        if (e != hipSuccess)
+            return e;
+        dy = pad;
+        channels = padded_channels(g.c_out, dt);
+    }
     if (by_phases(g))
-        return backward_data_phases(g, dt, dy, w_r, w_i, w_j, w_k, dx, wpack, stream, sep, claim, part, part_bytes);
+        return backward_data_phases(g, dt, dy, w_r, w_i, w_j, w_k, dx, wpack, stream, sep, claim, part, part_bytes,
+                                    channels);
     const PackGeom pg = qconv2d_pack_geom(t.c_in, t.c_out, t.k_h, t.k_w, dt);
     hipError_t e = sep ? pack_weights<kPackSeparableGrad>(pg, t.c_in, t.c_out, t.k_h, t.k_w, dt, w_r, w_i, w_j, w_k,
                                                           wpack, stream)
@@ -2598,9 +2724,10 @@ hipError_t qconv2d_backward_data_run(const ConvGeom &g, DType dt, const void *dy
                                                          wpack, stream);
     if (e != hipSuccess)
         return e;
+    t.c_in = channels;
     const void *z = dy;
     if (g.s_h != 1 || g.s_w != 1) {
-        const int row = 4 * g.c_out;
+        const int row = 4 * channels;
         const int vw = row % (dt == DType::BF16 ? 8 : 4) == 0 ? (dt == DType::BF16 ? 8 : 4) : 1;
         const int64_t total = int64_t(t.n) * t.h * t.w * (row / vw);
         const unsigned blocks = unsigned((total + 255) / 256);
@@ -2648,11 +2775,12 @@ size_t qconv2d_claim_bytes()
     return sizeof(unsigned) * (1 + size_t(kClaimMaxGroups));
 }
 
-hipError_t qconv2d_run(const ConvPlan &plan, const PackGeom &pg, const ConvGeom &g, DType dt,
+hipError_t qconv2d_run(const ConvPlan &plan, const PackGeom &pg, const ConvGeom &geom, DType dt,
                        const void *x, const void *wpack, const void *bias, void *out,
                        float *stats, const ConvFold *fold, hipStream_t stream, bool poincare, ConvClaim *claim,
                        const ConvScatter *scatter)
 {
+    ConvGeom g = geom;
     if (plan.pointwise) {
         if (poincare)
             return hipErrorInvalidValue;
@@ -2666,6 +2794,15 @@ hipError_t qconv2d_run(const ConvPlan &plan, const PackGeom &pg, const ConvGeom 
     const int es = dt == DType::BF16 ? 2 : 4;
     if (128 / (4 * es) != pg.pk || kPackCoutAlign % k.bnc != 0 || k.dt != dt || pg.bytes > 0x7fffffffu)
         return hipErrorInvalidValue;
+    if (plan.pad != nullptr && !poincare && g.c_in % epc != 0) {
+        // (the packed kernels are the same: blocks of 16 or 8 channels, zeros
+        // past c_in)
+        const hipError_t e = pad_channels(g, dt, x, plan.pad, stream);
+        if (e != hipSuccess)
+            return e;
+        x = plan.pad;
+        g.c_in = padded_channels(g.c_in, dt);
+    }
     KArgs a{};
     a.x = x;
     a.wpack = wpack;

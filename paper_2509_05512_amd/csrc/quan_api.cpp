@@ -57,7 +57,8 @@ enum Purpose {
     kIqbnBarrier = 6,  // the one-launch IQBN's grid-barrier flags: zeroed once, when allocated
     kConvClaim = 7,    // the convolution's tail-block claims: zeroed once, when allocated
     kIqbnMask = 8,     // sign bits of the saved ReLU output, IQBN gradient (optional)
-    kConvSplit = 9     // partial tiles of a convolution that splits K (optional)
+    kConvSplit = 9,    // partial tiles of a convolution that splits K (optional)
+    kConvPad = 10      // a convolution's input padded to whole chunks (optional)
 };
 
 // Returns a device buffer of at least `bytes` for (current device, stream,
@@ -165,6 +166,8 @@ quan::ConvPlan plan_conv(void *stream, const quan::ConvGeom &g, quan::DType dt, 
         if (plan.part == nullptr)
             plan = quan::qconv2d_plan(g, dt, form);
     }
+    if (const size_t pb = quan::qconv2d_pad_bytes(g, dt))
+        plan.pad = optional_workspace(stream, kConvPad, pb);
     return plan;
 }
 
@@ -778,8 +781,11 @@ int backward_data(const char *name, bool sep, const void *dy, const void *w_r, c
     void *part = pb > 0 ? optional_workspace(stream, kConvSplit, pb) : nullptr;
     if (part == nullptr)
         pb = 0;
+    const size_t db = quan::qconv2d_grad_data_pad_bytes(g, dt);
+    void *pad = db > 0 ? optional_workspace(stream, kConvPad, db) : nullptr;
     const hipError_t e = quan::qconv2d_backward_data_run(g, dt, dy, w_r, w_i, w_j, w_k, dx, wpack, stage,
-                                                         static_cast<hipStream_t>(stream), sep, &claim, part, pb);
+                                                         static_cast<hipStream_t>(stream), sep, &claim, part, pb,
+                                                         pad);
     if (e != hipSuccess)
         return fail_hip(e, "backward data launch");
     return QUAN_OK;

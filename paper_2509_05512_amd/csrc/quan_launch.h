@@ -56,8 +56,16 @@ struct ConvPlan {
     // split order, by a second launch that applies the epilogue.
     int splits;
     float *part;
+    // Room for x with its channels padded to whole 16-byte chunks
+    // (qconv2d_pad_bytes), or NULL: partial chunks are then loaded element by
+    // element.
+    void *pad;
 };
 size_t qconv2d_split_bytes(const ConvPlan &plan);
+
+// Bytes of x padded to whole chunks where a convolution is faster on that
+// (qconv2d_run writes it to plan.pad first), 0 where it takes x as it is.
+size_t qconv2d_pad_bytes(const ConvGeom &g, DType dt);
 
 // What a convolution launch computes: the Hamilton product (eq. 5), the
 // separable form (eq. 7), or the separable form's input gradient (eqs.
@@ -191,12 +199,14 @@ hipError_t qconv2d_stem_run(const PackGeom &pg, const ConvGeom &g, DType dt, con
 ConvGeom qconv2d_grad_data_geom(const ConvGeom &g);
 size_t qconv2d_grad_data_stage_bytes(const ConvGeom &g, DType dt);
 // Bytes with which every convolution of the call may split K (`part`, of
-// part_bytes, may be smaller or NULL: those that do not fit then don't).
+// part_bytes, may be smaller or NULL: those that do not fit then don't), and
+// with which it pads dy's channels (`pad`, or NULL: it does not).
 size_t qconv2d_grad_data_split_bytes(const ConvGeom &g, DType dt, bool sep);
+size_t qconv2d_grad_data_pad_bytes(const ConvGeom &g, DType dt);
 hipError_t qconv2d_backward_data_run(const ConvGeom &g, DType dt, const void *dy, const void *w_r, const void *w_i,
                                      const void *w_j, const void *w_k, void *dx, void *wpack, void *stage,
                                      hipStream_t stream, bool sep = false, ConvClaim *claim = nullptr,
-                                     void *part = nullptr, size_t part_bytes = 0);
+                                     void *part = nullptr, size_t part_bytes = 0, void *pad = nullptr);
 
 // Weight and bias gradients of the Hamilton convolution for dL/dY = dy:
 // dw_r..dw_k [c_out][c_in][k_h][k_w] and db [4][c_out] (NULL: skipped), all
