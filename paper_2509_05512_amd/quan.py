@@ -13,11 +13,11 @@ allocates it.
 """
 import ctypes
 import os
+import struct
 
 import torch
 
-_HERE = os.path.dirname(os.path.abspath(__file__))
-LIB_PATH = os.path.join(_HERE, "libquan.so")
+LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libquan.so")
 
 QUAN_F32, QUAN_BF16 = 0, 1
 _STATUS = {0: "QUAN_OK", -1: "QUAN_ERR_NULL", -2: "QUAN_ERR_SHAPE", -3: "QUAN_ERR_DTYPE",
@@ -33,20 +33,19 @@ class QuanTensor(ctypes.Structure):
                 ("shape", ctypes.c_int64 * 5), ("strides", ctypes.c_int64 * 5)]
 
 
+_PACK_DESC = struct.Struct("=Qii10q").pack  # the fields of QuanTensor in order (no padding)
+
+
 def describe(t):
     """A quan_tensor for a torch tensor (its real shape and strides), or None."""
     if t is None:
         return None
     if t.dim() > 5:
         raise ValueError("quan_tensor holds at most 5 axes")
-    d = QuanTensor()
-    d.data = t.data_ptr()
-    d.dtype = _dtype_code(t)
-    d.ndim = t.dim()
-    for i, (n, st) in enumerate(zip(t.shape, t.stride())):
-        d.shape[i] = n
-        d.strides[i] = st
-    return d
+    n = t.dim()
+    free = (0,) * (5 - n)
+    return QuanTensor.from_buffer_copy(_PACK_DESC(t.data_ptr(), _dtype_code(t), n, *t.shape, *free, *t.stride(), *free))
+
 
 # Every symbol include/quan.h declares, with its ctypes signature.
 _vp, _i32, _f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_float
@@ -125,11 +124,14 @@ def device_strides(n, c, h, w):
 
 
 def is_device_layout(t: torch.Tensor) -> bool:
-    if t.dim() != 5 or t.shape[1] != 4:
+    shape = t.shape
+    if len(shape) != 5 or shape[1] != 4:
         return False
-    n, _, c, h, w = t.shape
-    want = device_strides(n, c, h, w)
-    return all(st == wt or sz == 1 for st, wt, sz in zip(t.stride(), want, t.shape))
+    n, _, c, h, w = shape
+    s_n, s_q, s_c, s_h, s_w = t.stride()
+    row = 4 * c
+    return (s_q == c and (s_c == 1 or c == 1) and (s_w == row or w == 1) and (s_h == w * row or h == 1)
+            and (s_n == h * w * row or n == 1))
 
 
 def to_device_layout(t: torch.Tensor) -> torch.Tensor:
@@ -142,8 +144,33 @@ def empty_qmap(n, c, h, w, dtype, device):
     return torch.empty((n, h, w, 4, c), dtype=dtype, device=device).permute(0, 3, 4, 1, 2)
 
 
+# Host work per call matters where the kernels are short (a training step of a
+# 2 x 16 x 16 layer ran 100 us, its kernels 45; now 82): torch's raw stream handle
+# instead of a Stream object, a device guard only off the current device,
+# descriptors packed in one call, plain integers as pointers.
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
+class _Here:
+    def __enter__(self):
+        return None
+
+    def __exit__(self, *exc):
+        return False
+
+
+_HERE = _Here()
+
+
+def _on(device):
+    """A guard that makes `device` the current one."""
+    if device.type == "cuda" and device.index == torch.cuda.current_device():
+        return _HERE
+    return torch.cuda.device(device)
+
+
+_Pair = ctypes.c_int32 * 2
 
 
 def _pair(v):
@@ -151,7 +178,7 @@ def _pair(v):
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def conv_out_size(n, k, stride, pad, dil):
@@ -184,9 +211,9 @@ def quan_qconv2d_forward(x, w_r, w_i, w_j, w_k, bias=None, stride=1, pad=0, dila
     if out is None:
         ho, wo = conv_out_size(h, k_h, sh, ph, dh), conv_out_size(w, k_w, sw, pw, dw)
         out = empty_qmap(n, c_out, max(ho, 1), max(wo, 1), x.dtype, x.device)
-    pair = ctypes.c_int32 * 2
+    pair = _Pair
     descs = [describe(t) for t in (x, w_r, w_i, w_j, w_k, bias, out)]
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         rc = lib.quan_qconv2d_forward_desc(*[_ref(d) for d in descs[:6]], pair(sh, sw), pair(ph, pw),
                                            pair(dh, dw), _ref(descs[6]), _stream(x.device))
     _check(rc)
@@ -223,7 +250,7 @@ def _conv(fn_name, x, w_r, w_i, w_j, w_k, bias, stride, pad, dilation, out):
         out = empty_qmap(n, c_out, max(ho, 1), max(wo, 1), x.dtype, x.device)
     elif not is_device_layout(out) or tuple(out.shape) != (n, 4, c_out, ho, wo) or out.dtype != x.dtype:
         raise ValueError("out must be [N, 4, Cout, Ho, Wo] in device layout with x's dtype")
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         rc = getattr(lib, fn_name)(_ptr(x), _ptr(w_r), _ptr(w_i), _ptr(w_j), _ptr(w_k),
                                    _ptr(bias), sh, sw, ph, pw, dh, dw, _ptr(out),
                                    n, c_in, h, w, c_out, k_h, k_w, _dtype_code(x),
@@ -262,7 +289,7 @@ def quan_qconv2d_pack_weights(w_r, w_i, w_j, w_k, packed=None):
         packed = torch.empty(need, dtype=torch.uint8, device=w_r.device)
     elif packed.numel() * packed.element_size() < need or not packed.is_contiguous():
         raise ValueError(f"packed must be a contiguous buffer of at least {need} bytes")
-    with torch.cuda.device(w_r.device):
+    with _on(w_r.device):
         rc = lib.quan_qconv2d_pack_weights(_ptr(w_r), _ptr(w_i), _ptr(w_j), _ptr(w_k), c_in, c_out,
                                            k_h, k_w, _dtype_code(w_r), _ptr(packed),
                                            packed.numel() * packed.element_size(),
@@ -307,7 +334,7 @@ def _conv_packed(fn_name, x, packed, weight_shape, bias, stride, pad, dilation, 
         out = empty_qmap(n, c_out, max(ho, 1), max(wo, 1), x.dtype, x.device)
     elif not is_device_layout(out) or tuple(out.shape) != (n, 4, c_out, ho, wo) or out.dtype != x.dtype:
         raise ValueError("out must be [N, 4, Cout, Ho, Wo] in device layout with x's dtype")
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         rc = getattr(lib, fn_name)(_ptr(x), _ptr(packed), _ptr(bias), sh, sw, ph, pw,
                                    dh, dw, _ptr(out), n, c_in, h, w, c_out, k_h, k_w,
                                    _dtype_code(x), _stream(x.device))
@@ -352,7 +379,7 @@ def quan_qconv2d_iqbn_forward(x, packed, weight_shape, gamma, beta, bias=None, s
         mean = torch.empty(4, c_out, dtype=torch.float32, device=x.device)
     if var is None:
         var = torch.empty(4, c_out, dtype=torch.float32, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         rc = lib.quan_qconv2d_iqbn_forward(_ptr(x), _ptr(packed), _ptr(bias), sh, sw, ph, pw, dh, dw,
                                            _ptr(gamma), _ptr(beta), float(eps), int(bool(relu)),
                                            STATS_MODES[stats], _ptr(out), _ptr(mean), _ptr(var), n,
@@ -388,7 +415,7 @@ def quan_qconv2d_iqbn_inference(x, packed, weight_shape, running_mean, running_v
         out = empty_qmap(n, c_out, max(ho, 1), max(wo, 1), x.dtype, x.device)
     elif not is_device_layout(out) or tuple(out.shape) != (n, 4, c_out, ho, wo) or out.dtype != x.dtype:
         raise ValueError("out must be [N, 4, Cout, Ho, Wo] in device layout with x's dtype")
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         rc = lib.quan_qconv2d_iqbn_inference(_ptr(x), _ptr(packed), _ptr(bias), sh, sw, ph, pw, dh, dw,
                                              _ptr(running_mean), _ptr(running_var), _ptr(gamma),
                                              _ptr(beta), float(eps), int(bool(relu)), _ptr(out), n, c_in,
@@ -408,7 +435,7 @@ def quan_poincare_map(rgb, out=None):
         out = empty_qmap(n, 1, h, w, rgb.dtype, rgb.device)
     elif not is_device_layout(out) or tuple(out.shape) != (n, 4, 1, h, w) or out.dtype != rgb.dtype:
         raise ValueError("out must be [N, 4, 1, H, W] in device layout with rgb's dtype")
-    with torch.cuda.device(rgb.device):
+    with _on(rgb.device):
         rc = lib.quan_poincare_map(_ptr(rgb), _ptr(out), n, h, w, _dtype_code(rgb), _stream(rgb.device))
     _check(rc)
     return out
@@ -437,7 +464,7 @@ def quan_qconv2d_poincare_forward(rgb, packed, weight_shape, bias=None, stride=1
         out = empty_qmap(n, c_out, ho, wo, rgb.dtype, rgb.device)
     elif not is_device_layout(out) or tuple(out.shape) != (n, 4, c_out, ho, wo) or out.dtype != rgb.dtype:
         raise ValueError("out must be [N, 4, Cout, Ho, Wo] in device layout with rgb's dtype")
-    with torch.cuda.device(rgb.device):
+    with _on(rgb.device):
         rc = lib.quan_qconv2d_poincare_forward(_ptr(rgb), _ptr(packed), _ptr(bias), sh, sw, ph, pw, dh, dw,
                                                _ptr(out), n, h, w, c_out, k_h, k_w, _dtype_code(rgb),
                                                _stream(rgb.device))
@@ -467,7 +494,7 @@ def quan_qconv2d_backward_data(dy, w_r, w_i, w_j, w_k, input_hw, stride=1, pad=0
         dx = empty_qmap(n, c_in, h, w, dy.dtype, dy.device)
     elif not is_device_layout(dx) or tuple(dx.shape) != (n, 4, c_in, h, w) or dx.dtype != dy.dtype:
         raise ValueError("dx must be [N, 4, Cin, H, W] in device layout with dy's dtype")
-    with torch.cuda.device(dy.device):
+    with _on(dy.device):
         rc = getattr(lib, _fn)(_ptr(dy), _ptr(w_r), _ptr(w_i), _ptr(w_j), _ptr(w_k), sh, sw, ph, pw,
                                dh, dw, _ptr(dx), n, c_in, h, w, c_out, k_h, k_w, _dtype_code(dy),
                                _stream(dy.device))
@@ -496,7 +523,7 @@ def quan_qconv2d_backward_weight(x, dy, kernel_hw, stride=1, pad=0, dilation=1, 
         raise ValueError("dy's shape does not match x and the layer geometry")
     dws = [torch.empty((c_out, c_in, k_h, k_w), dtype=torch.float32, device=x.device) for _ in range(4)]
     db = torch.empty((4, c_out), dtype=torch.float32, device=x.device) if with_bias else None
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         rc = getattr(lib, _fn)(_ptr(x), _ptr(dy), sh, sw, ph, pw, dh, dw_, *[_ptr(t) for t in dws],
                                _ptr(db), n, c_in, h, w, c_out, k_h, k_w, _dtype_code(x),
                                _stream(x.device))
@@ -536,7 +563,7 @@ def quan_iqbn_backward(x, dout, mean, var, gamma, y=None, eps=1e-5, dx=None):
         raise ValueError("dx must be [N, 4, C, H, W] in device layout like x")
     dgamma = torch.empty(4, c, dtype=torch.float32, device=x.device)
     dbeta = torch.empty(4, c, dtype=torch.float32, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         rc = lib.quan_iqbn_backward(_ptr(x), _ptr(dout), _ptr(y), _ptr(mean), _ptr(var), _ptr(gamma),
                                     float(eps), _ptr(dx), _ptr(dgamma), _ptr(dbeta), n, c, h, w,
                                     _dtype_code(x), _stream(x.device))
@@ -560,7 +587,7 @@ def _iqbn(fn_name, x, gamma, beta, eps, out, mean, var):
         mean = torch.empty(4, c, dtype=torch.float32, device=x.device)
     if var is None:
         var = torch.empty(4, c, dtype=torch.float32, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         rc = getattr(lib, fn_name)(_ptr(x), _ptr(gamma), _ptr(beta), float(eps), _ptr(out),
                                    _ptr(mean), _ptr(var), n, c, h, w, _dtype_code(x),
                                    _stream(x.device))
@@ -583,7 +610,7 @@ def _iqbn_desc(fn_name, x, gamma, beta, eps, out, mean, var):
         if t.device != x.device:
             raise ValueError("all tensors must be on x's device")
     descs = [describe(t) for t in (x, gamma, beta, out, mean, var)]
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         rc = getattr(lib, fn_name)(_ref(descs[0]), _ref(descs[1]), _ref(descs[2]), float(eps),
                                    _ref(descs[3]), _ref(descs[4]), _ref(descs[5]), _stream(x.device))
     _check(rc)
