@@ -128,6 +128,11 @@ struct KArgs {
     const float *scale;
     const float *shift;
     int relu;
+    // With fold_tables the work-group forms the map itself from these, in its
+    // own table (scale then shift, 8 * c_out floats); scale is then NULL.
+    float *fold_tables;
+    const float *fold_mean, *fold_var, *fold_gamma, *fold_beta;
+    float fold_eps;
     ScatterMap scatter;  // (kEpiScatter) where each output pixel goes
     unsigned out_bytes;  // (kEpiScatter, bf16) bytes of the images written into
     float *part;         // (kEpiPartial) partial tiles
@@ -915,6 +920,24 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
     constexpr int N_FLIP = SEP ? 0 : NB * 4;
     Frags f0, f1;
     Frags fc, fd;  // separable form only
+    // The folded map, formed while the first stages are on their way (a launch
+    // of its own took 4.7 us); the barrier publishes it to the work-group.
+    const float *fold_scale = a.scale, *fold_shift = a.shift;
+    if constexpr (EPI == kEpiFold) {
+        if (a.fold_tables != nullptr) {
+            const int cols = 4 * a.c_out;
+            float *tab = a.fold_tables + size_t(bid) * 2 * cols;
+            for (int col = tid; col < cols; col += 64 * NCW) {
+                const float b = a.bias != nullptr ? float(static_cast<const T *>(a.bias)[col]) : 0.0f;
+                float sc, sh;
+                fold_map(a.fold_mean[col], a.fold_var[col], a.fold_gamma[col], a.fold_beta[col], b, a.fold_eps, sc, sh);
+                tab[col] = sc;
+                tab[cols + col] = sh;
+            }
+            fold_scale = tab;
+            fold_shift = tab + cols;
+        }
+    }
     __syncthreads();
     if constexpr (ALLP) {
         rd_act(0, xa0);
@@ -1291,8 +1314,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
     // scale 1 the fma is exactly acc + bias.
     auto col_affine = [&](int col, bool inside, float &sc, float &sh) {
         if constexpr (EPI == kEpiFold) {
-            sc = inside ? a.scale[col] : 0.0f;
-            sh = inside ? a.shift[col] : 0.0f;
+            sc = inside ? fold_scale[col] : 0.0f;
+            sh = inside ? fold_shift[col] : 0.0f;
         } else {
             sc = 1.0f;
             sh = (bias != nullptr && inside) ? float(bias[col]) : 0.0f;
@@ -1331,8 +1354,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
                         const bool in4 = o0 + oc < a.c_out;
                         const int col = in4 ? p * a.c_out + o0 + oc : 0;
                         if constexpr (EPI == kEpiFold) {
-                            const f32x4 s4 = *reinterpret_cast<const f32x4 *>(a.scale + col);
-                            const f32x4 h4 = *reinterpret_cast<const f32x4 *>(a.shift + col);
+                            const f32x4 s4 = *reinterpret_cast<const f32x4 *>(fold_scale + col);
+                            const f32x4 h4 = *reinterpret_cast<const f32x4 *>(fold_shift + col);
 #pragma unroll
                             for (int e = 0; e < 4; ++e) {
                                 sc[g][e] = in4 ? s4[e] : 0.0f;
@@ -1499,8 +1522,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
                             const bool in4 = o0 + oc < a.c_out;
                             const int col = in4 ? wn * a.c_out + o0 + oc : 0;
                             if constexpr (EPI == kEpiFold) {
-                                const f32x4 s4 = *reinterpret_cast<const f32x4 *>(a.scale + col);
-                                const f32x4 h4 = *reinterpret_cast<const f32x4 *>(a.shift + col);
+                                const f32x4 s4 = *reinterpret_cast<const f32x4 *>(fold_scale + col);
+                                const f32x4 h4 = *reinterpret_cast<const f32x4 *>(fold_shift + col);
 #pragma unroll
                                 for (int e = 0; e < 4; ++e) {
                                     sc[g][e] = in4 ? s4[e] : 0.0f;
@@ -2441,9 +2464,24 @@ size_t qconv2d_split_bytes(const ConvPlan &plan)
     return size_t(plan.splits) * plan.m_tiles * plan.n_tiles * plan.bm * 4 * plan.bnc * sizeof(float);
 }
 
-bool qconv2d_folds(const ConvPlan &plan)
+namespace {
+constexpr size_t kFoldTableBytes = size_t(16) << 20;  // of a launch's tables at most
+// Work-groups that a folding launch may have.
+int64_t fold_groups(const ConvPlan &plan)
 {
-    return plan.pointwise || plan.splits > 1;
+    const int64_t tiles = int64_t(plan.m_tiles) * plan.n_tiles, slots = 4 * int64_t(device_cus());
+    return tiles < slots ? tiles : slots;
+}
+}  // namespace
+
+// The pointwise kernel and a split's second launch keep the map on chip; wide
+// layers' tables on many work-groups (over 16 MiB) are not worth it: 0 too.
+size_t qconv2d_fold_bytes(const ConvPlan &plan, int c_out)
+{
+    if (plan.pointwise || plan.splits > 1)
+        return 0;
+    const size_t bytes = size_t(fold_groups(plan)) * 8 * c_out * sizeof(float);
+    return bytes <= kFoldTableBytes ? bytes : 0;
 }
 
 namespace {
@@ -2837,8 +2875,19 @@ hipError_t qconv2d_run(const ConvPlan &plan, const PackGeom &pg, const ConvGeom 
     a.relu = fold != nullptr && fold->relu ? 1 : 0;
     if (stats != nullptr && !qconv2d_writes_stats(plan, g, dt))
         return hipErrorInvalidValue;
-    if (fold != nullptr && plan.splits == 1 && (fold->scale == nullptr || fold->shift == nullptr))
-        return hipErrorInvalidValue;
+    if (fold != nullptr && plan.splits == 1) {
+        if (fold->tables != nullptr && fold->scale == nullptr) {
+            a.fold_tables = fold->tables;
+            a.fold_mean = fold->mean;
+            a.fold_var = fold->var;
+            a.fold_gamma = fold->gamma;
+            a.fold_beta = fold->beta;
+            a.fold_eps = fold->eps;
+            a.bias = fold->bias;
+        } else if (fold->scale == nullptr || fold->shift == nullptr) {
+            return hipErrorInvalidValue;
+        }
+    }
     void *args[] = {&a};
     if (scatter != nullptr) {
         if (stats != nullptr || fold != nullptr || bias != nullptr)
@@ -2912,7 +2961,9 @@ hipError_t qconv2d_run(const ConvPlan &plan, const PackGeom &pg, const ConvGeom 
     // most one per tile.
     const long long tiles = (long long)plan.m_tiles * plan.n_tiles;
     const long long slots = (long long)device_cus() * resident_wgs(fn, k.threads);
-    const unsigned blocks = unsigned(tiles < slots ? tiles : slots);
+    unsigned blocks = unsigned(tiles < slots ? tiles : slots);
+    if (a.fold_tables != nullptr && blocks > unsigned(fold_groups(plan)))
+        blocks = unsigned(fold_groups(plan));
     // With all-components waves and one N-tile, a last round that would
     // leave work-groups idle goes out as 32-pixel tail blocks instead:
     // every work-group takes `full` tiles, then claims one tail block (a

@@ -58,6 +58,7 @@ enum Purpose {
     kConvClaim = 7,    // the convolution's tail-block claims: zeroed once, when allocated
     kIqbnMask = 8,     // sign bits of the saved ReLU output, IQBN gradient (optional)
     kConvSplit = 9,    // partial tiles of a convolution that splits K (optional)
+    kConvFold = 11,    // folded maps, one per work-group (optional)
     kConvPad = 10      // a convolution's input padded to whole chunks (optional)
 };
 
@@ -644,9 +645,13 @@ QUAN_API int quan_qconv2d_iqbn_inference(const void *x, const void *packed, cons
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const quan::ConvPlan plan = plan_conv(stream, g, dt, quan::ConvForm::Hamilton);
-    quan::ConvFold fold{nullptr, nullptr, relu != 0, running_mean, running_var, gamma, beta, bias, eps};
+    quan::ConvFold fold{nullptr, nullptr, relu != 0, running_mean, running_var, gamma, beta, bias, eps,
+                        nullptr};
     hipError_t e;
-    if (!quan::qconv2d_folds(plan)) {
+    const size_t fb = quan::qconv2d_fold_bytes(plan, c_out);
+    if (fb > 0)
+        fold.tables = static_cast<float *>(optional_workspace(stream, kConvFold, fb));
+    if (fold.tables == nullptr && !plan.pointwise && plan.splits == 1) {
         void *work = nullptr;
         if (int rc = workspace(stream, kIqbnFold, 2 * sbytes, &work))
             return rc;

@@ -91,9 +91,10 @@ hipError_t qconv2d_pack_weights(const PackGeom &pg, int c_in, int c_out, int k_h
 // With `fold` non-NULL the epilogue applies out = scale[col] * acc +
 // shift[col] (fp32, [4][c_out] each, col = p * c_out + o) and max(0, .) when
 // relu is set, instead of adding the bias (inference IQBN folded in).  The map
-// is formed in fp64 from the statistics and parameters (fold_map), by the
-// launch itself where qconv2d_folds(plan) holds, else beforehand by
-// iqbn_fold_run into scale and shift; the launch then takes `bias` from here.
+// is formed in fp64 from the statistics and parameters (fold_map) by the
+// launch itself: where qconv2d_fold_bytes(plan, c_out) is not zero, each
+// work-group into a table of its own in `tables` (that many bytes).  With
+// scale and shift given (by iqbn_fold_run) it reads those instead.
 struct ConvFold {
     const float *scale;
     const float *shift;
@@ -101,8 +102,9 @@ struct ConvFold {
     const float *mean, *var, *gamma, *beta;  // [4][c_out]
     const void *bias;                        // [4][c_out] of the run's type, or NULL
     float eps;
+    float *tables;
 };
-bool qconv2d_folds(const ConvPlan &plan);
+size_t qconv2d_fold_bytes(const ConvPlan &plan, int c_out);
 //
 // With `poincare` (a stem layer: g.c_in == 1, bias epilogue) x is the colour
 // planes [n][3][h][w] of the input images, mapped to quaternions by eq. 4
