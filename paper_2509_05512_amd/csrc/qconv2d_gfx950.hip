@@ -364,7 +364,19 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
     constexpr int OUT_BYTES = DEFER ? NCW * OUT_WAVE : 0;
     static_assert(!DEFER || (OUT_CPR >= 2 && PPS >= 1 && (ALLP || PPS % OUT_CPR == 0)), "drain geometry");
 
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[NBUF * (A_BYTES + B_BYTES) + OUT_BYTES];
+    // Separable form, 64-channel tile: the bias of the tile's columns as floats
+    // (two tiles' worth, so that one tile's epilogue may still read its own
+    // when the next one's is written).  Loading it from memory where it is
+    // added cost a latency per channel, in registers it spills: 64 x 56 x 56,
+    // 64 -> 64, 3x3 209.5 -> 131 us (without a bias 145.8 -> 130, for the
+    // shorter epilogue).  The 32-channel tile's ring fills half of the LDS, so
+    // that two work-groups share a compute unit, and it loads from memory: lane
+    // permutes of a register copy made it 53 us with a bias (75 on 64 x 56 x 56,
+    // 32 -> 32), but 54-60 without one (51).
+    constexpr int TAB = (SEP && NB == 2) ? 4 * BNC : 0;  // floats of one tile's
+
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[NBUF * (A_BYTES + B_BYTES) + OUT_BYTES + 8 * TAB];
+    [[maybe_unused]] float *const bias_tab = reinterpret_cast<float *>(smem + NBUF * (A_BYTES + B_BYTES) + OUT_BYTES);
     unsigned char *const a_lds = smem;
     unsigned char *const b_lds = smem + NBUF * A_BYTES;
     unsigned char *const o_lds = smem + NBUF * (A_BYTES + B_BYTES);
@@ -1445,6 +1457,13 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
         const int tile = tile_of(kt);
         const int m0 = (tile / a.n_tiles) * BM;
         const int o0 = (tile % a.n_tiles) * BNC;
+        if constexpr (TAB > 0) {
+            // (read after this tile's barriers)
+            static_assert(TAB <= 64 * NCW, "one column per compute thread");
+            const int o = o0 + tid % BNC;
+            bias_tab[(kt & 1) * TAB + tid] =
+                bias != nullptr && o < a.c_out ? float(bias[tid / BNC * a.c_out + o]) : 0.0f;
+        }
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs)
 #pragma unroll
@@ -1606,7 +1625,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
 #pragma unroll
                                 for (int gh = 0; gh < 2; ++gh) {
                                     const int g = 2 * t + gh;
-                                    const int o = o0 + wn * WTN + nb * 32 + 8 * g + 4 * khalf;
+                                    const f32x4 bq = *reinterpret_cast<const f32x4 *>(
+                                        bias_tab + (kt & 1) * TAB + p * BNC + wn * WTN + nb * 32 + 8 * g + 4 * khalf);
                                     T v[4];
 #pragma unroll
                                     for (int e = 0; e < 4; ++e) {
@@ -1617,9 +1637,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + producer_waves<T, MB, NB,
                                             const float c = acc[q][nb][mb][4 * g + e];
                                             y = ((kSeparableNeg >> (4 * p + q)) & 1u) ? y - c : y + c;
                                         }
-                                        float sc, sh;
-                                        col_affine(p * a.c_out + o + e, o + e < a.c_out, sc, sh);
-                                        v[e] = T(epi(y, sc, sh));
+                                        v[e] = T(y + bq[e]);
                                     }
                                     __builtin_memcpy(h[gh], v, 8);
                                 }
