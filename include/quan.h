@@ -34,10 +34,14 @@
  * enqueued its kernels on `stream` (a hipStream_t; NULL is the default
  * stream): errors raised while they run surface at the next synchronisation.
  *
- * The library keeps a small per-(device, stream) workspace (the packed
+ * The library keeps a per-(device, stream) workspace (the packed
  * convolution weights and IQBN partial statistics), allocated with hipMalloc
  * on first use and grown on demand; quan_release() frees it.  Calls issued to
- * different streams never share a workspace.
+ * different streams never share a workspace.  Some calls are faster with a
+ * larger buffer of their own (partial tiles of a split convolution, an input
+ * padded to whole 16-byte chunks, folded maps, the sign bits of a ReLU
+ * output); they run without it where it cannot be allocated or would have to
+ * grow under graph capture, and one that a capture took stays allocated.
  */
 #ifndef QUAN_H
 #define QUAN_H

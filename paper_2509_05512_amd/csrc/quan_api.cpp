@@ -12,6 +12,7 @@
 #include <mutex>
 #include <string>
 #include <utility>
+#include <vector>
 
 #include "quan.h"
 #include "quan_launch.h"
@@ -42,6 +43,10 @@ struct Workspace {
     void *ptr = nullptr;
     size_t bytes = 0;
     unsigned uses = 0;  // calls that took it (the claim buffer's launch tags)
+    // Optional buffers: whether a captured graph may hold `ptr`, and the
+    // outgrown ones that a graph may hold, kept until quan_release.
+    bool in_graph = false;
+    std::vector<void *> retired;
 };
 
 std::mutex g_ws_mutex;
@@ -77,9 +82,13 @@ int workspace(void *stream, Purpose purpose, size_t bytes, void **out, unsigned 
             e = hipDeviceSynchronize();
             if (e != hipSuccess)
                 return fail_hip(e, "hipDeviceSynchronize");
-            e = hipFree(ws.ptr);
+            if (ws.in_graph)
+                ws.retired.push_back(ws.ptr);
+            else
+                e = hipFree(ws.ptr);
             ws.ptr = nullptr;
             ws.bytes = 0;
+            ws.in_graph = false;
             if (e != hipSuccess)
                 return fail_hip(e, "hipFree");
         }
@@ -105,23 +114,26 @@ int workspace(void *stream, Purpose purpose, size_t bytes, void **out, unsigned 
 
 // A buffer that a call is only faster with: NULL, without an error, where it
 // cannot be had: a stream under capture whose buffer would have to grow, or
-// no memory left.  The caller then takes its form without it.
+// no memory left.  The caller then takes its form without it.  A buffer that
+// a capture took stays allocated when a later call outgrows it, since the
+// graph's replays use it.
 void *optional_workspace(void *stream, Purpose purpose, size_t bytes)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess)
         return nullptr;
-    {
-        std::lock_guard<std::mutex> lock(g_ws_mutex);
-        const auto it = g_ws.find({dev, {stream, int(purpose)}});
-        if (it != g_ws.end() && it->second.bytes >= bytes)
-            return it->second.ptr;
-    }
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capturing) != hipSuccess ||
-        capturing != hipStreamCaptureStatusNone) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &status) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
+    }
+    if (status != hipStreamCaptureStatusNone) {
+        std::lock_guard<std::mutex> lock(g_ws_mutex);
+        const auto it = g_ws.find({dev, {stream, int(purpose)}});
+        if (it == g_ws.end() || it->second.bytes < bytes)
+            return nullptr;
+        it->second.in_graph = true;
+        return it->second.ptr;
     }
     void *p = nullptr;
     if (workspace(stream, purpose, bytes, &p) != QUAN_OK) {
@@ -1129,13 +1141,16 @@ QUAN_API int quan_release(void)
         saved = -1;
     for (auto &kv : g_ws) {
         Workspace &ws = kv.second;
-        if (!ws.ptr)
+        if (!ws.ptr && ws.retired.empty())
             continue;
         hipError_t e = hipSetDevice(kv.first.first);
         if (e == hipSuccess)
             e = hipDeviceSynchronize();
-        if (e == hipSuccess)
+        if (e == hipSuccess && ws.ptr)
             e = hipFree(ws.ptr);
+        for (void *p : ws.retired)
+            if (e == hipSuccess)
+                e = hipFree(p);
         if (e != hipSuccess && rc == QUAN_OK)
             rc = fail_hip(e, "quan_release");
         ws.ptr = nullptr;

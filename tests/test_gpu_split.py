@@ -124,3 +124,38 @@ def test_split_under_capture_without_warm_up():
         eager = quan.quan_qconv2d_forward_packed(xg, packed, wshape, pad=1)
         torch.cuda.synchronize()
         assert_close(f64(eager), ref, torch.bfloat16, "eager")
+
+
+def test_captured_buffer_outlives_a_larger_call():
+    """A graph captured after a warm-up holds the partial tiles' buffer; a
+    later, larger layer on the same stream takes a new one and the replays go
+    on giving the same result."""
+    say("split convolution captured, then outgrown")
+    x, w, _, _ = _inputs((1, 192, 96, 6, 7, 3, 1, 1, 1), torch.bfloat16, 9)
+    packed = quan.quan_qconv2d_pack_weights(*[w[q].contiguous().cuda() for q in range(4)])
+    xg, wshape = quan.to_device_layout(x.cuda()), tuple(w.shape[1:])
+    out = quan.empty_qmap(1, 96, 6, 7, torch.bfloat16, torch.device("cuda:0"))
+    big, wb, _, _ = _inputs((1, 256, 256, 20, 20, 3, 1, 1, 1), torch.bfloat16, 10)
+    bigg, pb = quan.to_device_layout(big.cuda()), quan.quan_qconv2d_pack_weights(*[wb[q].contiguous().cuda() for q in range(4)])
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(st):
+        eager = quan.quan_qconv2d_forward_packed(xg, packed, wshape, pad=1)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        quan.quan_qconv2d_forward_packed(xg, packed, wshape, pad=1, out=out)
+    with torch.cuda.stream(st):
+        y = quan.quan_qconv2d_forward_packed(bigg, pb, tuple(wb.shape[1:]), pad=1)
+    torch.cuda.synchronize()
+    filler = [torch.full((1 << 20,), float("nan"), device="cuda") for _ in range(8)]
+    for _ in range(3):
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
+        with torch.cuda.stream(st):
+            again = quan.quan_qconv2d_forward_packed(bigg, pb, tuple(wb.shape[1:]), pad=1)
+        torch.cuda.synchronize()
+        assert torch.equal(again, y)
+    assert all(bool(t.isnan().all()) for t in filler)
