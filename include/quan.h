@@ -37,7 +37,11 @@
  * The library keeps a per-(device, stream) workspace (the packed
  * convolution weights and IQBN partial statistics), allocated with hipMalloc
  * on first use and grown on demand; quan_release() frees it.  Calls issued to
- * different streams never share a workspace.  Some calls are faster with a
+ * different streams never share a workspace; several host threads may call on
+ * one stream, whose calls then run one after the other (each call's launches
+ * stay together).  Graphs captured from one stream hold its buffers: their
+ * replays, and that stream's calls, must not overlap in time.
+ * Some calls are faster with a
  * larger buffer of their own (partial tiles of a split convolution, an input
  * padded to whole 16-byte chunks, folded maps, the sign bits of a ReLU
  * output); they run without it where it cannot be allocated or would have to

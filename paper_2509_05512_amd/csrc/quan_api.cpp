@@ -10,6 +10,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <shared_mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -49,7 +50,7 @@ struct Workspace {
     std::vector<void *> retired;
 };
 
-std::mutex g_ws_mutex;
+std::mutex g_ws_mutex;  // of the maps
 std::map<std::pair<int, std::pair<void *, int>>, Workspace> g_ws;
 
 enum Purpose {
@@ -65,6 +66,34 @@ enum Purpose {
     kConvSplit = 9,    // partial tiles of a convolution that splits K (optional)
     kConvFold = 11,    // folded maps, one per work-group (optional)
     kConvPad = 10      // a convolution's input padded to whole chunks (optional)
+};
+
+// Held from a call's first look at the buffers of its (device, stream) to its
+// last launch: the launches of a call hand data on through buffers that every
+// call on the stream shares (packed kernels, a padded input, partial tiles,
+// statistics), so the launches of two host threads must not come between each
+// other's, nor may one call grow, and so free, a buffer that the other is about
+// to launch with.  Host work alone is serialised, and only within a stream.
+std::map<std::pair<int, void *>, std::mutex> g_stream_mutexes;  // entries stay
+std::shared_mutex g_release_mutex;                              // quan_release: alone
+
+class StreamCall {
+  public:
+    explicit StreamCall(void *stream) : running_(g_release_mutex)
+    {
+        int dev = 0;
+        (void)hipGetDevice(&dev);  // (a failure is reported by workspace())
+        std::mutex *m;
+        {
+            std::lock_guard<std::mutex> lock(g_ws_mutex);
+            m = &g_stream_mutexes[{dev, stream}];
+        }
+        lock_ = std::unique_lock<std::mutex>(*m);
+    }
+
+  private:
+    std::shared_lock<std::shared_mutex> running_;
+    std::unique_lock<std::mutex> lock_;
 };
 
 // Returns a device buffer of at least `bytes` for (current device, stream,
@@ -340,6 +369,7 @@ int iqbn_common(const void *x, const float *gamma, const float *beta, float eps,
         return rc;
     const int64_t pixels = int64_t(n) * h * w;
     const quan::DType dt = to_dt(dtype);
+    const StreamCall call(stream);
     void *work = nullptr;
     if (int rc = workspace(stream, kIqbnPartials, quan::iqbn_workspace_bytes(pixels, c), &work))
         return rc;
@@ -382,6 +412,7 @@ int conv_packed(const char *name, bool sep, const void *x, const void *packed, c
         return fail(QUAN_ERR_ALIAS, "%s: out overlaps the packed weights", name);
     const quan::DType dt = to_dt(dtype);
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
+    const StreamCall call(stream);
     const quan::ConvPlan plan =
         plan_conv(stream, g, dt, sep ? quan::ConvForm::Separable : quan::ConvForm::Hamilton);
     quan::ConvClaim claim{};
@@ -421,6 +452,7 @@ int conv_unpacked(const char *name, bool sep, const void *x, const void *w_r, co
     if (need < 0)
         return int(need);
 
+    const StreamCall call(stream);
     void *wpack = nullptr;
     if (int rc = workspace(stream, kWeightPack, size_t(need), &wpack))
         return rc;
@@ -572,6 +604,7 @@ QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const 
 
     const quan::DType dt = to_dt(dtype);
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
+    const StreamCall call(stream);
     const quan::ConvPlan plan = plan_conv(stream, g, dt, quan::ConvForm::Hamilton);
     const int64_t pixels = g.m();
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -656,6 +689,7 @@ QUAN_API int quan_qconv2d_iqbn_inference(const void *x, const void *packed, cons
     const quan::DType dt = to_dt(dtype);
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    const StreamCall call(stream);
     const quan::ConvPlan plan = plan_conv(stream, g, dt, quan::ConvForm::Hamilton);
     quan::ConvFold fold{nullptr, nullptr, relu != 0, running_mean, running_var, gamma, beta, bias, eps,
                         nullptr};
@@ -711,6 +745,7 @@ QUAN_API int quan_qconv2d_poincare_forward(const void *rgb, const void *packed, 
     // kernel with the map in its loads
     hipError_t e = quan::qconv2d_stem_run(pg, g, dt, rgb, packed, bias, out, static_cast<hipStream_t>(stream));
     if (e == hipErrorNotSupported) {
+        const StreamCall call(stream);
         quan::ConvClaim claim{};
         if (int rc = conv_claim(stream, &claim))
             return rc;
@@ -783,6 +818,7 @@ int backward_data(const char *name, bool sep, const void *dy, const void *w_r, c
     const int64_t need = quan_qconv2d_packed_bytes(c_out, c_in, k_h, k_w, dtype);
     if (need < 0)
         return int(need);
+    const StreamCall call(stream);
     void *wpack = nullptr, *stage = nullptr;
     if (int rc = workspace(stream, kGradPack, size_t(need), &wpack))
         return rc;
@@ -863,6 +899,7 @@ int backward_weight(const char *name, bool sep, const void *x, const void *dy, i
                 return fail(QUAN_ERR_ALIAS, "%s: gradients overlap each other", name);
         }
     }
+    const StreamCall call(stream);
     void *work = nullptr;
     if (int rc = workspace(stream, kWgrad, quan::qconv2d_wgrad_work_bytes(g, to_dt(dtype)), &work))
         return rc;
@@ -935,6 +972,7 @@ QUAN_API int quan_iqbn_backward(const void *x, const void *dout, const void *y, 
         overlaps(dgamma, sb, gamma, sb) || overlaps(dbeta, sb, mean, sb) || overlaps(dbeta, sb, var, sb) ||
         overlaps(dbeta, sb, gamma, sb))
         return fail(QUAN_ERR_ALIAS, "iqbn_backward: dgamma/dbeta overlap each other or the statistics");
+    const StreamCall call(stream);
     void *work = nullptr;
     const quan::DType dt = to_dt(dtype);
     if (int rc = workspace(stream, kIqbnPartials, quan::iqbn_workspace_bytes(pixels, c), &work))
@@ -1134,6 +1172,7 @@ QUAN_API const char *quan_last_error(void)
 
 QUAN_API int quan_release(void)
 {
+    std::unique_lock<std::shared_mutex> alone(g_release_mutex);
     std::lock_guard<std::mutex> lock(g_ws_mutex);
     int rc = QUAN_OK;
     int saved = -1;

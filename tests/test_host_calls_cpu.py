@@ -1,0 +1,98 @@
+"""The library's host side (plans, workspaces, launches) on a HIP runtime that
+records instead of running: no GPU needed."""
+import os
+import threading
+
+import pytest
+
+import host_calls
+from host_calls import BF16, F32
+
+
+@pytest.fixture(scope="module")
+def so(tmp_path_factory):
+    if not os.path.exists(host_calls.LIB):
+        pytest.skip("libquan.so not built")
+    return host_calls.build(tmp_path_factory.mktemp("fakehip"))
+
+
+# ---- host threads on one stream ----
+
+# (call, shape (n, c_in, h, w, c_out, k, stride, pad)): launches around a shared buffer
+SHARED = [("forward_packed", (8, 12, 20, 20, 20, 3, 1, 1)),   # a padded copy
+          ("forward_packed", (8, 20, 33, 31, 16, 3, 1, 1)),   # a larger one: the buffer grows
+          ("forward_packed", (1, 128, 7, 7, 64, 3, 1, 1)),    # partial tiles
+          ("forward_packed", (1, 256, 14, 14, 256, 3, 1, 1)),
+          ("forward", (4, 16, 16, 16, 32, 3, 1, 1)),          # packed kernels
+          ("inference", (4, 12, 16, 16, 32, 3, 1, 1)),
+          ("iqbn_layer", (16, 64, 56, 56, 64, 3, 1, 1)),      # statistics
+          ("backward_data", (4, 16, 16, 16, 32, 3, 2, 1)),
+          ("backward_weight", (4, 16, 16, 16, 32, 3, 1, 1))]
+
+
+def _threads(q, streams):
+    """Two threads, each its own order of the calls; what they launched."""
+    for name, shape in SHARED:      # each call's launches by itself
+        getattr(q, name)(shape, stream=streams[0])
+    alone = {}
+    for name, shape in SHARED:
+        q.clear()
+        getattr(q, name)(shape, stream=streams[0])
+        alone[(name, shape)] = [e.name for e in q.events() if e.what == "L"]
+    q.lib.quan_release()
+    q.clear()
+    q.fake.fake_delay(100)
+    failed = []
+
+    def run(tag):
+        try:
+            q.fake.fake_tag(tag)
+            for name, shape in (SHARED if tag == 1 else SHARED[::-1]) * 4:
+                getattr(q, name)(shape, stream=streams[tag - 1])
+        except Exception as e:  # noqa: BLE001
+            failed.append(repr(e))
+
+    threads = [threading.Thread(target=run, args=(t,)) for t in (1, 2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    return alone, q.events(), failed
+
+
+def test_calls_of_two_threads_on_one_stream_do_not_interleave(so):
+    """Calls that hand data from one launch to the next through a buffer of the
+    stream: with two threads on one stream, each call's launches stay
+    together, and a buffer that a call has taken is not freed before its last
+    launch."""
+    alone, events, failed = host_calls.in_child(_threads, so, (0, 0))
+    assert not failed, failed
+    assert all(len(v) > 1 for k, v in alone.items()), alone
+    per = {1: list(SHARED) * 4, 2: SHARED[::-1] * 4}
+    launches = [e for e in events if e.what == "L"]
+    i = 0
+    while i < len(launches):
+        tag = launches[i].tag
+        want = alone[per[tag].pop(0)]
+        got = launches[i:i + len(want)]
+        assert [(e.tag, e.name) for e in got] == [(tag, n) for n in want], f"launch {i}"
+        i += len(want)
+    assert not per[1] and not per[2]
+    # a launch whose first argument lies in a buffer finds it allocated
+    live = {}
+    for e in events:
+        if e.what == "M":
+            live[e.ptr] = e.bytes
+        elif e.what == "F":
+            del live[e.ptr]
+        elif e.what == "L" and 0x600000000000 <= e.ptr < 0x700000000000:
+            assert any(p <= e.ptr < p + b for p, b in live.items()), e
+
+
+def test_threads_on_different_streams_run_side_by_side(so):
+    """Streams have their own buffers and wait for nobody."""
+    _, events, failed = host_calls.in_child(_threads, so, (0x11, 0x22))
+    assert not failed, failed
+    tags = [e.tag for e in events if e.what == "L"]
+    changes = sum(a != b for a, b in zip(tags, tags[1:]))
+    assert changes > len(SHARED) * 8, "one thread waited for the other's calls"
