@@ -141,6 +141,17 @@ int workspace(void *stream, Purpose purpose, size_t bytes, void **out, unsigned 
     return QUAN_OK;
 }
 
+// Whether `stream` is being captured into a graph (or cannot say).
+bool capturing(void *stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return status != hipStreamCaptureStatusNone;
+}
+
 // A buffer that a call is only faster with: NULL, without an error, where it
 // cannot be had: a stream under capture whose buffer would have to grow, or
 // no memory left.  The caller then takes its form without it.  A buffer that
@@ -151,12 +162,7 @@ void *optional_workspace(void *stream, Purpose purpose, size_t bytes)
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess)
         return nullptr;
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &status) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    if (status != hipStreamCaptureStatusNone) {
+    if (capturing(stream)) {
         std::lock_guard<std::mutex> lock(g_ws_mutex);
         const auto it = g_ws.find({dev, {stream, int(purpose)}});
         if (it == g_ws.end() || it->second.bytes < bytes)
@@ -697,10 +703,16 @@ QUAN_API int quan_qconv2d_iqbn_inference(const void *x, const void *packed, cons
     const size_t fb = quan::qconv2d_fold_bytes(plan, c_out);
     if (fb > 0)
         fold.tables = static_cast<float *>(optional_workspace(stream, kConvFold, fb));
-    if (fold.tables == nullptr && !plan.pointwise && plan.splits == 1) {
-        void *work = nullptr;
+    // The one map that a call without tables reads.  Every call outside a
+    // capture sees to it, since a later one of another size or kernel may need
+    // it under capture, where it could not be had.
+    const bool one_map = fold.tables == nullptr && !plan.pointwise && plan.splits == 1;
+    void *work = nullptr;
+    if (one_map || !capturing(stream)) {
         if (int rc = workspace(stream, kIqbnFold, 2 * sbytes, &work))
             return rc;
+    }
+    if (one_map) {
         float *scale = static_cast<float *>(work), *shift = scale + size_t(4) * c_out;
         e = quan::iqbn_fold_run(running_mean, running_var, gamma, beta, bias, eps, c_out, dt, scale, shift, s);
         if (e != hipSuccess)

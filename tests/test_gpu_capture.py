@@ -1,0 +1,58 @@
+"""Graphs captured on a stream that has run the layer with another batch:
+replays, with eager work between them, equal the eager result."""
+import pytest
+import torch
+
+import oracle
+from paper_2509_05512_amd import quan
+from parity import assert_close, f64, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _maps(seed, *shape):
+    g = torch.Generator().manual_seed(seed)
+    return torch.randn(*shape, generator=g)
+
+
+def _capture(stream, fn):
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        fn()
+    return graph
+
+
+@pytest.mark.parametrize("dtype,c,o,k,warm,n", [("bf16", 32, 48, 3, 1, 6), ("bf16", 32, 48, 3, 6, 1),
+                                                ("fp32", 8, 24, 3, 1, 4), ("bf16", 64, 64, 1, 1, 5)])
+def test_inference_of_another_batch(dtype, c, o, k, warm, n):
+    say(f"capture of an inference layer {dtype} {c}->{o} k{k} batch {warm} then {n}")
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    x = _maps(1, max(n, warm), 4, c, 28, 27).to(dt)
+    w = (_maps(2, 4, o, c, k, k) * 0.1).to(dt)
+    mean, gamma, beta = _maps(3, 3, 4, o)
+    var = _maps(4, 4, o).abs() + 0.5
+    packed = quan.quan_qconv2d_pack_weights(*[w[q].contiguous().cuda() for q in range(4)])
+    params = [t.contiguous().cuda() for t in (mean, var, gamma, beta)]
+    small, xg = [quan.to_device_layout(x[:m].cuda()) for m in (warm, n)]
+    out = quan.empty_qmap(n, o, 28, 27, dt, xg.device)
+
+    def run(t, **kw):
+        return quan.quan_qconv2d_iqbn_inference(t, packed, tuple(w.shape[1:]), *params, pad=k // 2, relu=True, **kw)
+
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(st):
+        run(small)
+    torch.cuda.synchronize()
+    graph = _capture(st, lambda: run(xg, out=out))
+    ref = oracle.iqbn_inference(oracle.qconv2d(f64(x[:n]), f64(w), None, 1, k // 2, 1), f64(mean), f64(var), f64(gamma),
+                                f64(beta), 1e-5, True)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_close(f64(out), ref, dt, "replay")
+        with torch.cuda.stream(st):
+            eager = run(xg)
+        torch.cuda.synchronize()
+        assert_close(f64(eager), ref, dt, "eager")

@@ -96,3 +96,44 @@ def test_threads_on_different_streams_run_side_by_side(so):
     tags = [e.tag for e in events if e.what == "L"]
     changes = sum(a != b for a, b in zip(tags, tags[1:]))
     assert changes > len(SHARED) * 8, "one thread waited for the other's calls"
+
+
+# ---- calls under graph capture, after a warm-up on another size ----
+
+S = 0x33  # the stream
+
+
+def _captured(q, call, warm, shape, kw):
+    getattr(q, call)(warm, stream=S, **kw)
+    q.clear()
+    q.fake.fake_capture(S, 1)
+    try:
+        getattr(q, call)(shape, stream=S, **kw)
+    finally:
+        q.fake.fake_capture(S, 0)
+    return q.events()
+
+
+def check_captured(so, call, warm, shape, **kw):
+    events = host_calls.in_child(_captured, so, call, warm, shape, kw)
+    assert any(e.what == "L" for e in events)
+    assert all(e.what == "L" and e.in_capture for e in events), [e for e in events if e.what != "L"]
+
+
+ONE, FEW, MANY = (1, 64, 14, 14), (4, 64, 28, 28), (64, 64, 28, 28)
+
+
+@pytest.mark.parametrize("dtype", [BF16, F32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("k", [1, 3])
+@pytest.mark.parametrize("c_out", [32, 64, 200, 600])
+@pytest.mark.parametrize("warm,shape", [(ONE, FEW), (ONE, MANY), (FEW, MANY), (MANY, ONE), (MANY, FEW)])
+def test_inference_captured_after_another_size(so, dtype, k, c_out, warm, shape):
+    """An inference layer that has run on the stream, with any batch, is
+    captured without an allocation: whichever form the new size takes."""
+    tail = (c_out, k, 1, k // 2)
+    check_captured(so, "inference", warm + tail, shape + tail, dtype=dtype)
+
+
+def test_inference_captured_after_another_layer(so):
+    """A layer of another kernel size and as many output channels is warm-up enough."""
+    check_captured(so, "inference", (16, 64, 56, 56, 64, 1, 1, 0), (16, 64, 56, 56, 64, 3, 1, 1))
