@@ -34,18 +34,18 @@
  * enqueued its kernels on `stream` (a hipStream_t; NULL is the default
  * stream): errors raised while they run surface at the next synchronisation.
  *
- * The library keeps a per-(device, stream) workspace (the packed
- * convolution weights and IQBN partial statistics), allocated with hipMalloc
- * on first use and grown on demand; quan_release() frees it.  Calls issued to
+ * The library keeps a per-(device, stream) workspace (packed convolution
+ * weights, IQBN partial statistics and the like), allocated with hipMalloc on
+ * first use and grown on demand; quan_release() frees it.  Calls issued to
  * different streams never share a workspace; several host threads may call on
  * one stream, whose calls then run one after the other (each call's launches
- * stay together).  Graphs captured from one stream hold its buffers: their
- * replays, and that stream's calls, must not overlap in time.
- * Some calls are faster with a
- * larger buffer of their own (partial tiles of a split convolution, an input
- * padded to whole 16-byte chunks, folded maps, the sign bits of a ReLU
- * output); they run without it where it cannot be allocated or would have to
- * grow under graph capture, and one that a capture took stays allocated.
+ * stay together).  Some calls are faster with a larger buffer of their own
+ * (partial tiles of a split convolution, an input padded to whole 16-byte
+ * chunks, folded maps, the sign bits of a ReLU output); they run without it
+ * where it cannot be allocated or would have to grow under graph capture.
+ * Graphs captured from a stream hold its buffers, which stay allocated until
+ * quan_release() also when a later call outgrows them.  Replays of such graphs,
+ * and that stream's own calls, must not overlap in time.
  */
 #ifndef QUAN_H
 #define QUAN_H

@@ -44,8 +44,8 @@ struct Workspace {
     void *ptr = nullptr;
     size_t bytes = 0;
     unsigned uses = 0;  // calls that took it (the claim buffer's launch tags)
-    // Optional buffers: whether a captured graph may hold `ptr`, and the
-    // outgrown ones that a graph may hold, kept until quan_release.
+    // Whether a captured graph may hold `ptr`, and the outgrown ones that a
+    // graph may hold, kept until quan_release: its replays use them.
     bool in_graph = false;
     std::vector<void *> retired;
 };
@@ -68,44 +68,56 @@ enum Purpose {
     kConvPad = 10      // a convolution's input padded to whole chunks (optional)
 };
 
-// Held from a call's first look at the buffers of its (device, stream) to its
-// last launch: the launches of a call hand data on through buffers that every
-// call on the stream shares (packed kernels, a padded input, partial tiles,
-// statistics), so the launches of two host threads must not come between each
-// other's, nor may one call grow, and so free, a buffer that the other is about
-// to launch with.  Host work alone is serialised, and only within a stream.
+// A call on (current device, stream).  Held from its first look at the buffers
+// to its last launch: the launches of a call hand data on through buffers that
+// every call on the stream shares (packed kernels, a padded input, partial
+// tiles, statistics), so the launches of two host threads must not come between
+// each other's, nor may one call grow, and so free, a buffer that the other is
+// about to launch with.  Host work alone is serialised, and only within a
+// stream.
 std::map<std::pair<int, void *>, std::mutex> g_stream_mutexes;  // entries stay
 std::shared_mutex g_release_mutex;                              // quan_release: alone
 
 class StreamCall {
   public:
-    explicit StreamCall(void *stream) : running_(g_release_mutex)
+    explicit StreamCall(void *stream_) : stream(stream_), running_(g_release_mutex)
     {
-        int dev = 0;
-        (void)hipGetDevice(&dev);  // (a failure is reported by workspace())
+        device_error = hipGetDevice(&dev);
         std::mutex *m;
         {
             std::lock_guard<std::mutex> lock(g_ws_mutex);
             m = &g_stream_mutexes[{dev, stream}];
         }
         lock_ = std::unique_lock<std::mutex>(*m);
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &status) != hipSuccess) {
+            (void)hipGetLastError();
+            capturing = true;
+        } else {
+            capturing = status != hipStreamCaptureStatusNone;
+        }
     }
+
+    void *const stream;
+    int dev = 0;
+    hipError_t device_error;
+    bool capturing;  // into a graph (or the runtime cannot say)
 
   private:
     std::shared_lock<std::shared_mutex> running_;
     std::unique_lock<std::mutex> lock_;
 };
 
-// Returns a device buffer of at least `bytes` for (current device, stream,
-// purpose).  Growing it first waits for the device to finish with the old one.
-int workspace(void *stream, Purpose purpose, size_t bytes, void **out, unsigned *uses = nullptr)
+// Returns a device buffer of at least `bytes` for (device, stream, purpose).
+// Growing it first waits for the device to finish with the old one, which is
+// freed, or kept where a captured graph may hold it.
+int workspace(const StreamCall &call, Purpose purpose, size_t bytes, void **out, unsigned *uses = nullptr)
 {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess)
-        return fail_hip(e, "hipGetDevice");
+    if (call.device_error != hipSuccess)
+        return fail_hip(call.device_error, "hipGetDevice");
+    hipError_t e;
     std::lock_guard<std::mutex> lock(g_ws_mutex);
-    Workspace &ws = g_ws[{dev, {stream, int(purpose)}}];
+    Workspace &ws = g_ws[{call.dev, {call.stream, int(purpose)}}];
     if (ws.bytes < bytes) {
         if (ws.ptr) {
             e = hipDeviceSynchronize();
@@ -130,48 +142,31 @@ int workspace(void *stream, Purpose purpose, size_t bytes, void **out, unsigned 
         }
         ws.bytes = want;
         if (purpose == kIqbnBarrier || purpose == kConvClaim) {
-            e = hipMemsetAsync(ws.ptr, 0, want, static_cast<hipStream_t>(stream));
+            e = hipMemsetAsync(ws.ptr, 0, want, static_cast<hipStream_t>(call.stream));
             if (e != hipSuccess)
                 return fail_hip(e, "hipMemsetAsync (barrier flags, claim counter)");
         }
     }
     *out = ws.ptr;
+    ws.in_graph = ws.in_graph || call.capturing;
     if (uses != nullptr)
         *uses = ws.uses++;
     return QUAN_OK;
 }
 
-// Whether `stream` is being captured into a graph (or cannot say).
-bool capturing(void *stream)
-{
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &status) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
-    }
-    return status != hipStreamCaptureStatusNone;
-}
-
 // A buffer that a call is only faster with: NULL, without an error, where it
 // cannot be had: a stream under capture whose buffer would have to grow, or
-// no memory left.  The caller then takes its form without it.  A buffer that
-// a capture took stays allocated when a later call outgrows it, since the
-// graph's replays use it.
-void *optional_workspace(void *stream, Purpose purpose, size_t bytes)
+// no memory left.  The caller then takes its form without it.
+void *optional_workspace(const StreamCall &call, Purpose purpose, size_t bytes)
 {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess)
-        return nullptr;
-    if (capturing(stream)) {
+    if (call.capturing) {
         std::lock_guard<std::mutex> lock(g_ws_mutex);
-        const auto it = g_ws.find({dev, {stream, int(purpose)}});
+        const auto it = g_ws.find({call.dev, {call.stream, int(purpose)}});
         if (it == g_ws.end() || it->second.bytes < bytes)
             return nullptr;
-        it->second.in_graph = true;
-        return it->second.ptr;
     }
     void *p = nullptr;
-    if (workspace(stream, purpose, bytes, &p) != QUAN_OK) {
+    if (workspace(call, purpose, bytes, &p) != QUAN_OK) {
         g_last_error.clear();
         (void)hipGetLastError();
         return nullptr;
@@ -180,10 +175,10 @@ void *optional_workspace(void *stream, Purpose purpose, size_t bytes)
 }
 
 // The grid-barrier flags of the one-launch IQBN on this (device, stream).
-int iqbn_flags(void *stream, unsigned **out)
+int iqbn_flags(const StreamCall &call, unsigned **out)
 {
     void *p = nullptr;
-    if (int rc = workspace(stream, kIqbnBarrier, quan::iqbn_barrier_bytes(), &p))
+    if (int rc = workspace(call, kIqbnBarrier, quan::iqbn_barrier_bytes(), &p))
         return rc;
     *out = static_cast<unsigned *>(p);
     return QUAN_OK;
@@ -191,11 +186,11 @@ int iqbn_flags(void *stream, unsigned **out)
 
 // The claim counter and mailboxes of the convolution's tail blocks on this
 // (device, stream): every launch leaves the counter zero.
-int conv_claim(void *stream, quan::ConvClaim *out)
+int conv_claim(const StreamCall &call, quan::ConvClaim *out)
 {
     void *p = nullptr;
     unsigned uses = 0;
-    if (int rc = workspace(stream, kConvClaim, quan::qconv2d_claim_bytes(), &p, &uses))
+    if (int rc = workspace(call, kConvClaim, quan::qconv2d_claim_bytes(), &p, &uses))
         return rc;
     out->buf = static_cast<unsigned *>(p);
     // each call's launches (up to 16 output phases of an input gradient)
@@ -206,16 +201,16 @@ int conv_claim(void *stream, quan::ConvClaim *out)
 
 // The plan of a convolution on this stream, split over K where that pays and
 // the partial tiles can be had.
-quan::ConvPlan plan_conv(void *stream, const quan::ConvGeom &g, quan::DType dt, quan::ConvForm form)
+quan::ConvPlan plan_conv(const StreamCall &call, const quan::ConvGeom &g, quan::DType dt, quan::ConvForm form)
 {
     quan::ConvPlan plan = quan::qconv2d_plan(g, dt, form, true);
     if (plan.splits > 1) {
-        plan.part = static_cast<float *>(optional_workspace(stream, kConvSplit, quan::qconv2d_split_bytes(plan)));
+        plan.part = static_cast<float *>(optional_workspace(call, kConvSplit, quan::qconv2d_split_bytes(plan)));
         if (plan.part == nullptr)
             plan = quan::qconv2d_plan(g, dt, form);
     }
     if (const size_t pb = quan::qconv2d_pad_bytes(g, dt))
-        plan.pad = optional_workspace(stream, kConvPad, pb);
+        plan.pad = optional_workspace(call, kConvPad, pb);
     return plan;
 }
 
@@ -377,10 +372,10 @@ int iqbn_common(const void *x, const float *gamma, const float *beta, float eps,
     const quan::DType dt = to_dt(dtype);
     const StreamCall call(stream);
     void *work = nullptr;
-    if (int rc = workspace(stream, kIqbnPartials, quan::iqbn_workspace_bytes(pixels, c), &work))
+    if (int rc = workspace(call, kIqbnPartials, quan::iqbn_workspace_bytes(pixels, c), &work))
         return rc;
     unsigned *flags = nullptr;
-    if (int rc = iqbn_flags(stream, &flags))
+    if (int rc = iqbn_flags(call, &flags))
         return rc;
     hipError_t e = quan::iqbn_run(x, gamma, beta, eps, relu, out, mean, var, pixels, c, dt, work, flags,
                                   static_cast<hipStream_t>(stream));
@@ -420,9 +415,9 @@ int conv_packed(const char *name, bool sep, const void *x, const void *packed, c
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
     const StreamCall call(stream);
     const quan::ConvPlan plan =
-        plan_conv(stream, g, dt, sep ? quan::ConvForm::Separable : quan::ConvForm::Hamilton);
+        plan_conv(call, g, dt, sep ? quan::ConvForm::Separable : quan::ConvForm::Hamilton);
     quan::ConvClaim claim{};
-    if (int rc = conv_claim(stream, &claim))
+    if (int rc = conv_claim(call, &claim))
         return rc;
     hipError_t e = quan::qconv2d_run(plan, pg, g, dt, x, packed, bias, out, nullptr, nullptr,
                                      static_cast<hipStream_t>(stream), false, &claim);
@@ -460,7 +455,7 @@ int conv_unpacked(const char *name, bool sep, const void *x, const void *w_r, co
 
     const StreamCall call(stream);
     void *wpack = nullptr;
-    if (int rc = workspace(stream, kWeightPack, size_t(need), &wpack))
+    if (int rc = workspace(call, kWeightPack, size_t(need), &wpack))
         return rc;
     const quan::DType dt = to_dt(dtype);
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
@@ -470,9 +465,9 @@ int conv_unpacked(const char *name, bool sep, const void *x, const void *w_r, co
     if (e != hipSuccess)
         return fail_hip(e, "qconv2d weight pack launch");
     quan::ConvClaim claim{};
-    if (int rc = conv_claim(stream, &claim))
+    if (int rc = conv_claim(call, &claim))
         return rc;
-    e = quan::qconv2d_run(plan_conv(stream, g, dt, sep ? quan::ConvForm::Separable : quan::ConvForm::Hamilton), pg, g,
+    e = quan::qconv2d_run(plan_conv(call, g, dt, sep ? quan::ConvForm::Separable : quan::ConvForm::Hamilton), pg, g,
                           dt, x, wpack, bias, out, nullptr, nullptr, s, false, &claim);
     if (e != hipSuccess)
         return fail_hip(e, "qconv2d launch");
@@ -611,12 +606,12 @@ QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const 
     const quan::DType dt = to_dt(dtype);
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
     const StreamCall call(stream);
-    const quan::ConvPlan plan = plan_conv(stream, g, dt, quan::ConvForm::Hamilton);
+    const quan::ConvPlan plan = plan_conv(call, g, dt, quan::ConvForm::Hamilton);
     const int64_t pixels = g.m();
     hipStream_t s = static_cast<hipStream_t>(stream);
     void *work = nullptr;
     quan::ConvClaim claim{};
-    if (int rc = conv_claim(stream, &claim))
+    if (int rc = conv_claim(call, &claim))
         return rc;
     hipError_t e;
     // AUTO: an IQBN pass after the plain convolution where the tensor takes
@@ -633,7 +628,7 @@ QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const 
     const bool epilogue = stats == QUAN_STATS_EPILOGUE || (stats == QUAN_STATS_AUTO && !pass);
     if (epilogue && quan::qconv2d_writes_stats(plan, g, dt)) {
         // statistics gathered in the convolution's epilogue
-        if (int rc = workspace(stream, kIqbnPartials, quan::iqbn_tile_stats_bytes(plan.stat_tiles, c_out), &work))
+        if (int rc = workspace(call, kIqbnPartials, quan::iqbn_tile_stats_bytes(plan.stat_tiles, c_out), &work))
             return rc;
         e = quan::qconv2d_run(plan, pg, g, dt, x, packed, bias, out, static_cast<float *>(work), nullptr, s, false,
                               &claim);
@@ -642,10 +637,10 @@ QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const 
         e = quan::iqbn_from_tiles_run(static_cast<const float *>(work), plan.stat_tiles, plan.stat_rows, gamma,
                                       beta, eps, relu != 0, out, mean, var, pixels, c_out, dt, s);
     } else {
-        if (int rc = workspace(stream, kIqbnPartials, quan::iqbn_workspace_bytes(pixels, c_out), &work))
+        if (int rc = workspace(call, kIqbnPartials, quan::iqbn_workspace_bytes(pixels, c_out), &work))
             return rc;
         unsigned *flags = nullptr;
-        if (int rc = iqbn_flags(stream, &flags))
+        if (int rc = iqbn_flags(call, &flags))
             return rc;
         e = quan::qconv2d_run(plan, pg, g, dt, x, packed, bias, out, nullptr, nullptr, s, false, &claim);
         if (e != hipSuccess)
@@ -696,20 +691,20 @@ QUAN_API int quan_qconv2d_iqbn_inference(const void *x, const void *packed, cons
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const StreamCall call(stream);
-    const quan::ConvPlan plan = plan_conv(stream, g, dt, quan::ConvForm::Hamilton);
+    const quan::ConvPlan plan = plan_conv(call, g, dt, quan::ConvForm::Hamilton);
     quan::ConvFold fold{nullptr, nullptr, relu != 0, running_mean, running_var, gamma, beta, bias, eps,
                         nullptr};
     hipError_t e;
     const size_t fb = quan::qconv2d_fold_bytes(plan, c_out);
     if (fb > 0)
-        fold.tables = static_cast<float *>(optional_workspace(stream, kConvFold, fb));
+        fold.tables = static_cast<float *>(optional_workspace(call, kConvFold, fb));
     // The one map that a call without tables reads.  Every call outside a
     // capture sees to it, since a later one of another size or kernel may need
     // it under capture, where it could not be had.
     const bool one_map = fold.tables == nullptr && !plan.pointwise && plan.splits == 1;
     void *work = nullptr;
-    if (one_map || !capturing(stream)) {
-        if (int rc = workspace(stream, kIqbnFold, 2 * sbytes, &work))
+    if (one_map || !call.capturing) {
+        if (int rc = workspace(call, kIqbnFold, 2 * sbytes, &work))
             return rc;
     }
     if (one_map) {
@@ -721,7 +716,7 @@ QUAN_API int quan_qconv2d_iqbn_inference(const void *x, const void *packed, cons
         fold.shift = shift;
     }
     quan::ConvClaim claim{};
-    if (int rc = conv_claim(stream, &claim))
+    if (int rc = conv_claim(call, &claim))
         return rc;
     e = quan::qconv2d_run(plan, pg, g, dt, x, packed, bias, out, nullptr, &fold, s, false, &claim);
     if (e != hipSuccess)
@@ -759,7 +754,7 @@ QUAN_API int quan_qconv2d_poincare_forward(const void *rgb, const void *packed, 
     if (e == hipErrorNotSupported) {
         const StreamCall call(stream);
         quan::ConvClaim claim{};
-        if (int rc = conv_claim(stream, &claim))
+        if (int rc = conv_claim(call, &claim))
             return rc;
         e = quan::qconv2d_run(quan::qconv2d_plan(g, dt, quan::ConvForm::Hamilton), pg, g, dt, rgb, packed, bias, out,
                               nullptr, nullptr, static_cast<hipStream_t>(stream), true, &claim);
@@ -832,22 +827,22 @@ int backward_data(const char *name, bool sep, const void *dy, const void *w_r, c
         return int(need);
     const StreamCall call(stream);
     void *wpack = nullptr, *stage = nullptr;
-    if (int rc = workspace(stream, kGradPack, size_t(need), &wpack))
+    if (int rc = workspace(call, kGradPack, size_t(need), &wpack))
         return rc;
     const size_t sb = quan::qconv2d_grad_data_stage_bytes(g, dt);
     if (sb > 0) {
-        if (int rc = workspace(stream, kGradStage, sb, &stage))
+        if (int rc = workspace(call, kGradStage, sb, &stage))
             return rc;
     }
     quan::ConvClaim claim{};
-    if (int rc = conv_claim(stream, &claim))
+    if (int rc = conv_claim(call, &claim))
         return rc;
     size_t pb = quan::qconv2d_grad_data_split_bytes(g, dt, sep);
-    void *part = pb > 0 ? optional_workspace(stream, kConvSplit, pb) : nullptr;
+    void *part = pb > 0 ? optional_workspace(call, kConvSplit, pb) : nullptr;
     if (part == nullptr)
         pb = 0;
     const size_t db = quan::qconv2d_grad_data_pad_bytes(g, dt);
-    void *pad = db > 0 ? optional_workspace(stream, kConvPad, db) : nullptr;
+    void *pad = db > 0 ? optional_workspace(call, kConvPad, db) : nullptr;
     const hipError_t e = quan::qconv2d_backward_data_run(g, dt, dy, w_r, w_i, w_j, w_k, dx, wpack, stage,
                                                          static_cast<hipStream_t>(stream), sep, &claim, part, pb,
                                                          pad);
@@ -913,7 +908,7 @@ int backward_weight(const char *name, bool sep, const void *x, const void *dy, i
     }
     const StreamCall call(stream);
     void *work = nullptr;
-    if (int rc = workspace(stream, kWgrad, quan::qconv2d_wgrad_work_bytes(g, to_dt(dtype)), &work))
+    if (int rc = workspace(call, kWgrad, quan::qconv2d_wgrad_work_bytes(g, to_dt(dtype)), &work))
         return rc;
     const hipError_t e = quan::qconv2d_backward_weight_run(g, to_dt(dtype), x, dy, dw_r, dw_i, dw_j, dw_k, db, work,
                                                            static_cast<hipStream_t>(stream), sep);
@@ -987,10 +982,10 @@ QUAN_API int quan_iqbn_backward(const void *x, const void *dout, const void *y, 
     const StreamCall call(stream);
     void *work = nullptr;
     const quan::DType dt = to_dt(dtype);
-    if (int rc = workspace(stream, kIqbnPartials, quan::iqbn_workspace_bytes(pixels, c), &work))
+    if (int rc = workspace(call, kIqbnPartials, quan::iqbn_workspace_bytes(pixels, c), &work))
         return rc;
     const size_t mb = y != nullptr ? quan::iqbn_mask_bytes(pixels, c, dt) : 0;
-    void *mask = mb > 0 ? optional_workspace(stream, kIqbnMask, mb) : nullptr;
+    void *mask = mb > 0 ? optional_workspace(call, kIqbnMask, mb) : nullptr;
     const hipError_t e = quan::iqbn_backward_run(x, dout, y, mean, var, gamma, eps, dx, dgamma, dbeta, pixels, c, dt,
                                                  work, static_cast<unsigned char *>(mask),
                                                  static_cast<hipStream_t>(stream));

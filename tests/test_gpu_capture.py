@@ -56,3 +56,35 @@ def test_inference_of_another_batch(dtype, c, o, k, warm, n):
             eager = run(xg)
         torch.cuda.synchronize()
         assert_close(f64(eager), ref, dt, "eager")
+
+
+def test_weight_gradient_captured_then_outgrown():
+    """The partial sums' buffer of a captured weight gradient outlives a larger
+    layer's call on the stream."""
+    say("capture of a weight gradient, then a larger call")
+    bf = torch.bfloat16
+    x, dy = [quan.to_device_layout(_maps(i, 4, 4, 16, 20, 21).to(bf).cuda()) for i in (1, 2)]
+    bx, bdy = [quan.to_device_layout(_maps(i, 4, 4, 128, 30, 30).to(bf).cuda()) for i in (3, 4)]
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(st):
+        want, wb = quan.quan_qconv2d_backward_weight(x, dy, (3, 3), pad=1)
+    torch.cuda.synchronize()
+    held = []
+    graph = _capture(st, lambda: held.append(quan.quan_qconv2d_backward_weight(x, dy, (3, 3), pad=1)))
+    with torch.cuda.stream(st):
+        big, _ = quan.quan_qconv2d_backward_weight(bx, bdy, (3, 3), pad=1)
+    torch.cuda.synchronize()
+    filler = [torch.full((1 << 20,), float("nan"), device="cuda") for _ in range(16)]
+    for _ in range(3):
+        dw, db = held[0]
+        for t in (*dw, db):
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((*dw, db), (*want, wb)))
+        with torch.cuda.stream(st):
+            again, _ = quan.quan_qconv2d_backward_weight(bx, bdy, (3, 3), pad=1)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(again, big))
+    assert all(bool(t.isnan().all()) for t in filler)

@@ -137,3 +137,43 @@ def test_inference_captured_after_another_size(so, dtype, k, c_out, warm, shape)
 def test_inference_captured_after_another_layer(so):
     """A layer of another kernel size and as many output channels is warm-up enough."""
     check_captured(so, "inference", (16, 64, 56, 56, 64, 1, 1, 0), (16, 64, 56, 56, 64, 3, 1, 1))
+
+
+# ---- buffers that a captured graph holds ----
+
+# (call, captured, the larger call after it)
+OUTGROWN = [("forward", (2, 16, 12, 12, 16, 3, 1, 1), (2, 128, 12, 12, 128, 3, 1, 1)),       # packed kernels
+            ("forward_packed", (1, 128, 7, 7, 64, 3, 1, 1), (1, 256, 14, 14, 256, 3, 1, 1)),  # partial tiles
+            ("forward_packed", (2, 12, 20, 20, 16, 3, 1, 1), (8, 12, 40, 40, 16, 3, 1, 1)),   # a padded copy
+            ("backward_data", (2, 16, 12, 12, 16, 3, 1, 1), (2, 128, 12, 12, 128, 3, 1, 1)),  # packed kernels
+            ("backward_weight", (8, 16, 32, 32, 16, 3, 1, 1), (8, 128, 32, 32, 128, 3, 1, 1)),
+            ("inference", (16, 64, 28, 28, 64, 3, 1, 1), (16, 64, 28, 28, 128, 3, 1, 1)),     # folded maps
+            ("iqbn_layer", (2, 64, 12, 12, 64, 3, 1, 1), (16, 64, 56, 56, 512, 1, 1, 0)),     # statistics
+            ("iqbn", (2, 64, 40, 40), (16, 512, 56, 56)),
+            ("iqbn_backward", (2, 64, 40, 40), (16, 512, 56, 56))]
+
+
+def _outgrown(q, call, shape, larger):
+    getattr(q, call)(*(shape if call in FLAT else (shape,)), stream=S)
+    q.fake.fake_capture(S, 1)
+    getattr(q, call)(*(shape if call in FLAT else (shape,)), stream=S)
+    q.fake.fake_capture(S, 0)
+    q.clear()
+    getattr(q, call)(*(larger if call in FLAT else (larger,)), stream=S)
+    grown = q.events()
+    q.clear()
+    q._ok(q.lib.quan_release())
+    return grown, q.events()
+
+
+FLAT = ("iqbn", "iqbn_backward")
+
+
+@pytest.mark.parametrize("call,shape,larger", OUTGROWN, ids=[f"{c}-{s}" for c, s, _ in OUTGROWN])
+def test_captured_buffers_outlive_a_larger_call(so, call, shape, larger):
+    """Whatever buffer a captured call took, its replays still find it after a
+    larger call on the stream; quan_release gives all of them back."""
+    grown, released = host_calls.in_child(_outgrown, so, call, shape, larger)
+    assert any(e.what == "M" for e in grown), "the larger call grew nothing"
+    assert not [e for e in grown if e.what == "F"]
+    assert len([e for e in released if e.what == "F"]) > len([e for e in grown if e.what == "M"])
