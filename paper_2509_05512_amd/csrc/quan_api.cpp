@@ -5,6 +5,7 @@
 // asynchronously on the caller's stream.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -626,10 +627,27 @@ QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const 
     const bool big = pixels * 4 * c_out * int64_t(elem_size(dtype)) >= kPassMinBytes;
     const bool pass = (big && quan::iqbn_one_launch(pixels, c_out, dt)) || quan::iqbn_merged(pixels, c_out, dt);
     const bool epilogue = stats == QUAN_STATS_EPILOGUE || (stats == QUAN_STATS_AUTO && !pass);
-    if (epilogue && quan::qconv2d_writes_stats(plan, g, dt)) {
-        // statistics gathered in the convolution's epilogue
-        if (int rc = workspace(call, kIqbnPartials, quan::iqbn_tile_stats_bytes(plan.stat_tiles, c_out), &work))
+    const bool in_epilogue = epilogue && quan::qconv2d_writes_stats(plan, g, dt);
+    // Outside a capture a call sees to the buffers of both forms, since a later
+    // one of another batch may take the other form under capture, where they
+    // could not be had.
+    const bool both = !call.capturing;
+    size_t bytes = 0;
+    if (in_epilogue || both) {
+        const quan::ConvPlan whole = plan.splits == 1 ? plan : quan::qconv2d_plan(g, dt, quan::ConvForm::Hamilton);
+        if (quan::qconv2d_writes_stats(whole, g, dt))
+            bytes = quan::iqbn_tile_stats_bytes(whole.stat_tiles, c_out);
+    }
+    unsigned *flags = nullptr;
+    if (!in_epilogue || both) {
+        bytes = std::max(bytes, quan::iqbn_workspace_bytes(pixels, c_out));
+        if (int rc = iqbn_flags(call, &flags))
             return rc;
+    }
+    if (int rc = workspace(call, kIqbnPartials, bytes, &work))
+        return rc;
+    if (in_epilogue) {
+        // statistics gathered in the convolution's epilogue
         e = quan::qconv2d_run(plan, pg, g, dt, x, packed, bias, out, static_cast<float *>(work), nullptr, s, false,
                               &claim);
         if (e != hipSuccess)
@@ -637,11 +655,6 @@ QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const 
         e = quan::iqbn_from_tiles_run(static_cast<const float *>(work), plan.stat_tiles, plan.stat_rows, gamma,
                                       beta, eps, relu != 0, out, mean, var, pixels, c_out, dt, s);
     } else {
-        if (int rc = workspace(call, kIqbnPartials, quan::iqbn_workspace_bytes(pixels, c_out), &work))
-            return rc;
-        unsigned *flags = nullptr;
-        if (int rc = iqbn_flags(call, &flags))
-            return rc;
         e = quan::qconv2d_run(plan, pg, g, dt, x, packed, bias, out, nullptr, nullptr, s, false, &claim);
         if (e != hipSuccess)
             return fail_hip(e, "qconv2d launch");

@@ -177,3 +177,43 @@ def test_captured_buffers_outlive_a_larger_call(so, call, shape, larger):
     assert any(e.what == "M" for e in grown), "the larger call grew nothing"
     assert not [e for e in grown if e.what == "F"]
     assert len([e for e in released if e.what == "F"]) > len([e for e in grown if e.what == "M"])
+
+
+# ---- captures of a smaller batch than the stream has run ----
+
+def _smaller(q, cases):
+    """The cases whose capture allocated or failed."""
+    bad = []
+    for i, (call, shape, batch, kw) in enumerate(cases):
+        stream = 0x1000 + 16 * i
+
+        def go(n):
+            args = (n, *shape) if call in FLAT else ((n, *shape),)
+            getattr(q, call)(*args, stream=stream, **kw)
+
+        go(batch[0])
+        q.clear()
+        q.fake.fake_capture(stream, 1)
+        try:
+            go(batch[1])
+        except RuntimeError as e:
+            bad.append((call, shape, batch, kw, str(e)))
+        q.fake.fake_capture(stream, 0)
+        q.fake.hipGetLastError()
+        bad += [(call, shape, batch, kw, e.what) for e in q.events() if e.what != "L"]
+    return bad
+
+
+BATCHES = [(64, 4), (64, 1), (8, 1), (8, 5), (4, 3), (16, 5), (3, 2), (1, 1)]
+
+
+@pytest.mark.parametrize("stats", [0, 1, 2], ids=["auto", "epilogue", "pass"])
+@pytest.mark.parametrize("dtype", [BF16, F32], ids=["bf16", "fp32"])
+def test_training_layer_captured_on_a_smaller_batch(so, dtype, stats):
+    """A convolution with IQBN behind it that has run on the stream is captured
+    with any smaller batch without an allocation, whichever place its
+    statistics then come from."""
+    layers = [(20, 8, 8, 8, 3, 1, 1), (48, 32, 32, 32, 3, 2, 1), (32, 16, 16, 32, 3, 1, 1), (64, 28, 28, 64, 3, 1, 1),
+              (256, 14, 14, 256, 3, 1, 1), (400, 8, 8, 32, 3, 1, 1), (64, 28, 28, 128, 1, 1, 0), (16, 32, 32, 16, 5, 1, 2)]
+    cases = [("iqbn_layer", s, b, dict(dtype=dtype, stats=stats)) for s in layers for b in BATCHES]
+    assert host_calls.in_child(_smaller, so, cases) == []
