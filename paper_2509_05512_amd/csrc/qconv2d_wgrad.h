@@ -24,6 +24,7 @@ struct WgradRows {
     int rh, ksteps;  // rows and MFMA K steps of a chunk
     int x_pos, step; // window positions of a row, from one pixel to the next
     int chunks, per_split, splits;
+    int most_splits;  // of this layer with this many images or fewer
     int kx_groups, o_tiles, c_tiles;
 };
 WgradRows qconv2d_wgrad_rows_plan(const ConvGeom &g, DType dt);

@@ -29,6 +29,7 @@
 // gradient is the column sum of dY.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <type_traits>
 
@@ -662,6 +663,7 @@ constexpr int kBiasBlocks = 512;
 struct WPlan {
     int wo, wc;  // channel blocks of 32 per tile
     int o_tiles, c_tiles, taps, splits;
+    int64_t most_splits;  // of this layer with this many images or fewer
     int64_t per_split;
 };
 
@@ -686,6 +688,7 @@ WPlan wgrad_plan(const ConvGeom &g)
         splits = max_splits;
     if (splits < 1)
         splits = 1;
+    p.most_splits = splits;  // (grows with the pixels, where the rounded p.splits may not)
     p.per_split = (pixels + splits - 1) / splits;
     const int chunk = p.wo * p.wc == 1 ? 2 * kChunk : kChunk;
     p.per_split = (p.per_split + chunk - 1) / chunk * chunk;
@@ -697,12 +700,15 @@ WPlan wgrad_plan(const ConvGeom &g)
 
 size_t qconv2d_wgrad_work_bytes(const ConvGeom &g, DType dt)
 {
+    // Enough for every smaller batch of the layer too, so that one that has run
+    // can be captured with fewer images: a row plan's room also where only its
+    // 32-bit spans refused it.
     const WgradRows r = qconv2d_wgrad_rows_plan(g, dt);
-    const size_t slices = r.takes ? r.splits * r.segs : wgrad_plan(g).splits;
-    const size_t dw_part =
-        slices * g.k_h * g.k_w * (r.takes && !r.fold ? 16 : 4) * g.c_out * g.c_in * sizeof(float);
+    const size_t dw = size_t(g.k_h) * g.k_w * g.c_out * g.c_in * sizeof(float);
+    const size_t rows = size_t(r.most_splits) * r.segs * (r.fold ? 4 : 16) * dw;
+    const size_t tiles = r.takes ? 0 : size_t(wgrad_plan(g).most_splits) * 4 * dw;
     const size_t b_part = size_t(kBiasBlocks) * 4 * g.c_out * sizeof(float);
-    return dw_part > b_part ? dw_part : b_part;
+    return std::max(std::max(rows, tiles), b_part);
 }
 
 hipError_t qconv2d_backward_weight_run(const ConvGeom &g, DType dt, const void *x, const void *dy, float *dw_r,

@@ -603,6 +603,7 @@ WgradRows qconv2d_wgrad_rows_plan(const ConvGeom &g, DType dt)
     const int most = (p.chunks + 1) / 2;
     splits = splits > most ? most : splits;
     splits = splits < 1 ? 1 : splits;
+    p.most_splits = splits;  // (grows with the chunks, where the rounded p.splits may not)
     p.per_split = ceil_div(p.chunks, splits);
     p.splits = ceil_div(p.chunks, p.per_split);
     // 32-bit offsets within a slice

@@ -127,3 +127,30 @@ def test_training_layer_of_a_smaller_batch():
         with torch.cuda.stream(st):
             run(big)
         torch.cuda.synchronize()
+
+
+def test_weight_gradient_of_a_smaller_batch():
+    """More slices for 3 images than for 4: the stream that has run 4 is
+    captured with 3."""
+    say("capture of a weight gradient, batch 4 then 3")
+    bf = torch.bfloat16
+    x, dy = [quan.to_device_layout(_maps(i, 4, 4, c, 32, 32).to(bf).cuda()) for i, c in ((1, 32), (2, 8))]
+    xs, dys = x[:3], dy[:3]
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    want, wb = quan.quan_qconv2d_backward_weight(xs, dys, (3, 3), pad=1)
+    with torch.cuda.stream(st):
+        quan.quan_qconv2d_backward_weight(x, dy, (3, 3), pad=1)
+    torch.cuda.synchronize()
+    held = []
+    graph = _capture(st, lambda: held.append(quan.quan_qconv2d_backward_weight(xs, dys, (3, 3), pad=1)))
+    for _ in range(3):
+        dw, db = held[0]
+        for t in (*dw, db):
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((*dw, db), (*want, wb)))
+        with torch.cuda.stream(st):
+            quan.quan_qconv2d_backward_weight(x, dy, (3, 3), pad=1)
+        torch.cuda.synchronize()

@@ -217,3 +217,14 @@ def test_training_layer_captured_on_a_smaller_batch(so, dtype, stats):
               (256, 14, 14, 256, 3, 1, 1), (400, 8, 8, 32, 3, 1, 1), (64, 28, 28, 128, 1, 1, 0), (16, 32, 32, 16, 5, 1, 2)]
     cases = [("iqbn_layer", s, b, dict(dtype=dtype, stats=stats)) for s in layers for b in BATCHES]
     assert host_calls.in_child(_smaller, so, cases) == []
+
+
+@pytest.mark.parametrize("dtype", [BF16, F32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("call", ["backward_weight", "backward_data", "forward", "iqbn", "iqbn_backward"])
+def test_other_calls_captured_on_a_smaller_batch(so, call, dtype):
+    """So are the other calls that need a buffer."""
+    sizes = [(c, h, w) for c in (1, 12, 16, 32, 48, 69, 128) for h, w in ((32, 32), (14, 14), (9, 11), (5, 40))]
+    layers = sizes if call in FLAT else [(c, h, w, o, k, s, k // 2) for c, h, w in sizes for o in (8, 16, 20, 70)
+                                         for k, s in ((1, 1), (3, 1), (3, 2), (5, 1))]
+    cases = [(call, s, b, dict(dtype=dtype)) for s in layers for b in BATCHES]
+    assert host_calls.in_child(_smaller, so, cases) == []
