@@ -201,10 +201,11 @@ int conv_claim(const StreamCall &call, quan::ConvClaim *out)
 }
 
 // The plan of a convolution on this stream, split over K where that pays and
-// the partial tiles can be had.
-quan::ConvPlan plan_conv(const StreamCall &call, const quan::ConvGeom &g, quan::DType dt, quan::ConvForm form)
+// the partial tiles can be had (split false: whole).
+quan::ConvPlan plan_conv(const StreamCall &call, const quan::ConvGeom &g, quan::DType dt, quan::ConvForm form,
+                         bool split = true)
 {
-    quan::ConvPlan plan = quan::qconv2d_plan(g, dt, form, true);
+    quan::ConvPlan plan = quan::qconv2d_plan(g, dt, form, split);
     if (plan.splits > 1) {
         plan.part = static_cast<float *>(optional_workspace(call, kConvSplit, quan::qconv2d_split_bytes(plan)));
         if (plan.part == nullptr)
@@ -607,7 +608,12 @@ QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const 
     const quan::DType dt = to_dt(dtype);
     const quan::PackGeom pg = quan::qconv2d_pack_geom(c_in, c_out, k_h, k_w, dt);
     const StreamCall call(stream);
-    const quan::ConvPlan plan = plan_conv(call, g, dt, quan::ConvForm::Hamilton);
+    // (a split convolution has no epilogue that could gather the statistics a
+    // caller asks for there)
+    const quan::ConvPlan whole = quan::qconv2d_plan(g, dt, quan::ConvForm::Hamilton);
+    const bool whole_stats = quan::qconv2d_writes_stats(whole, g, dt);
+    const quan::ConvPlan plan =
+        plan_conv(call, g, dt, quan::ConvForm::Hamilton, stats != QUAN_STATS_EPILOGUE || !whole_stats);
     const int64_t pixels = g.m();
     hipStream_t s = static_cast<hipStream_t>(stream);
     void *work = nullptr;
@@ -633,11 +639,8 @@ QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const 
     // could not be had.
     const bool both = !call.capturing;
     size_t bytes = 0;
-    if (in_epilogue || both) {
-        const quan::ConvPlan whole = plan.splits == 1 ? plan : quan::qconv2d_plan(g, dt, quan::ConvForm::Hamilton);
-        if (quan::qconv2d_writes_stats(whole, g, dt))
-            bytes = quan::iqbn_tile_stats_bytes(whole.stat_tiles, c_out);
-    }
+    if (whole_stats && (in_epilogue || both))
+        bytes = quan::iqbn_tile_stats_bytes(whole.stat_tiles, c_out);
     unsigned *flags = nullptr;
     if (!in_epilogue || both) {
         bytes = std::max(bytes, quan::iqbn_workspace_bytes(pixels, c_out));

@@ -228,3 +228,34 @@ def test_other_calls_captured_on_a_smaller_batch(so, call, dtype):
                                          for k, s in ((1, 1), (3, 1), (3, 2), (5, 1))]
     cases = [(call, s, b, dict(dtype=dtype)) for s in layers for b in BATCHES]
     assert host_calls.in_child(_smaller, so, cases) == []
+
+
+# ---- where the statistics of a convolution + IQBN come from ----
+
+def _stats_launches(q, shapes, stats, dtype):
+    out = []
+    for i, shape in enumerate(shapes):
+        q.iqbn_layer(shape, dtype=dtype, stats=stats, stream=0x5000 + 16 * i)
+        q.clear()
+        q.iqbn_layer(shape, dtype=dtype, stats=stats, stream=0x5000 + 16 * i)
+        out.append([e.name for e in q.events() if e.what == "L"])
+    return out
+
+
+# few tiles and many stages: layers whose convolution splits K where it may
+SPLIT = [(1, 256, 14, 14, 256, 3, 1, 1), (1, 64, 28, 28, 64, 3, 1, 1), (4, 128, 7, 7, 32, 3, 1, 1),
+         (1, 64, 40, 40, 48, 3, 1, 1)]
+
+
+def test_epilogue_statistics_are_the_epilogues(so):
+    """A caller that asks for statistics in the convolution's epilogue gets them
+    there wherever the layer's tiles can gather them, also on a layer that
+    would split K otherwise."""
+    for names in host_calls.in_child(_stats_launches, so, SPLIT, 1, BF16):
+        assert len(names) == 3, names
+        assert any("iqbn_finalize_tiles" in n for n in names) and not any("add_splits" in n for n in names), names
+    for names in host_calls.in_child(_stats_launches, so, SPLIT[:2], 0, BF16):
+        assert any("add_splits" in n for n in names), names
+    # fp32 tiles cannot: the pass, behind a split convolution
+    for names in host_calls.in_child(_stats_launches, so, SPLIT[:2], 1, F32):
+        assert any("add_splits" in n for n in names) and not any("tiles" in n for n in names), names
