@@ -109,8 +109,33 @@ class StreamCall {
     std::unique_lock<std::mutex> lock_;
 };
 
+// While one lives, this thread's allocations leave other streams' captures
+// alone: in the default mode a hipMalloc, hipFree or stream synchronisation
+// here is refused, and breaks the capture, while any thread captures any
+// stream.  (hipDeviceSynchronize does so in every mode.  Not for a call whose
+// own stream is captured: its allocations are refused as they should be.)
+class CaptureApart {
+  public:
+    explicit CaptureApart(const StreamCall &call) : active_(!call.capturing)
+    {
+        if (active_)
+            active_ = hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess;
+    }
+    ~CaptureApart()
+    {
+        if (active_)
+            (void)hipThreadExchangeStreamCaptureMode(&mode_);
+    }
+    CaptureApart(const CaptureApart &) = delete;
+    CaptureApart &operator=(const CaptureApart &) = delete;
+
+  private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+    bool active_;
+};
+
 // Returns a device buffer of at least `bytes` for (device, stream, purpose).
-// Growing it first waits for the device to finish with the old one, which is
+// Growing it first waits for the stream to finish with the old one, which is
 // freed, or kept where a captured graph may hold it.
 int workspace(const StreamCall &call, Purpose purpose, size_t bytes, void **out, unsigned *uses = nullptr)
 {
@@ -120,10 +145,12 @@ int workspace(const StreamCall &call, Purpose purpose, size_t bytes, void **out,
     std::lock_guard<std::mutex> lock(g_ws_mutex);
     Workspace &ws = g_ws[{call.dev, {call.stream, int(purpose)}}];
     if (ws.bytes < bytes) {
+        const CaptureApart apart(call);
         if (ws.ptr) {
-            e = hipDeviceSynchronize();
+            // (every launch with it went out on this stream, or is a graph's)
+            e = hipStreamSynchronize(static_cast<hipStream_t>(call.stream));
             if (e != hipSuccess)
-                return fail_hip(e, "hipDeviceSynchronize");
+                return fail_hip(e, "hipStreamSynchronize");
             if (ws.in_graph)
                 ws.retired.push_back(ws.ptr);
             else

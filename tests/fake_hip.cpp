@@ -10,12 +10,13 @@
 #include <mutex>
 #include <set>
 #include <string>
+#include <utility>
 #include <vector>
 
 namespace {
 
 struct Event {
-    char what;       // 'L' launch, 'M' malloc, 'F' free, 'S' memset, 'D' device synchronize
+    char what;       // 'L' launch, 'M' malloc, 'F' free, 'S' memset, 'D' device and 'W' stream synchronize
     int tag;         // the calling thread's (fake_tag)
     void *stream;
     std::string name;  // of the kernel, mangled
@@ -34,6 +35,7 @@ int g_delay_us = 0;
 size_t g_limit = size_t(1) << 40;  // bytes that may be live
 thread_local int t_tag = 0;
 thread_local hipError_t t_last = hipSuccess;
+thread_local hipStreamCaptureMode t_mode = hipStreamCaptureModeGlobal;
 
 struct Config {
     dim3 grid, block;
@@ -117,15 +119,22 @@ hipError_t hipGetSymbolAddress(void **p, const void *)
     return hipSuccess;
 }
 
-// As the runtime does while any stream is captured in the global mode: the
-// calls that touch memory or wait are refused.
+// As the runtime does while any stream is captured: the calls that touch
+// memory or wait are refused, unless the thread is in the relaxed mode.
+bool refused() { return !g_capturing.empty() && t_mode != hipStreamCaptureModeRelaxed; }
+
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *mode)
+{
+    std::swap(*mode, t_mode);
+    return hipSuccess;
+}
 hipError_t hipMalloc(void **p, size_t bytes)
 {
     std::lock_guard<std::mutex> lock(g_mutex);
     size_t live = 0;
     for (const auto &b : g_live)
         live += b.second;
-    const bool capturing = !g_capturing.empty();
+    const bool capturing = refused();
     if (capturing || live + bytes > g_limit) {
         add('M', nullptr, "refused", nullptr, bytes, capturing);
         return done(capturing ? hipErrorStreamCaptureUnsupported : hipErrorOutOfMemory);
@@ -139,7 +148,7 @@ hipError_t hipMalloc(void **p, size_t bytes)
 hipError_t hipFree(void *p)
 {
     std::lock_guard<std::mutex> lock(g_mutex);
-    const bool capturing = !g_capturing.empty();
+    const bool capturing = refused();
     add('F', nullptr, capturing ? "refused" : "", p, 0, capturing);
     if (capturing)
         return done(hipErrorStreamCaptureUnsupported);
@@ -154,8 +163,15 @@ hipError_t hipMemsetAsync(void *p, int, size_t bytes, hipStream_t s)
 hipError_t hipDeviceSynchronize()
 {
     std::lock_guard<std::mutex> lock(g_mutex);
-    const bool capturing = !g_capturing.empty();
+    const bool capturing = !g_capturing.empty();  // in every mode
     add('D', nullptr, capturing ? "refused" : "", nullptr, 0, capturing);
+    return capturing ? done(hipErrorStreamCaptureUnsupported) : hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t s)
+{
+    std::lock_guard<std::mutex> lock(g_mutex);
+    const bool capturing = refused();
+    add('W', s, capturing ? "refused" : "", nullptr, 0, capturing);
     return capturing ? done(hipErrorStreamCaptureUnsupported) : hipSuccess;
 }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *status)

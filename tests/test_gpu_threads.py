@@ -58,3 +58,47 @@ def test_two_threads_on_one_stream(packed):
         assert len(got[tag]) == 20 * len(layers)
         for i, y in got[tag]:
             assert torch.equal(y, want[i]), f"thread {tag}, layer {LAYERS[i]}"
+
+
+def test_call_beside_a_capture():
+    """Another thread's calls that allocate and outgrow the buffers of their own
+    stream leave a capture in progress alone."""
+    say("calls beside another thread's capture")
+    held, small, large, whole = [_layer(10 + i, s) for i, s in enumerate(
+        [(4, 32, 28, 28, 32), (2, 12, 20, 20, 20), (8, 12, 40, 40, 20), (64, 32, 32, 32, 64)])]
+
+    def call(layer, out):
+        return quan.quan_qconv2d_forward_packed(layer[0], layer[2], tuple(layer[1][0].shape), pad=1, out=out)
+
+    outs = [torch.empty_like(quan.quan_qconv2d_forward_packed(x, p, tuple(ws[0].shape), pad=1))
+            for x, ws, p in (held, small, large, whole)]
+    want = [call(layer, None) for layer in (held, small, large)]
+    mine, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for st in (mine, other):
+        with torch.cuda.stream(st):
+            call(whole, outs[3])
+    torch.cuda.synchronize()
+    failed = []
+
+    def run():
+        try:
+            with torch.cuda.stream(other):
+                call(small, outs[1])
+                call(large, outs[2])
+        except Exception as e:  # noqa: BLE001
+            failed.append(repr(e))
+
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=mine):
+        call(held, outs[0])
+        t = threading.Thread(target=run)
+        t.start()
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for _ in range(3):
+        outs[0].fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outs, want))

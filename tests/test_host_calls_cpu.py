@@ -259,3 +259,26 @@ def test_epilogue_statistics_are_the_epilogues(so):
     # fp32 tiles cannot: the pass, behind a split convolution
     for names in host_calls.in_child(_stats_launches, so, SPLIT[:2], 1, F32):
         assert any("add_splits" in n for n in names) and not any("tiles" in n for n in names), names
+
+
+# ---- calls beside another stream's capture ----
+
+def _beside(q, calls):
+    for name, args in calls:        # the stream's other buffers
+        getattr(q, name)(*args, stream=S)
+    q.clear()
+    q.fake.fake_capture(0x99, 1)    # by another thread
+    for name, args in calls:
+        args = tuple((a[0] * 16,) + a[1:] if isinstance(a, tuple) else a for a in args)
+        getattr(q, name)(*args, stream=S)
+    q.fake.fake_capture(0x99, 0)
+    return q.events()
+
+
+def test_growing_buffers_leave_other_streams_captures_alone(so):
+    """A call that allocates or outgrows its buffers while another thread
+    captures another stream makes no call that would break that capture."""
+    calls = [(name, (shape,)) for name, shape in SHARED]
+    events = host_calls.in_child(_beside, so, calls)
+    assert any(e.what == "M" for e in events) and any(e.what == "F" for e in events)
+    assert not [e for e in events if e.name == "refused"]
