@@ -40,9 +40,10 @@
  * different streams never share a workspace; several host threads may call on
  * one stream, whose calls then run one after the other (each call's launches
  * stay together).  Some calls are faster with a larger buffer of their own
- * (partial tiles of a split convolution, an input padded to whole 16-byte
- * chunks, folded maps, the sign bits of a ReLU output); they run without it
- * where it cannot be allocated or would have to grow under graph capture.
+ * (partial tiles of a split convolution, at most 64 MiB; an input padded to
+ * whole 16-byte chunks, at most 512 MiB; folded maps, at most 20 MiB; the sign
+ * bits of a ReLU output, one per element); they run without it where it cannot
+ * be allocated or would have to grow under graph capture.
  * Graphs captured from a stream hold its buffers, which stay allocated until
  * quan_release() also when a later call outgrows them.  Replays of such graphs,
  * and that stream's own calls, must not overlap in time.

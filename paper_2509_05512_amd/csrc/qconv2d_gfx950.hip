@@ -2454,23 +2454,49 @@ hipError_t pad_channels(const ConvGeom &g, DType dt, const void *x, void *pad, h
 }
 }  // namespace
 
-// The pad costs a launch and one pass over x; a stage of element loads costs
-// about 1.8 us more than one of DMA (2.2 against 0.4), so it pays from about
-// four stages per work-group on.  The padded tensor keeps to the limits that
-// the entry points set for x.
-size_t qconv2d_pad_bytes(const ConvGeom &g, DType dt)
+// Whether a padded copy pays: a launch and a pass over both copies, against
+// what element loads cost a stage more than DMA, which grows with the channels
+// that the stage loads.  A work-group loads a tile's only stage while it
+// finishes the tile before, so layers of one stage (1x1 kernels on one block of
+// channels) pad later.  The constants follow from element loads / pad, us:
+//  - 1x1, 32 x 112 x 112 -> 16 bf16: 3 channels 36 / 43, 9: 43 / 45, 12: 50 / 44;
+//    64 x 56 x 56 -> 32: 5: 25 / 28, 12: 28 / 34, 18 (two stages): 37 / 35, 28: 45
+//    / 39; 16 x 56 x 56 -> 16: 18: 14 / 18, 60: 23 / 27, 100: 42 / 33;
+//  - 3x3: one channel, 1 x 32 x 32 -> 16: 17 / 12, 64 x 224 x 224: 1084 / 485; 12
+//    channels, 32 x 112 x 112: 236 / 78;
+//  - fp32 (tiles of 64 pixels, four work-groups a compute unit): 1x1, 16 x 56 x
+//    56 -> 16: 9: 17 / 23, 33: 30 / 36; 64 x 56 x 56 -> 32: 9: 80 / 71, 33: 174 /
+//    145; 3x3, one channel, 32 x 112 x 112: 222 / 189.
+// phases: the launches that share g's pixels and taps (a strided gradient).
+namespace {
+bool pad_pays(const ConvGeom &g, DType dt, int phases)
 {
+    const bool f32 = dt == DType::F32;
+    const int pk = f32 ? 8 : 16, blocks = (g.c_in + pk - 1) / pk;
+    const int bm = f32 ? 64 : 128, bnc = f32 ? 16 : g.c_out <= 32 ? 32 : 64;
+    const double ch = double(g.c_in) / blocks;  // of a stage
+    const int64_t stages = int64_t(g.k_h) * g.k_w * blocks;
+    const int64_t tiles = (g.m() + bm - 1) / bm * ((g.c_out + bnc - 1) / bnc);
+    const int64_t rounds = (tiles + device_cus() - 1) / device_cus();
+    const bool one = stages == 1;
+    const double stage_us = f32 ? (one ? 0.1 + 0.05 * ch : 0.3 + 0.025 * ch) : (one ? 0.3 + 0.12 * ch : 0.6 + 0.066 * ch);
+    const double bytes = double(g.n) * g.h * g.w * 4 * (g.c_in + padded_channels(g.c_in, dt)) * (f32 ? 4 : 2);
+    return double(stages) * double(rounds) / phases * stage_us > (one ? 7.0 : 5.7) + bytes / 6.2e6;
+}
+}  // namespace
+
+// The padded tensor keeps to the limits that the entry points set for x, and
+// to kPadBytes: one channel becomes eight, and the copy stays allocated.
+size_t qconv2d_pad_bytes(const ConvGeom &g, DType dt, int phases)
+{
+    constexpr int64_t kPadBytes = int64_t(512) << 20;
     const int cp = padded_channels(g.c_in, dt);
-    if (cp == g.c_in)
-        return 0;
-    const int pk = dt == DType::BF16 ? 16 : 8;
-    const int64_t stages = int64_t(g.k_h) * g.k_w * ((g.c_in + pk - 1) / pk);
-    const int64_t rounds = (g.m() / 128 + device_cus() - 1) / device_cus();
-    if (stages * (rounds > 0 ? rounds : 1) < 4)
+    if (cp == g.c_in || !pad_pays(g, dt, phases))
         return 0;
     const int64_t es = dt == DType::BF16 ? 2 : 4, limit = (int64_t(1) << 31) - 1;
     const int64_t img = int64_t(g.h) * g.w * 4 * cp;
-    if (img * g.n > limit || img * es * (256 / (int64_t(g.h_out) * g.w_out) + 2) > limit)
+    if (img * g.n > limit || img * g.n * es > kPadBytes ||
+        img * es * (256 / (int64_t(g.h_out) * g.w_out) + 2) > limit)
         return 0;
     return size_t(img) * g.n * es;
 }
@@ -2730,7 +2756,7 @@ size_t qconv2d_grad_data_pad_bytes(const ConvGeom &g, DType dt)
     ConvGeom t = qconv2d_grad_data_geom(g);
     t.h = g.h_out;
     t.w = g.w_out;
-    return qconv2d_pad_bytes(t, dt);
+    return qconv2d_pad_bytes(t, dt, by_phases(g) ? g.s_h * g.s_w : 1);
 }
 
 size_t qconv2d_grad_data_split_bytes(const ConvGeom &g, DType dt, bool sep)

@@ -161,7 +161,8 @@ int workspace(const StreamCall &call, Purpose purpose, size_t bytes, void **out,
             if (e != hipSuccess)
                 return fail_hip(e, "hipFree");
         }
-        size_t want = bytes + bytes / 4;  // headroom for slightly larger calls
+        // headroom for slightly larger calls (the padded copies are large)
+        size_t want = purpose == kConvPad ? bytes : bytes + bytes / 4;
         want = (want + 4095) & ~size_t(4095);
         e = hipMalloc(&ws.ptr, want);
         if (e != hipSuccess) {

@@ -65,7 +65,7 @@ size_t qconv2d_split_bytes(const ConvPlan &plan);
 
 // Bytes of x padded to whole chunks where a convolution is faster on that
 // (qconv2d_run writes it to plan.pad first), 0 where it takes x as it is.
-size_t qconv2d_pad_bytes(const ConvGeom &g, DType dt);
+size_t qconv2d_pad_bytes(const ConvGeom &g, DType dt, int phases = 1);
 
 // What a convolution launch computes: the Hamilton product (eq. 5), the
 // separable form (eq. 7), or the separable form's input gradient (eqs.

@@ -63,6 +63,17 @@ def test_padded_channels(dtype, shape, sep):
     assert_close(f64(dx), ref_dx, dt, f"dX {shape}")
 
 
+# Layers that pad with few channels or in phases (more stages), and 1x1 layers
+# on both sides of the rule.
+@pytest.mark.parametrize("sep", [False, True], ids=["hamilton", "separable"])
+@pytest.mark.parametrize("dtype,shape", [("fp32", (2, c, 12, 13, 11, 5, 1, 2, 1)) for c in (1, 2, 3, 5, 6, 7)] +
+                         [("bf16", (2, c, 70, 21, 19, 3, 2, 1, 1)) for c in (69, 100, 133)] +
+                         [("bf16", (1, 7, 8, 64, 66, 1, 1, 0, 1)), ("bf16", (1, 15, 130, 70, 80, 1, 1, 0, 1)),
+                          ("fp32", (1, 9, 32, 130, 140, 1, 1, 0, 1))], ids=str)
+def test_padded_channels_more_stages(dtype, shape, sep):
+    test_padded_channels(dtype, shape, sep)
+
+
 @pytest.mark.parametrize("dtype,cin", [("bf16", 7), ("bf16", 12), ("fp32", 3)])
 def test_padded_channels_other_epilogues(dtype, cin):
     say(f"padded channels epilogues {dtype} {cin}")

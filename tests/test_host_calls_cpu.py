@@ -282,3 +282,43 @@ def test_growing_buffers_leave_other_streams_captures_alone(so):
     events = host_calls.in_child(_beside, so, calls)
     assert any(e.what == "M" for e in events) and any(e.what == "F" for e in events)
     assert not [e for e in events if e.name == "refused"]
+
+
+# ---- the padded copy of partial channel chunks ----
+
+def _pads(q, cases):
+    out = []
+    for i, (call, shape, dtype) in enumerate(cases):
+        q.clear()
+        getattr(q, call)(shape, dtype=dtype, stream=0x7000 + 16 * i)
+        ev = q.events()
+        out.append((any("pad_channels" in e.name for e in ev), max([e.bytes for e in ev if e.what == "M"], default=0)))
+    return out
+
+
+def test_padded_copy_is_made_where_it_pays(so):
+    """The rule's two sides at sizes that were measured (one launch more and a
+    pass over both copies, against element loads in every stage)."""
+    no = [((32, 3, 112, 112, 16, 1, 1, 0), BF16), ((32, 9, 112, 112, 16, 1, 1, 0), BF16),
+          ((64, 5, 56, 56, 32, 1, 1, 0), BF16), ((64, 12, 56, 56, 32, 1, 1, 0), BF16),
+          ((16, 18, 56, 56, 16, 1, 1, 0), BF16), ((16, 60, 56, 56, 16, 1, 1, 0), BF16),
+          ((16, 9, 56, 56, 16, 1, 1, 0), F32), ((16, 33, 56, 56, 16, 1, 1, 0), F32),
+          ((32, 1, 112, 112, 16, 1, 1, 0), F32)]
+    yes = [((32, 12, 112, 112, 16, 1, 1, 0), BF16), ((64, 28, 56, 56, 32, 1, 1, 0), BF16),
+           ((16, 100, 56, 56, 16, 1, 1, 0), BF16), ((1, 1, 32, 32, 16, 3, 1, 1), BF16),
+           ((64, 1, 224, 224, 16, 3, 1, 1), BF16), ((8, 12, 75, 77, 20, 3, 1, 1), BF16),
+           ((64, 9, 56, 56, 32, 1, 1, 0), F32), ((64, 33, 56, 56, 32, 1, 1, 0), F32),
+           ((32, 1, 112, 112, 16, 3, 1, 1), F32)]
+    got = host_calls.in_child(_pads, so, [("forward_packed", s, t) for s, t in no + yes])
+    wrong = [(s, t) for (s, t), (padded, _) in zip(no + yes, got) if padded != ((s, t) in yes)]
+    assert not wrong
+
+
+def test_padded_copy_is_bounded(so):
+    """No call keeps more than 512 MiB for a padded copy, though one bf16 channel
+    becomes eight."""
+    cases = [("forward_packed", (16, 1, 700, 700, 8, 3, 1, 1), BF16), ("forward_packed", (64, 1, 512, 512, 8, 3, 1, 1), BF16),
+             ("forward_packed", (64, 3, 512, 512, 4, 3, 1, 1), F32), ("backward_data", (64, 4, 512, 512, 1, 3, 1, 1), BF16)]
+    for (padded, largest), case in zip(host_calls.in_child(_pads, so, cases), cases):
+        assert largest <= 512 << 20, (case, largest)
+        assert padded == (case[1][0] == 16), case
