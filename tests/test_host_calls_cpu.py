@@ -305,7 +305,8 @@ def test_padded_copy_is_made_where_it_pays(so):
           ((16, 9, 56, 56, 16, 1, 1, 0), F32), ((16, 33, 56, 56, 16, 1, 1, 0), F32),
           ((32, 1, 112, 112, 16, 1, 1, 0), F32)]
     yes = [((32, 12, 112, 112, 16, 1, 1, 0), BF16), ((64, 28, 56, 56, 32, 1, 1, 0), BF16),
-           ((16, 100, 56, 56, 16, 1, 1, 0), BF16), ((1, 1, 32, 32, 16, 3, 1, 1), BF16),
+           ((16, 100, 56, 56, 16, 1, 1, 0), BF16), ((8, 7, 112, 112, 128, 1, 1, 0), BF16),
+           ((8, 1, 64, 64, 16, 3, 1, 1), BF16), ((1, 1, 32, 32, 16, 3, 1, 1), BF16),
            ((64, 1, 224, 224, 16, 3, 1, 1), BF16), ((8, 12, 75, 77, 20, 3, 1, 1), BF16),
            ((64, 9, 56, 56, 32, 1, 1, 0), F32), ((64, 33, 56, 56, 32, 1, 1, 0), F32),
            ((32, 1, 112, 112, 16, 3, 1, 1), F32)]
