@@ -6,8 +6,8 @@
 // kernel would stage 16 input channels per step with 15 of them zero; this
 // kernel builds each MFMA's K = 16 slice (two taps x four components) of
 // one output pixel per lane from the colour planes, with the map of eq. 4
-// evaluated in fp32 and rounded once to bf16.  The layer is bound by writing its output (4 * c_out reals per pixel
-// against 3 inputs).
+// evaluated in fp32 and rounded once to bf16.  The layer is bound by writing
+// its output (4 * c_out reals per pixel against 3 inputs).
 //
 // A work-group takes bands of consecutive output rows of one image.  It maps
 // the band's input rows once per pixel into LDS (8 bytes a quaternion, zeros
@@ -28,10 +28,11 @@
 //       parks 64 of them at a time in LDS (rows padded by 8 bytes, so the 32
 //       pixels' 8-byte pieces fall on different banks) and stores 16 bytes a
 //       lane, whole lines, where 8-byte stores from D touched 32 lines each.
-// 64 x 224 x 224 RGB, 3x3 stride 2 to 16 channels: 54.6 -> 33.1 us (122 MB;
-// a device copy of as much takes 24).  Bands of two rows or one work-group a
-// band instead of three work-groups a compute unit: 33.9, 35.0.
+// 64 x 224 x 224 RGB, 3x3 stride 2 to 16 channels: 53.6 -> 32.0 us (122 MB; a
+// device copy of as much takes 24).
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "gfx950_dma.h"
 #include "quan_launch.h"
@@ -45,7 +46,7 @@ typedef float stem_f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kStemThreads = 256;
 constexpr int kStemWaves = kStemThreads / 64;
 constexpr int kStemMaxFrags = 32;  // NBLK x KM weight fragments held in LDS (1 KB each)
-constexpr int kStemMaxBand = 8;    // output rows of a band at most
+constexpr int kStemMaxBand = 32;   // output rows of a band at most
 // LDS of a work-group: three fit a compute unit (160 KB), and no launch needs
 // more than the 64 KB that a kernel gets without asking.
 constexpr size_t kStemLds = 52 * 1024, kStemMaxLds = 64 * 1024;
@@ -63,7 +64,7 @@ struct StemArgs {
     int bands;           // of all images
     int patch_w;         // staged columns: input columns -p_w .. patch_w - p_w - 1
     int patch;           // staged pixels of a band (the zero pixel follows); 0: not staged
-    FastDiv by_w_out, by_patch_w, by_last;  // by_last: pieces of the last parked slice of a pixel
+    FastDiv by_c_out, by_w_out, by_patch_w, by_last;  // by_last: pieces of the last parked slice of a pixel
 };
 
 // The quaternion of an RGB pixel (eq. 4) in bf16.
@@ -109,17 +110,44 @@ __global__ __launch_bounds__(kStemThreads) void qconv2d_stem(StemArgs a)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, l32 = lane & 31;
     const int taps = a.k_h * a.k_w;
     const int rows = 4 * a.c_out;
+    static_assert(32 * NBLK <= kStemThreads, "one row's bias per thread");
+    float bias = 0.0f;
+    if (a.bias != nullptr && int(threadIdx.x) < rows)
+        bias = float(a.bias[threadIdx.x]);
+    // The kernels' own values first, four loads in flight per thread, where the
+    // parked output will lie: every work-group reads the same few lines (two
+    // bytes of each 32), and a table built straight from memory read each value
+    // sixteen times.
+    __bf16 *const vals = reinterpret_cast<__bf16 *>(parks);
+    const int n_vals = 4 * taps * a.c_out;
+    static_assert(4 * (4 * kStemMaxFrags / NBLK) * 8 * NBLK * 2 <= kStemWaves * 32 * prow, "the values fit the parks");
+    for (int i = threadIdx.x; i < n_vals; i += 4 * kStemThreads) {
+        __bf16 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int at = i + u * kStemThreads < n_vals ? i + u * kStemThreads : i;
+            const int tm = fast_div(at, a.by_c_out);
+            v[u] = a.wpack[(size_t(tm) * a.cout_pad + (at - tm * a.c_out)) * a.pk];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i + u * kStemThreads < n_vals)
+                vals[i + u * kStemThreads] = v[u];
+    }
+    if (threadIdx.x < 32 * NBLK)
+        btab[threadIdx.x] = bias;
+    __syncthreads();
     for (int idx = threadIdx.x; idx < NBLK * a.km * 64; idx += kStemThreads) {
         const int fl = idx & 63, fm = (idx >> 6) % a.km, fb = (idx >> 6) / a.km;
         const int r = 32 * fb + (fl & 31);
-        const int p = r < rows ? r / a.c_out : 0, c = r < rows ? r - p * a.c_out : 0;
+        const int p = r < rows ? fast_div(r, a.by_c_out) : 0, c = r < rows ? r - p * a.c_out : 0;
         stem_bf16x8 f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int k = 16 * fm + 8 * (fl >> 5) + e, tap = k >> 2, q = k & 3;
             float v = 0.0f;
             if (r < rows && tap < taps) {
-                v = float(a.wpack[(size_t(tap * 4 + (p ^ q)) * a.cout_pad + c) * a.pk]);
+                v = float(vals[(tap * 4 + (p ^ q)) * a.c_out + c]);
                 if ((kHamiltonNeg >> (4 * p + q)) & 1u)
                     v = -v;
             }
@@ -127,8 +155,6 @@ __global__ __launch_bounds__(kStemThreads) void qconv2d_stem(StemArgs a)
         }
         wtab[fb * a.km + fm][fl] = f;
     }
-    for (int r = threadIdx.x; r < 32 * NBLK; r += kStemThreads)
-        btab[r] = (a.bias != nullptr && r < rows) ? float(a.bias[r]) : 0.0f;
     if constexpr (STAGED) {
         // taps past the kernel (zero weights) read the zero pixel; -1 marks
         // them, as their address does not move with the output pixel
@@ -259,8 +285,6 @@ hipError_t launch_stem(StemArgs a, int64_t n, hipStream_t stream)
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess)
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    // The band: as many rows as leave three work-groups a compute unit, both
-    // in LDS and in number, since a taller band shares more input rows.
     const int64_t span_h = int64_t(a.k_h - 1) * a.d_h + 1, span_w = int64_t(a.k_w - 1) * a.d_w + 1;
     const int64_t cols = int64_t(a.w_out - 1) * a.s_w + span_w;
     auto patch_of = [&](int band) { return (int64_t(band - 1) * a.s_h + span_h) * cols; };
@@ -271,19 +295,52 @@ hipError_t launch_stem(StemArgs a, int64_t n, hipStream_t stream)
         return px < int64_t(lds / 8) && fixed + size_t(px + 1) * 8 <= lds;
     };
     const bool staged = fits(1, kStemMaxLds);
-    while (a.band < kStemMaxBand && 2 * a.band <= a.h_out && (!staged || fits(2 * a.band, kStemLds)) &&
-           n * ((a.h_out + 2 * a.band - 1) / (2 * a.band)) >= 3LL * cus)
-        a.band *= 2;
+    // The band: even parts of an image that take the least time by a model: a
+    // work-group alone needs 1 us per round of its four waves' pixels and a
+    // band's staging (0.5 + 0.4 per round of loads), those of a compute unit
+    // share its stores, and each builds the table.  A row of a narrow image
+    // fills few of the four waves' lanes, and a work-group a row leaves its
+    // table's cost to few pixels: in bands of one row, rows of 14 to 86 pixels
+    // and 36 or 64 channels took up to 2.9 times as long as pixels dealt without
+    // regard to rows (64 x 37 x 37, 1x1 stride 2 to 64: 10.1 us so, 29.6, now
+    // 10.2).  One image of wide rows is left 0.3 to 2.4 us slower than that: a row
+    // of 138 pixels is two rounds, the second nearly empty.
+    auto rounds_of = [&](int64_t rows) { return (rows * a.w_out + 32 * kStemWaves - 1) / (32 * kStemWaves); };
+    double best = 0.0;
+    int64_t cap = 0;  // work-groups
+    for (int band = 1; band <= a.h_out && band <= kStemMaxBand; ++band) {
+        const int parts = (a.h_out + band - 1) / band;
+        if ((a.h_out + parts - 1) / parts != band)
+            continue;  // (not even)
+        if (band > 1 && staged && !fits(band, kStemMaxLds))
+            break;
+        // (two resident work-groups by registers or LDS, else three)
+        const int64_t slots = int64_t(NBLK == 8 || (staged && !fits(band, kStemLds)) ? 2 : 3) * cus;
+        const int64_t bands = n * parts, wgs = std::min(bands, slots);
+        const double stage = staged ? 0.5 + 0.4 * double((patch_of(band) + 1023) / 1024) : 0.2;
+        const double alone = stage + double(rounds_of(band));
+        const double shared = (slots < 3 * cus ? 1.15 : 1.0) * (0.35 * NBLK * double(rounds_of(band)) + 0.4 * stage);
+        // one band each of `groups` work-groups
+        auto turn = [&](int64_t groups) { return std::max(alone, double((groups + cus - 1) / cus) * shared); };
+        const double cost = double(bands / wgs) * turn(wgs) + (bands % wgs ? turn(bands % wgs) : 0.0) +
+                            0.1 * NBLK * a.km * std::max(1.0, double(wgs) / cus);
+        // (a taller band shares more input rows)
+        if (band == 1 || cost <= 1.05 * best) {
+            best = band == 1 ? cost : std::min(best, cost);
+            a.band = band;
+            cap = slots;
+        }
+    }
     a.img_bands = (a.h_out + a.band - 1) / a.band;
     a.bands = int(n * a.img_bands);
     a.patch_w = staged ? int(cols) : 1;
     a.patch = staged ? int(patch_of(a.band)) : 0;
+    a.by_c_out = FastDiv(a.c_out);
     a.by_w_out = FastDiv(a.w_out);
     a.by_patch_w = FastDiv(a.patch_w);
     const int last = 4 * a.c_out % (NBLK < 2 ? 32 : 64) / 8;
     a.by_last = FastDiv(last > 0 ? last : 1);
     const size_t lds = stem_lds_bytes(NBLK, a.km, a.patch);
-    const int64_t cap = 3LL * cus;
     const dim3 wgs(unsigned(a.bands < cap ? a.bands : cap));
     if (staged)
         hipLaunchKernelGGL((qconv2d_stem<NBLK, true>), wgs, dim3(kStemThreads), lds, stream, a);

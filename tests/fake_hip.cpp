@@ -21,7 +21,7 @@ struct Event {
     void *stream;
     std::string name;  // of the kernel, mangled
     void *ptr;       // buffer, or a launch's first argument word
-    size_t bytes;
+    size_t bytes;    // of a buffer; work-groups of a launch
     int in_capture;  // (of the launch's stream, or of any for the others)
 };
 
@@ -180,13 +180,13 @@ hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *status)
     *status = g_capturing.count(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *fn, dim3, dim3, void **args, size_t, hipStream_t s)
+hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3, void **args, size_t, hipStream_t s)
 {
     {
         std::lock_guard<std::mutex> lock(g_mutex);
         void *first = nullptr;
         std::memcpy(&first, args[0], sizeof(first));
-        add('L', s, g_kernels[fn], first, 0, int(g_capturing.count(s)));
+        add('L', s, g_kernels[fn], first, grid.x, int(g_capturing.count(s)));
     }
     // (another thread's launch comes between this call's, if it may)
     if (g_delay_us > 0)

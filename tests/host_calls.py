@@ -107,6 +107,11 @@ class Calls:
             self.at(), self.at(), *self._geo(s, p), *[self.at() for _ in range(5)],
             *self._sizes(n, c, h, w, o, k, dtype, stream)))
 
+    def stem(self, n, h, w, c_out, k, stride, dtype=BF16, stream=0):
+        self._ok(self.lib.quan_qconv2d_poincare_forward(
+            self.at(), self.at(), None, *self._geo(stride, k // 2), self.at(),
+            *[_i(v) for v in (n, h, w, c_out, k, k, dtype)], _vp(stream)))
+
     def iqbn(self, n, c, h, w, dtype=BF16, stream=0):
         self._ok(self.lib.quan_iqbn_forward(self.at(), self.at(), self.at(), _f(1e-5), self.at(), self.at(), self.at(),
                                             *[_i(v) for v in (n, c, h, w, dtype)], _vp(stream)))

@@ -1,6 +1,6 @@
 """The stem kernel's bands of output rows: every width of its stored slices
 (output channels from 1 to 64), tap counts around a K slice, strides and
-dilations, bands of one to eight rows with a short last one, images narrower
+dilations, bands of one row, of several and of a whole image, with a short last one, images narrower
 than a wave's 32 pixels, and layers whose input rows do not fit LDS; against
 the oracle, and the many-row cases against the separate map and convolution
 (the same quaternions and products, fp32 sums in another order)."""
@@ -20,12 +20,15 @@ BF16 = torch.bfloat16
 SMALL = ([(1, 7, 9, c, 3, 1, 1, 1) for c in (1, 2, 3, 6, 7, 8, 9, 15, 16, 17, 24, 33, 50, 63, 64)] +
          [(2, 9, 37, 16, k, s, k // 2, 1) for k in (1, 2, 4, 5) for s in (1, 2, 3)] +
          [(1, 30, 33, 8, 7, 2, 3, 1), (1, 21, 20, 16, 3, 1, 2, 2), (2, 70, 75, 4, 7, 1, 30, 10),
-          (1, 40, 37, 8, 3, 1, 0, 1), (1, 5, 5, 8, 3, 1, 0, 1), (1, 8, 6, 8, 3, 4, 1, 1)])
+          (1, 40, 37, 8, 3, 1, 0, 1), (1, 5, 5, 8, 3, 1, 0, 1), (1, 8, 6, 8, 3, 4, 1, 1)] +
+         [(n, h, h + 1, c, k, s, k // 2, 1) for n, h, c, k, s in ((5, 14, 36, 3, 1), (3, 37, 64, 1, 2), (2, 26, 64, 3, 1),
+                                                                  (2, 43, 24, 5, 2), (1, 69, 24, 5, 1), (1, 33, 16, 7, 1))])
 # not staged: 7 rows of 2000 columns; a span of 97 rows
 UNSTAGED = [(1, 8, 2000, 8, 7, 2, 3, 1), (1, 101, 99, 4, 7, 1, 48, 16)]
-# bands of 2, 4 and 8 rows; odd heights leave a short one
+# bands of several rows; odd heights leave a short one
 TALL = [(16, 97, 23, 6, 3, 1, 1, 1), (40, 99, 31, 16, 3, 1, 1, 1), (64, 101, 17, 20, 3, 1, 1, 1),
-        (64, 203, 45, 16, 3, 2, 1, 1)]
+        (64, 203, 45, 16, 3, 2, 1, 1), (64, 37, 37, 64, 1, 2, 0, 1), (64, 27, 27, 38, 3, 2, 1, 1),
+        (8, 86, 85, 64, 3, 1, 1, 1), (32, 69, 70, 24, 5, 1, 2, 1), (16, 112, 113, 16, 7, 2, 3, 1)]
 
 
 def _run(case, scale=1.0):
