@@ -109,7 +109,10 @@ Layout make_layout(int64_t pixels, int c, int vw, bool partials = true)
     if (partials) {
         const int64_t room = kPartialBytes / (int64_t(2) * l.row_len * sizeof(float));
         const int64_t few = blocks_of(kPartialRowsPerThread);
-        want = want < room ? want : room;
+        // (rows read element by element, few of them side by side: the partials
+        // of short row ranges cost as much as the rows, 1024 rows of 924 bf16
+        // columns, gradient, 11.9 us at 24 rows per thread, 15.0 at 4)
+        want = vw == 1 && l.rpi < 8 ? few : want < room ? want : room;
         want = want > few ? want : few;
     }
     const int64_t cap = partials ? kMaxBlocks : kStreamBlocks;  // per column group
@@ -1681,7 +1684,14 @@ hipError_t launch_all(const void *x, const float *gamma, const float *beta, floa
                       hipStream_t stream)
 {
     const T *xt = static_cast<const T *>(x);
-    if (small_takes<T, VW>(pixels)) {
+    // Wide fp32 rows over 4 MiB take the merged form: a column group of the
+    // one-launch form reads half lines of them.  1024 rows of 4096 columns 12.3
+    // us against 9.4, and of 2048 columns just written by a convolution 5 us
+    // more; 256 channels, 4 MiB, 6.5 against 7.4.
+    constexpr int64_t kSmallF32Bytes = int64_t(4) << 20;
+    const bool wide = sizeof(T) == 4 && pixels * 4 * c * int64_t(sizeof(T)) > kSmallF32Bytes &&
+                      merge_takes(pixels, c, VW, int(sizeof(T)));
+    if (small_takes<T, VW>(pixels) && !wide) {
         const SmallGrid sg = small_grid<T, VW>(pixels, c);
         const SmallArgs a = {gamma, beta, eps, mean, var};
         if (relu)

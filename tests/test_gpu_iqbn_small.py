@@ -25,6 +25,8 @@ SHAPES = [
     (2, 10, 5, 7), (1, 3, 8, 16), (1, 3, 3, 43), (3, 5, 11, 13),
     (1, 300, 7, 7),           # many column groups, the last one short in fp32
     (5, 20, 25, 27),          # three launches, a block's rows not a whole round
+    (1, 256, 32, 32), (1, 257, 32, 32),  # fp32: 4 MiB, and the first forward of the merged form
+    (1, 231, 25, 41), (3, 55, 31, 30),   # bf16 rows read element by element, three launches
 ]
 
 

@@ -345,3 +345,32 @@ def test_stem_work_groups_have_pixels_for_their_table(so):
         n, h, _, c, k, s = case
         pixels = n * ((h - 1) // s + 1) ** 2
         assert len(groups) == 1 and groups[0] <= max(n, pixels / 64), (case, groups)
+
+
+# ---- forms by size ----
+
+def _names(q, cases):
+    out = []
+    for i, (call, args, kw) in enumerate(cases):
+        q.clear()
+        getattr(q, call)(*args, stream=0x9000 + 16 * i, **kw)
+        ev = q.events()
+        out.append(([(e.name, e.bytes) for e in ev if e.what == "L"], [e.bytes for e in ev if e.what == "M"]))
+    return out
+
+
+def test_wide_fp32_rows_take_the_merged_form(so):
+    """A tensor of few pixels takes one launch, but fp32 rows above 4 MiB, of
+    which a column group reads half lines, the merged two."""
+    cases = [("iqbn", (1, c, 32, 32), dict(dtype=t)) for c, t in ((256, F32), (260, F32), (1024, F32), (512, BF16), (1024, BF16))]
+    small = [any("iqbn_small" in n for n, _ in names) for names, _ in host_calls.in_child(_names, so, cases)]
+    assert small == [True, False, False, True, True]
+
+
+def test_partials_of_rows_read_by_element(so):
+    """Rows that are no whole 16-byte pieces, few side by side in a block, leave
+    partials for at least 24 rows each."""
+    cases = [("iqbn_backward", (1, c, 1, px), dict(relu=False)) for c in (55, 231, 291) for px in (1024, 2000, 5000)]
+    for (call, args, _), (names, _) in zip(cases, host_calls.in_child(_names, so, cases)):
+        assert "iqbn_bwd_reduce" in names[0][0]
+        assert names[0][1] <= args[3] // 24 + 1, (args, names[0])
