@@ -448,24 +448,29 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
 
 // dW_m[o][c][ky][kx] = sum over slices of the partials in fp64.  A slice is
 // one run of [tap][m][o][c]; SG threads share four consecutive outputs, thread
-// s taking slices s, s + SG, ... in order (eight 16-byte loads in flight), and
-// are added in order through LDS: deterministic.
+// s taking slices s, s + SG, ... in order (U 16-byte loads in flight), and are
+// added in order through LDS: deterministic.  Blocks go through the run m by m
+// (`seg` blocks to a tap of one m), so that the stores of an m's taps, which lie
+// side by side, meet in the caches: 25 taps of 120 -> 144 channels in 4 slices
+// 30.0 us in the run's order, 13.7 so.
 // Bound by reading the partials.  One thread per output walking every slice
 // (the former form) kept too few loads in flight: 33.6 MB of partials (64 x
-// 64 channels, 9 taps, 57 slices) took 17.4 us, and 21.3 us for 57 slices of
-// a 16-channel layer; the latter now takes 4.0.
-template <int SG>
+// 64 channels, 9 taps, 57 slices) took 17.4 us, now 7.5; 57 slices of a
+// 16-channel layer 21.3, now 4.2.  Four-byte loads of a run of outputs of one tap
+// and m instead: 13.2 and 11.1.
+template <int SG, int U>
 __global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce(const float *__restrict__ part, int slices, int taps,
-                                                                 int oc_n, float *__restrict__ dw0,
+                                                                 int oc_n, int seg, float *__restrict__ dw0,
                                                                  float *__restrict__ dw1, float *__restrict__ dw2,
                                                                  float *__restrict__ dw3)
 {
     constexpr int QUADS = kThreads / SG;  // output quads per block
-    constexpr int U = 8;
     __shared__ double red[SG > 1 ? SG : 1][QUADS * 4];
     const int ql = threadIdx.x % QUADS, sg = threadIdx.x / QUADS;
     const int64_t n = int64_t(4) * taps * oc_n;  // a multiple of 4
-    const int64_t f0 = (int64_t(blockIdx.x) * QUADS + ql) * 4;
+    const int mt0 = int(blockIdx.x) / seg;  // segment (m, tap) of the order, at tap * 4 + m of the run
+    const int64_t blk = int64_t(mt0 % taps * 4 + mt0 / taps) * seg + int(blockIdx.x) % seg;
+    const int64_t f0 = (blk * QUADS + ql) * 4;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     if (f0 < n) {
         for (int sp = sg; sp < slices; sp += SG * U) {
@@ -495,7 +500,7 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce(const float *__
 #pragma unroll
             for (int k = 0; k < SG; ++k)
                 t += red[k][j];
-            const int64_t f = int64_t(blockIdx.x) * QUADS * 4 + j;
+            const int64_t f = blk * QUADS * 4 + j;
             if (f < n) {
                 const int mt = int(f / oc_n), m = mt & 3, tap = mt >> 2;
                 float *dw = m == 0 ? dw0 : m == 1 ? dw1 : m == 2 ? dw2 : dw3;
@@ -516,8 +521,9 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce(const float *__
 // Dense partials G[(p,o)][(q,c)] per slice and tap ([slices][taps][4*c_out]
 // [4*c_in]): dW_m[o][c][tap] = sum over slices and p of s(p, p xor m)
 // G[(p,o)][(p xor m, c)] (eq. 6's signs), in fp64; with sep (the separable
-// form) of S[p][m] G[(p,o)][(m,c)] (eq. 7's signs).  Sixteen threads share
-// an output, as above.
+// form) of S[p][m] G[(p,o)][(m,c)] (eq. 7's signs).  SG threads share an
+// output, as above.
+template <int SG>
 __global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce_dense(const float *__restrict__ part, int slices,
                                                                        int taps, int c_out, int c_in, int sep,
                                                                        float *__restrict__ dw0,
@@ -525,7 +531,7 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce_dense(const flo
                                                                        float *__restrict__ dw2,
                                                                        float *__restrict__ dw3)
 {
-    constexpr int SG = 16, OUTS = kThreads / SG;
+    constexpr int OUTS = kThreads / SG;
     __shared__ double red[SG][OUTS];
     const int ol = threadIdx.x % OUTS, sg = threadIdx.x / OUTS;
     const int64_t oc_n = int64_t(c_out) * c_in;
@@ -667,15 +673,19 @@ struct WPlan {
     int64_t per_split;
 };
 
-WPlan wgrad_plan(const ConvGeom &g)
+WPlan wgrad_plan(const ConvGeom &g, DType dt)
 {
     WPlan p;
     // A tile of 64 channels a side, or 32 where 64 would leave a block idle
     // (two or four waves then split a chunk's K steps): 32 -> 64 channels on
     // 16 x 160 x 160, stride 2: 108.8 -> 65 us with half the MFMAs of the
     // 64-wide tile gone; 32 -> 32 in fp32 on 16 x 28 x 28: 138 -> 39 us.
-    p.wo = g.c_out <= 32 || (g.c_out > 64 && g.c_out <= 96) ? 1 : 2;
-    p.wc = g.c_in <= 32 || (g.c_in > 64 && g.c_in <= 96) ? 1 : 2;
+    // In bf16 three tiles of 32 stage more than two of 64 for their MFMAs: 87 -> 92
+    // on 16 x 16 x 16 70.1 us with 64, 99.8 with 32; 96 -> 96, 5x5 stride 3 on 10 x 24
+    // x 24 19.2 / 22.3 (fp32, bound by its MFMAs: 125 / 86).
+    auto narrow = [&](int c) { return c <= 32 || (dt == DType::F32 && c > 64 && c <= 96); };
+    p.wo = narrow(g.c_out) ? 1 : 2;
+    p.wc = narrow(g.c_in) ? 1 : 2;
     p.o_tiles = (g.c_out + 32 * p.wo - 1) / (32 * p.wo);
     p.c_tiles = (g.c_in + 32 * p.wc - 1) / (32 * p.wc);
     p.taps = g.k_h * g.k_w;
@@ -683,7 +693,17 @@ WPlan wgrad_plan(const ConvGeom &g)
     const int64_t per_split_pass = int64_t(p.o_tiles) * p.c_tiles * p.taps;
     // about two work-groups per compute unit, each at least a few chunks long
     int64_t splits = (512 + per_split_pass - 1) / per_split_pass;
-    const int64_t max_splits = (pixels + 2 * kChunk - 1) / (2 * kChunk);
+    // (two chunks at least; eight, where the partials of more would pass
+    // kPartBytes and the loads need no hiding: 64 -> 96, 3x3 on 2 x 28 x 28, 17
+    // slices of 0.9 MB 22.0 us, 7 slices 17.3; 40 -> 24, 0.14 MB: 11.2 and 13.8;
+    // 87 -> 92, element loads: 40 and 56)
+    constexpr int64_t kPartBytes = int64_t(8) << 20;
+    const int64_t dw_bytes = int64_t(p.taps) * 4 * g.c_out * g.c_in * int64_t(sizeof(float));
+    const bool whole = g.c_in % 8 == 0 && g.c_out % 8 == 0;
+    auto slices_of = [&](int chunks) { return (pixels + chunks * kChunk - 1) / (chunks * kChunk); };
+    int64_t max_splits = slices_of(2);
+    if (dt == DType::BF16 && whole)
+        max_splits = std::min(max_splits, std::max(slices_of(8), kPartBytes / dw_bytes));
     if (splits > max_splits)
         splits = max_splits;
     if (splits < 1)
@@ -702,11 +722,11 @@ size_t qconv2d_wgrad_work_bytes(const ConvGeom &g, DType dt)
 {
     // Enough for every smaller batch of the layer too, so that one that has run
     // can be captured with fewer images: a row plan's room also where only its
-    // 32-bit spans refused it.
+    // 32-bit spans refused it, and the tiles' where fewer pixels go to them.
     const WgradRows r = qconv2d_wgrad_rows_plan(g, dt);
     const size_t dw = size_t(g.k_h) * g.k_w * g.c_out * g.c_in * sizeof(float);
     const size_t rows = size_t(r.most_splits) * r.segs * (r.fold ? 4 : 16) * dw;
-    const size_t tiles = r.takes ? 0 : size_t(wgrad_plan(g).most_splits) * 4 * dw;
+    const size_t tiles = size_t(wgrad_plan(g, dt).most_splits) * 4 * dw;
     const size_t b_part = size_t(kBiasBlocks) * 4 * g.c_out * sizeof(float);
     return std::max(std::max(rows, tiles), b_part);
 }
@@ -723,7 +743,7 @@ hipError_t qconv2d_backward_weight_run(const ConvGeom &g, DType dt, const void *
     if (r.takes) {
         e = qconv2d_wgrad_rows_run(r, g, dt, x, dy, part, stream, sep);
     } else {
-        const WPlan p = wgrad_plan(g);
+        const WPlan p = wgrad_plan(g, dt);
         slices = p.splits;
         WArgs a;
         a.x = x;
@@ -783,25 +803,42 @@ hipError_t qconv2d_backward_weight_run(const ConvGeom &g, DType dt, const void *
     }
     if (e != hipSuccess)
         return e;
+    // as many threads to an output as its slices keep busy (70 -> 70, 25 taps, dense
+    // in 2 slices, whole call: 74.3 us with sixteen, 62.7 with one)
     const int64_t outs = int64_t(4) * g.c_out * g.c_in * taps;
+    using One = std::integral_constant<int, 1>;
+    using Four = std::integral_constant<int, 4>;
+    using Sixteen = std::integral_constant<int, 16>;
     if (r.takes && !r.fold) {
-        hipLaunchKernelGGL(qconv2d_wgrad_reduce_dense, dim3(unsigned((outs + 15) / 16)), dim3(kThreads), 0, stream,
-                           (const float *)part, slices, taps, g.c_out, g.c_in, sep ? 1 : 0, dw_r, dw_i, dw_j, dw_k);
-    } else {
-        // as many threads to an output as the slices keep busy
         auto reduce = [&](auto sgc) {
-            constexpr int SG = decltype(sgc)::value;
-            const int64_t per_block = kThreads / SG * 4;
-            hipLaunchKernelGGL((qconv2d_wgrad_reduce<SG>), dim3(unsigned((outs + per_block - 1) / per_block)),
-                               dim3(kThreads), 0, stream, (const float *)part, slices, taps, g.c_out * g.c_in, dw_r,
-                               dw_i, dw_j, dw_k);
+            constexpr int SG = decltype(sgc)::value, per_block = kThreads / SG;
+            hipLaunchKernelGGL((qconv2d_wgrad_reduce_dense<SG>), dim3(unsigned((outs + per_block - 1) / per_block)),
+                               dim3(kThreads), 0, stream, (const float *)part, slices, taps, g.c_out, g.c_in,
+                               sep ? 1 : 0, dw_r, dw_i, dw_j, dw_k);
         };
         if (slices >= 12)
-            reduce(std::integral_constant<int, 16>{});
+            reduce(Sixteen{});
         else if (slices >= 3)
-            reduce(std::integral_constant<int, 4>{});
+            reduce(Four{});
         else
-            reduce(std::integral_constant<int, 1>{});
+            reduce(One{});
+    } else {
+        auto reduce = [&](auto sgc, auto uc) {
+            constexpr int SG = decltype(sgc)::value, U = decltype(uc)::value;
+            const int64_t blocks = (outs + kThreads / SG * 4 - 1) / (kThreads / SG * 4);
+            const int seg = int((blocks + 4 * taps - 1) / (4 * taps));
+            hipLaunchKernelGGL((qconv2d_wgrad_reduce<SG, U>), dim3(unsigned(4 * taps) * unsigned(seg)),
+                               dim3(kThreads), 0, stream, (const float *)part, slices, taps, g.c_out * g.c_in, seg,
+                               dw_r, dw_i, dw_j, dw_k);
+        };
+        if (slices >= 64)
+            reduce(Sixteen{}, std::integral_constant<int, 8>{});
+        else if (slices >= 12)
+            reduce(Sixteen{}, Four{});
+        else if (slices >= 3)
+            reduce(Four{}, std::integral_constant<int, 3>{});
+        else
+            reduce(One{}, Four{});
     }
     e = hipGetLastError();
     if (e != hipSuccess || db == nullptr)

@@ -549,8 +549,14 @@ WgradRows qconv2d_wgrad_rows_plan(const ConvGeom &g, DType dt)
     const bool whole = g.c_in % (16 / es) == 0 && g.c_out % (16 / es) == 0;
     const bool few = int64_t(p.o_tiles) * p.c_tiles <= 25;
     const bool f32 = dt == DType::F32;
-    if (!(p.fold || (!whole && few && (!f32 || 10 * rows_work <= 9 * other_work)) ||
-          (f32 && 2 * rows_work <= other_work)))
+    //  - kernel widths that are no multiple of three leave a tap group part
+    //    empty: fp32 then at half the work only (66 -> 40, 5x5 on 10 x 24 x 24:
+    //    849 / 563; 70 -> 70: 1288 / 1016), and bf16 with more than 9 taps from
+    //    1024 pixels on (70 -> 70, 5x5, 640 pixels: 62 / 55).
+    const bool filled = g.k_w % 3 == 0 || g.k_w == 1;
+    const bool odd = !whole && few &&
+                     (f32 ? filled && 10 * rows_work <= 9 * other_work : g.k_h * g.k_w <= 9 || g.m() >= 1024);
+    if (!(p.fold || odd || (f32 && 2 * rows_work <= other_work)))
         return p;
     p.kw = g.k_w == 1 ? 1 : 3;
     p.kx_groups = ceil_div(g.k_w, p.kw);

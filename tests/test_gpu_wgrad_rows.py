@@ -50,6 +50,15 @@ SHAPES = [
     (1, 64, 32, 7, 9, 3, 1, 1, 1),
     (1, 72, 40, 6, 6, 1, 1, 0, 1),
     (3, 32, 32, 13, 11, 3, 1, 1, 1),
+    # slices around the reduction's counts of threads (1, 4, 16, eight loads
+    # each) in whole and odd runs; dense slices of few and many pixels
+    (1, 72, 64, 5, 5, 3, 1, 1, 1),
+    (2, 70, 34, 12, 12, 5, 3, 2, 1),
+    (4, 40, 24, 28, 28, 1, 1, 0, 1),
+    (2, 33, 43, 40, 41, 1, 1, 0, 1),
+    (2, 88, 96, 16, 17, 3, 1, 1, 1),
+    (1, 66, 40, 14, 15, 5, 1, 2, 1),
+    (1, 18, 50, 40, 30, 5, 1, 2, 1),
 ]
 
 
