@@ -15,8 +15,8 @@ constexpr unsigned kWgradSepNeg = (1u << 1) | (1u << 2) | (1u << 3) | (1u << 7) 
 
 // The row kernel (several taps of a kernel row per work-group): whether it
 // takes the layer, and how it splits it.  It writes splits * segs slices of
-// partial sums, [slice][taps][4][c_out][c_in] with `fold`, else the product of
-// all component pairs [slice][taps][4 c_out][4 c_in].
+// partial sums, [slice][taps][4][c_out][c_in] in fp64 with `fold`, else the
+// product of all component pairs [slice][taps][4 c_out][4 c_in] in fp32.
 struct WgradRows {
     bool takes, fold;
     int wo, wc, kw;  // blocks of 32 per tile, taps of a work-group

@@ -458,13 +458,16 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
 // 64 channels, 9 taps, 57 slices) took 17.4 us, now 7.5; 57 slices of a
 // 16-channel layer 21.3, now 4.2.  Four-byte loads of a run of outputs of one tap
 // and m instead: 13.2 and 11.1.
-template <int SG, int U>
-__global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce(const float *__restrict__ part, int slices, int taps,
+template <typename P, int SG, int U>
+__global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce(const P *__restrict__ part, int slices, int taps,
                                                                  int oc_n, int seg, float *__restrict__ dw0,
                                                                  float *__restrict__ dw1, float *__restrict__ dw2,
                                                                  float *__restrict__ dw3)
 {
     constexpr int QUADS = kThreads / SG;  // output quads per block
+    struct alignas(16) Quad {
+        P e[4];
+    };
     __shared__ double red[SG > 1 ? SG : 1][QUADS * 4];
     const int ql = threadIdx.x % QUADS, sg = threadIdx.x / QUADS;
     const int64_t n = int64_t(4) * taps * oc_n;  // a multiple of 4
@@ -474,19 +477,18 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad_reduce(const float *__
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     if (f0 < n) {
         for (int sp = sg; sp < slices; sp += SG * U) {
-            float4 v[U];
+            Quad v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int at = sp + u * SG;
-                v[u] = *reinterpret_cast<const float4 *>(part + int64_t(at < slices ? at : sp) * n + f0);
+                v[u] = *reinterpret_cast<const Quad *>(part + int64_t(at < slices ? at : sp) * n + f0);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (sp + u * SG < slices) {
-                    s[0] += double(v[u].x);
-                    s[1] += double(v[u].y);
-                    s[2] += double(v[u].z);
-                    s[3] += double(v[u].w);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        s[e] += double(v[u].e[e]);
                 }
         }
     }
@@ -725,7 +727,7 @@ size_t qconv2d_wgrad_work_bytes(const ConvGeom &g, DType dt)
     // 32-bit spans refused it, and the tiles' where fewer pixels go to them.
     const WgradRows r = qconv2d_wgrad_rows_plan(g, dt);
     const size_t dw = size_t(g.k_h) * g.k_w * g.c_out * g.c_in * sizeof(float);
-    const size_t rows = size_t(r.most_splits) * r.segs * (r.fold ? 4 : 16) * dw;
+    const size_t rows = size_t(r.most_splits) * r.segs * (r.fold ? 4 * 2 : 16) * dw;  // (fp64 with fold)
     const size_t tiles = size_t(wgrad_plan(g, dt).most_splits) * 4 * dw;
     const size_t b_part = size_t(kBiasBlocks) * 4 * g.c_out * sizeof(float);
     return std::max(std::max(rows, tiles), b_part);
@@ -823,14 +825,16 @@ hipError_t qconv2d_backward_weight_run(const ConvGeom &g, DType dt, const void *
         else
             reduce(One{});
     } else {
-        auto reduce = [&](auto sgc, auto uc) {
+        auto launch = [&](auto of, auto sgc, auto uc) {
+            using P = decltype(of);
             constexpr int SG = decltype(sgc)::value, U = decltype(uc)::value;
             const int64_t blocks = (outs + kThreads / SG * 4 - 1) / (kThreads / SG * 4);
             const int seg = int((blocks + 4 * taps - 1) / (4 * taps));
-            hipLaunchKernelGGL((qconv2d_wgrad_reduce<SG, U>), dim3(unsigned(4 * taps) * unsigned(seg)),
-                               dim3(kThreads), 0, stream, (const float *)part, slices, taps, g.c_out * g.c_in, seg,
-                               dw_r, dw_i, dw_j, dw_k);
+            hipLaunchKernelGGL((qconv2d_wgrad_reduce<P, SG, U>), dim3(unsigned(4 * taps) * unsigned(seg)),
+                               dim3(kThreads), 0, stream, reinterpret_cast<const P *>(part), slices, taps,
+                               g.c_out * g.c_in, seg, dw_r, dw_i, dw_j, dw_k);
         };
+        auto reduce = [&](auto sgc, auto uc) { r.takes ? launch(double{}, sgc, uc) : launch(float{}, sgc, uc); };
         if (slices >= 64)
             reduce(Sixteen{}, std::integral_constant<int, 8>{});
         else if (slices >= 12)

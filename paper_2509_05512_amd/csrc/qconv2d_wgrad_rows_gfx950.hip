@@ -25,13 +25,13 @@
 // The 4*C reals of a pixel are one row of the product (dense): G holds all
 // sixteen component pairs, the same useful work as adding them into four dW_m
 // by component, without padding each component to a tile.  For a layer whose
-// rows fit one tile the signed sum over p that makes dW_m is taken in LDS
-// before anything is written.  The rows are multiples of 8 bytes (bf16) or
+// rows fit one tile the signed sum over p that makes dW_m is taken from LDS, in
+// fp64, and its partials written as such.  The rows are multiples of 8 bytes (bf16) or
 // 16 (fp32) whatever C is, so odd channel counts load in whole pieces too.
 //
 // The WK waves that share a block split the chunk's K steps and are added
-// at the end in wave order; slices of the rows write fp32 partials which
-// qconv2d_wgrad_reduce adds in slice order in fp64: deterministic.
+// at the end in wave order; slices of the rows write partials (fp32, fp64 once
+// summed over p) which the reduction adds in slice order in fp64: deterministic.
 //
 // Bound by staging: each tensor is read k_h times from L2, once from memory.
 // A form with four components per row and four dW_m accumulators per tap
@@ -442,16 +442,16 @@ __global__ __launch_bounds__(kThreads, 2) void qconv2d_wgrad_rows(RArgs a)
             }
             __syncthreads();
             const int oc = a.q_out * a.q_in;
-            float *dst = a.part + (size_t(grp) * taps + tap0 + t) * 4 * oc;
+            double *dst = reinterpret_cast<double *>(a.part) + (size_t(grp) * taps + tap0 + t) * 4 * oc;
             if (tid < oc) {  // at most 16 x 16
                 const int oo = quot(tid, a.magic_c), c = tid - oo * a.q_in;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
-                    float s = 0.0f;
+                    double s = 0.0;
 #pragma unroll
                     for (int p = 0; p < 4; ++p) {
                         const int q = a.sep ? m : p ^ m;
-                        const float v = gt[(p * a.q_out + oo) * LD + q * a.q_in + c];
+                        const double v = double(gt[(p * a.q_out + oo) * LD + q * a.q_in + c]);
                         s = (((a.sep ? kWgradSepNeg : kWgradNeg) >> (4 * p + q)) & 1u) ? s - v : s + v;
                     }
                     dst[m * oc + tid] = s;

@@ -101,3 +101,22 @@ def test_infinite_pixel_stays_out_of_other_taps(dtype):
     got = np.stack([f64(t) for t in dws])
     assert_close(got[..., 0], ref[..., 0], torch.float32, "tap 0")
     assert not np.isfinite(got[..., 1]).any()
+
+
+@pytest.mark.parametrize("sep", [False, True], ids=["hamilton", "separable"])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("c,o", [(1, 1), (5, 16), (16, 9), (13, 21)])
+def test_component_sum_is_taken_in_fp64(c, o, dtype, sep):
+    """Products of component pairs that are exact in fp32 and whose signed sum
+    cancels: 2^24 + 1 - 2^24 in eq. 6's and eq. 7's order.  The sum is 1."""
+    say(f"weight gradient cancellation {dtype} {c}->{o} sep={sep}")
+    dt = DT[dtype]
+    x, dy = torch.zeros(1, 4, c, 1, 1), torch.zeros(1, 4, o, 1, 1)
+    for q, v in enumerate((4096, 0, 0, 0) if sep else (4096, 1, 4096, 0)):
+        x[:, q] = v
+    for p, v in enumerate((4096, 2.0 ** -12, -4096, 0) if sep else (4096, 1, -4096, 0)):
+        dy[:, p] = v
+    fn = quan.quan_qconv2d_separable_backward_weight if sep else quan.quan_qconv2d_backward_weight
+    dws, _ = fn(quan.to_device_layout(x.to(dt).cuda()), quan.to_device_layout(dy.to(dt).cuda()), (1, 1), with_bias=False)
+    torch.cuda.synchronize()
+    assert torch.equal(dws[0].cpu(), torch.ones(o, c, 1, 1))
