@@ -2462,10 +2462,11 @@ hipError_t pad_channels(const ConvGeom &g, DType dt, const void *x, void *pad, h
 // channels) pad later.  The constants follow from element loads / pad, us:
 //  - 1x1, 32 x 112 x 112 -> 16 bf16: 3 channels 36 / 43, 9: 43 / 45, 12: 50 / 44;
 //    64 x 56 x 56 -> 32: 5: 25 / 28, 12: 28 / 34, 18 (two stages): 37 / 35, 28: 45
-//    / 39; 16 x 56 x 56 -> 16: 18: 14 / 18, 60: 23 / 27, 100: 42 / 33; the tile of 64
-//    output channels, 8 x 112 x 112 -> 128: 7: 41 / 35;
-//  - 3x3: one channel, 1 x 32 x 32 -> 16: 17 / 12, 8 x 64 x 64: 17 / 13, 64 x 224 x 224: 1084 / 485; 12
-//    channels, 32 x 112 x 112: 236 / 78;
+//    / 39; 16 x 56 x 56 -> 16: 18: 14 / 18, 60: 23 / 27, 100: 42 / 33; 20 x 40 x 40 ->
+//    13: 92: 24 / 28; the tile of 64 output channels, 8 x 112 x 112 -> 128: 7: 41
+//    / 35;
+//  - 3x3: one channel, 1 x 32 x 32 -> 16: 17 / 12, 8 x 64 x 64: 17 / 13, 64 x 224
+//    x 224: 1084 / 485; 12 channels, 32 x 112 x 112: 236 / 78;
 //  - fp32 (tiles of 64 pixels, four work-groups a compute unit): 1x1, 16 x 56 x
 //    56 -> 16: 9: 17 / 23, 33: 30 / 36; 64 x 56 x 56 -> 32: 9: 80 / 71, 33: 174 /
 //    145; 3x3, one channel, 32 x 112 x 112: 222 / 189.
@@ -2479,10 +2480,13 @@ bool pad_pays(const ConvGeom &g, DType dt, int phases)
     const double ch = double(g.c_in) / blocks;  // of a stage
     const int64_t stages = int64_t(g.k_h) * g.k_w * blocks;
     const int64_t tiles = (g.m() + bm - 1) / bm * ((g.c_out + bnc - 1) / bnc);
-    const double rounds = std::max(1.0, double(tiles) / device_cus() + 0.5);
+    const double share = double(tiles) / device_cus();
+    const double rounds = share <= 1.0 ? 1.0 : share + 0.5;
     const bool one = stages == 1;
-    const double stage_us = f32 ? (one ? 0.1 + 0.05 * ch : 0.3 + 0.025 * ch)
-                                : (one ? 0.3 + 0.12 * ch : 0.6 + 0.067 * ch) * (bnc == 64 ? 1.4 : 1.0);
+    double stage_us = f32 ? (one ? 0.1 + 0.05 * ch : 0.3 + 0.025 * ch)
+                          : (one ? 0.3 + 0.12 * ch : 0.6 + 0.067 * ch) * (bnc == 64 ? 1.4 : 1.0);
+    if (!f32 && !one && share <= 1.0)
+        stage_us = std::max(stage_us, 1.05);  // (alone on its compute unit, a work-group waits out each load)
     const double bytes = double(g.n) * g.h * g.w * 4 * (g.c_in + padded_channels(g.c_in, dt)) * (f32 ? 4 : 2);
     return double(stages) * rounds / phases * stage_us > (one ? 7.0 : 5.7) + bytes / 6.6e6;
 }

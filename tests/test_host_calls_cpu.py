@@ -302,6 +302,7 @@ def test_padded_copy_is_made_where_it_pays(so):
     no = [((32, 3, 112, 112, 16, 1, 1, 0), BF16), ((32, 9, 112, 112, 16, 1, 1, 0), BF16),
           ((64, 5, 56, 56, 32, 1, 1, 0), BF16), ((64, 12, 56, 56, 32, 1, 1, 0), BF16),
           ((16, 18, 56, 56, 16, 1, 1, 0), BF16), ((16, 60, 56, 56, 16, 1, 1, 0), BF16),
+          ((20, 92, 40, 40, 13, 1, 1, 0), BF16), ((8, 100, 56, 56, 16, 1, 1, 0), BF16),
           ((16, 9, 56, 56, 16, 1, 1, 0), F32), ((16, 33, 56, 56, 16, 1, 1, 0), F32),
           ((32, 1, 112, 112, 16, 1, 1, 0), F32)]
     yes = [((32, 12, 112, 112, 16, 1, 1, 0), BF16), ((64, 28, 56, 56, 32, 1, 1, 0), BF16),
