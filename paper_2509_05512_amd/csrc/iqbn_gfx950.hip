@@ -31,6 +31,7 @@
 // normalization then costs one read and one write of the tensor.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -49,9 +50,10 @@ constexpr int kStreamBlocks = 1024;
 // in flight, so that small tensors still spread over the compute units
 // (measured against 24 rows: the input-gradient pass of 131072 rows of 64 bf16
 // columns, 171 -> 1024 blocks, 19.9 -> 12.9 us, of 12544 x 128 fp32, 66 -> 392
-// blocks, 15.2 -> 6.4; the gradient reductions 15.2 -> 12.7 and 9.8 -> 5.8).  A pass that keeps partials goes
-// below kPartialRowsPerThread only while they stay under kPartialBytes, so
-// wide rows need no more scratch than they do at that many rows.
+// blocks, 15.2 -> 6.4; the gradient reductions 15.2 -> 12.7 and 9.8 -> 5.8).  A
+// pass that keeps partials goes below kPartialRowsPerThread only while they
+// stay under kPartialBytes, so wide rows need no more scratch than they do at
+// that many rows.
 constexpr int kMinRowsPerThread = 4;
 constexpr int kPartialRowsPerThread = 24;
 constexpr int64_t kPartialBytes = int64_t(2) << 20;
@@ -89,9 +91,10 @@ struct Layout {
     int64_t rows_per_block;  // contiguous rows of one block
 };
 
-// Layout of a pass that writes partials, or (partials false) of an
-// element-wise one.
-Layout make_layout(int64_t pixels, int c, int vw, bool partials = true)
+// What a pass keeps: the statistics' or the gradient's partials, or none.
+enum class Pass : int { Stats, Gradient, Elements };
+
+Layout make_layout(int64_t pixels, int c, int vw, Pass pass)
 {
     Layout l;
     l.pixels = pixels;
@@ -105,17 +108,26 @@ Layout make_layout(int64_t pixels, int c, int vw, bool partials = true)
         const int64_t rows = int64_t(l.rpi) * rows_per_thread;
         return (pixels + rows - 1) / rows;
     };
+    const int64_t few = blocks_of(kPartialRowsPerThread);
     int64_t want = blocks_of(kMinRowsPerThread);
-    if (partials) {
-        const int64_t room = kPartialBytes / (int64_t(2) * l.row_len * sizeof(float));
-        const int64_t few = blocks_of(kPartialRowsPerThread);
-        // (rows read element by element, few of them side by side: the partials
-        // of short row ranges cost as much as the rows, 1024 rows of 924 bf16
+    auto at_most = [&](int64_t blocks) { want = std::min(want, std::max(few, blocks)); };
+    if (pass == Pass::Elements) {
+        // enough blocks over all column groups: 11135 rows of 1604 bf16 columns
+        // (seven groups) 13.6 us in 464 x 7 blocks, 16.2 in 1013 x 7
+        at_most(kStreamBlocks / l.col_groups);
+    } else {
+        at_most(kPartialBytes / (int64_t(2) * l.row_len * sizeof(float)));
+        // one stream to read: a block per compute unit (36469 rows of 96 fp32
+        // columns 4.6 us in 152 blocks, 5.4 in 507)
+        if (pass == Pass::Stats)
+            at_most(256 / l.col_groups);
+        // rows read element by element, few of them side by side: the partials
+        // of short row ranges cost as much as the rows (1024 rows of 924 bf16
         // columns, gradient, 11.9 us at 24 rows per thread, 15.0 at 4)
-        want = vw == 1 && l.rpi < 8 ? few : want < room ? want : room;
-        want = want > few ? want : few;
+        if (vw == 1 && l.rpi < 8)
+            want = few;
     }
-    const int64_t cap = partials ? kMaxBlocks : kStreamBlocks;  // per column group
+    const int64_t cap = pass == Pass::Elements ? kStreamBlocks : kMaxBlocks;  // per column group
     if (want > cap)
         want = cap;
     if (want < 1)
@@ -1249,8 +1261,13 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_reduce(const T *__restrict_
     const int rl = tid / l.cg;
     const int col = blockIdx.y * l.cg + cl;
     const bool active = rl < l.rpi && col < l.chunks;
-    // (rows dealt round-robin over the blocks, as in iqbn_bwd_apply)
-    const int64_t r1 = l.pixels;
+    // With sign bits rows are dealt round-robin over the blocks, as in
+    // iqbn_bwd_apply, which then starts where this pass ended; else a block takes
+    // a range of rows and the next pass goes forward (57582 rows of 552 fp32
+    // columns with ReLU, both passes: 217 us dealt and backward, 182 so).
+    constexpr bool dealt = RELU && VW == 8;
+    const int64_t r0 = dealt ? int64_t(blockIdx.x) * l.rpi : int64_t(blockIdx.x) * l.rows_per_block;
+    const int64_t r1 = dealt || r0 + l.rows_per_block > l.pixels ? l.pixels : r0 + l.rows_per_block;
     float s1[VW], s2[VW];
 #pragma unroll
     for (int e = 0; e < VW; ++e)
@@ -1258,7 +1275,7 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_reduce(const T *__restrict_
     if (active) {
         float mu[VW], inv[VW];
         load_col_params<T, VW>(mean, var, eps, col, mu, inv);
-        const int64_t step = int64_t(l.rpi) * l.blocks;
+        const int64_t step = dealt ? int64_t(l.rpi) * l.blocks : l.rpi;
         auto add = [&](const Vec<T, VW> &xv, const Vec<T, VW> &gv, const Vec<T, VW> &yv, int64_t r) {
             unsigned bits = 0;
 #pragma unroll
@@ -1277,7 +1294,7 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_reduce(const T *__restrict_
                 if (keep)
                     mask[r * l.chunks + col] = (unsigned char)bits;
         };
-        int64_t r = int64_t(blockIdx.x) * l.rpi + rl;
+        int64_t r = r0 + rl;
         // four rows in flight per thread
         for (; r + 3 * step < r1; r += 4 * step) {
             Vec<T, VW> xv[4], gv[4], yv[4];
@@ -1289,6 +1306,9 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_reduce(const T *__restrict_
                 if (RELU)
                     yv[u] = *reinterpret_cast<const Vec<T, VW> *>(y + off);
             }
+            // (all loads first: the scheduler, short of registers for their
+            // addresses, had the last of them wait one by one)
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 add(xv[u], gv[u], yv[u], r + u * step);
@@ -1392,10 +1412,12 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_apply(const T *__restrict__
     // -> 46.0 us on 200704 x 256 bf16 without ReLU against contiguous row ranges per
     // work-group (which the two-stream passes keep: there round-robin rows
     // were 1-3 us slower).
-    // Taken from the last row down: the reduction has read the last rows most
-    // recently, so more of them are still in the last-level cache (that
-    // size: 70 -> 61 us without the sign bits, 56.5 -> 54.6 with them).
+    // With sign bits they are taken from the last row down: the reduction has
+    // read the last rows most recently, so more of them are still in the
+    // last-level cache (that size: 56.5 -> 54.6 us).
+    constexpr bool back = RELU && VW == 8;
     const int64_t r1 = l.pixels, last = r1 - 1;
+    auto row = [&](int64_t i) { return back ? last - i : i; };
     struct Sign {
         Vec<T, VW> y;
         unsigned bits;
@@ -1429,19 +1451,20 @@ __global__ __launch_bounds__(kThreads) void iqbn_bwd_apply(const T *__restrict__
         Sign sv[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int64_t off = (last - r - u * step) * l.row_len + col * VW;
+            const int64_t off = row(r + u * step) * l.row_len + col * VW;
             xv[u] = *reinterpret_cast<const Vec<T, VW> *>(x + off);
             gv[u] = *reinterpret_cast<const Vec<T, VW> *>(dout + off);
-            load_sign(last - r - u * step, sv[u]);
+            load_sign(row(r + u * step), sv[u]);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            store_stream(reinterpret_cast<Vec<T, VW> *>(dx + (last - r - u * step) * l.row_len + col * VW), grad(xv[u], gv[u], sv[u]));
+            store_stream(reinterpret_cast<Vec<T, VW> *>(dx + row(r + u * step) * l.row_len + col * VW),
+                         grad(xv[u], gv[u], sv[u]));
     }
     for (; r < r1; r += step) {
-        const int64_t off = (last - r) * l.row_len + col * VW;
+        const int64_t off = row(r) * l.row_len + col * VW;
         Sign sv;
-        load_sign(last - r, sv);
+        load_sign(row(r), sv);
         *reinterpret_cast<Vec<T, VW> *>(dx + off) =
             grad(*reinterpret_cast<const Vec<T, VW> *>(x + off), *reinterpret_cast<const Vec<T, VW> *>(dout + off), sv);
     }
@@ -1545,7 +1568,7 @@ hipError_t launch_backward(const void *x, const void *dout, const void *y, const
                                gt, yt, static_cast<T *>(dx), sg, a);
         return hipGetLastError();
     }
-    const Layout l = make_layout(pixels, c, VW);
+    const Layout l = make_layout(pixels, c, VW, Pass::Gradient);
     float *part = static_cast<float *>(work);
     float *coef = part + size_t(l.blocks) * 2 * l.row_len;
     const dim3 grid(l.blocks, l.col_groups);
@@ -1558,7 +1581,7 @@ hipError_t launch_backward(const void *x, const void *dout, const void *y, const
     const int fin_blocks = (l.row_len + kThreads / 64 - 1) / (kThreads / 64);
     hipLaunchKernelGGL(iqbn_bwd_finalize, dim3(fin_blocks), dim3(kThreads), 0, stream, l, (const float *)part,
                        var, gamma, eps, dgamma, dbeta, coef);
-    const Layout ls = make_layout(pixels, c, VW, false);
+    const Layout ls = make_layout(pixels, c, VW, Pass::Elements);
     const dim3 sgrid(ls.blocks, ls.col_groups);
     if constexpr (VW == 8)
         if (y != nullptr && mask != nullptr) {
@@ -1718,14 +1741,14 @@ hipError_t launch_all(const void *x, const float *gamma, const float *beta, floa
                                static_cast<T *>(out), l, a);
         return hipGetLastError();
     }
-    const Layout l = make_layout(pixels, c, VW);
+    const Layout l = make_layout(pixels, c, VW, Pass::Stats);
     float *affine = part + size_t(l.blocks) * 2 * l.row_len;
     const dim3 grid(l.blocks, l.col_groups);
     hipLaunchKernelGGL((iqbn_stats<T, VW>), grid, dim3(kThreads), 0, stream, xt, l, part, nullptr);
     const int fin_blocks = (l.row_len + kThreads / 64 - 1) / (kThreads / 64);
     hipLaunchKernelGGL((iqbn_finalize<T>), dim3(fin_blocks), dim3(kThreads), 0, stream, xt, l, part,
                        gamma, beta, eps, mean, var, affine);
-    const Layout ls = make_layout(pixels, c, VW, false);
+    const Layout ls = make_layout(pixels, c, VW, Pass::Elements);
     const dim3 sgrid(ls.blocks, ls.col_groups);
     if (relu)
         hipLaunchKernelGGL((iqbn_affine<T, VW, true>), sgrid, dim3(kThreads), 0, stream, xt,
@@ -1741,11 +1764,11 @@ hipError_t launch_from_tiles(const float *part, int m_tiles, int tile_rows, cons
                              const float *beta, float eps, bool relu, void *io, float *mean, float *var,
                              int64_t pixels, int c, float *affine, hipStream_t stream)
 {
-    const Layout l = make_layout(pixels, c, VW);
+    const Layout l = make_layout(pixels, c, VW, Pass::Stats);
     hipLaunchKernelGGL(iqbn_finalize_tiles, dim3(l.row_len), dim3(kThreads), 0, stream, part, m_tiles,
                        tile_rows, pixels, l.row_len, gamma, beta, eps, mean, var, affine);
     T *t = static_cast<T *>(io);
-    const Layout ls = make_layout(pixels, c, VW, false);
+    const Layout ls = make_layout(pixels, c, VW, Pass::Elements);
     const dim3 sgrid(ls.blocks, ls.col_groups);
     if (relu)
         hipLaunchKernelGGL((iqbn_affine<T, VW, true>), sgrid, dim3(kThreads), 0, stream, t, t, ls,
@@ -1856,7 +1879,7 @@ size_t iqbn_workspace_bytes(int64_t pixels, int c)
     for (int vw : {1, 4, 8}) {
         if ((4 * c) % vw)
             continue;
-        const Layout l = make_layout(pixels, c, vw);
+        const Layout l = make_layout(pixels, c, vw, Pass::Gradient);  // (no fewer blocks than the statistics)
         const size_t b = (size_t(l.blocks) * 2 + 3) * size_t(l.row_len) * sizeof(float);
         if (b > best)
             best = b;

@@ -375,3 +375,14 @@ def test_partials_of_rows_read_by_element(so):
     for (call, args, _), (names, _) in zip(cases, host_calls.in_child(_names, so, cases)):
         assert "iqbn_bwd_reduce" in names[0][0]
         assert names[0][1] <= args[3] // 24 + 1, (args, names[0])
+
+
+def test_blocks_of_wide_rows(so):
+    """Passes without partials go to about four blocks per compute unit over all
+    column groups, however many those are; the statistics to one."""
+    cases = [("iqbn_backward", (1, 401, 1, 11135), dict(relu=False)), ("iqbn", (1, 401, 1, 11135), dict()),
+             ("iqbn", (1, 24, 1, 36469), dict(dtype=F32))]
+    (gradient, _), (forward, _), (narrow, _) = host_calls.in_child(_names, so, cases)
+    assert "iqbn_bwd_apply" in gradient[-1][0] and gradient[-1][1] <= 11135 // 24 + 1
+    assert "iqbn_affine" in forward[-1][0] and forward[-1][1] <= 11135 // 24 + 1
+    assert "iqbn_stats" in narrow[0][0] and narrow[0][1] <= 256
