@@ -306,8 +306,8 @@ hipError_t launch_stem(StemArgs a, int64_t n, hipStream_t stream)
     // 10.2).  One image of wide rows is left 0.3 to 2.4 us slower than that: a row
     // of 138 pixels is two rounds, the second nearly empty.
     auto rounds_of = [&](int64_t rows) { return (rows * a.w_out + 32 * kStemWaves - 1) / (32 * kStemWaves); };
-    double best = 0.0;
-    int64_t cap = 0;  // work-groups
+    double best = 0.0, costs[kStemMaxBand + 1] = {};
+    int64_t caps[kStemMaxBand + 1] = {};  // work-groups
     for (int band = 1; band <= a.h_out && band <= kStemMaxBand; ++band) {
         const int parts = (a.h_out + band - 1) / band;
         if ((a.h_out + parts - 1) / parts != band)
@@ -324,13 +324,14 @@ hipError_t launch_stem(StemArgs a, int64_t n, hipStream_t stream)
         auto turn = [&](int64_t groups) { return std::max(alone, double((groups + cus - 1) / cus) * shared); };
         const double cost = double(bands / wgs) * turn(wgs) + (bands % wgs ? turn(bands % wgs) : 0.0) +
                             0.1 * NBLK * a.km * std::max(1.0, double(wgs) / cus);
-        // (a taller band shares more input rows)
-        if (band == 1 || cost <= 1.05 * best) {
-            best = band == 1 ? cost : std::min(best, cost);
-            a.band = band;
-            cap = slots;
-        }
+        costs[band] = cost;
+        caps[band] = slots;
+        best = band == 1 ? cost : std::min(best, cost);
     }
+    // (the least band within 4 %: more bands even out better)
+    while (costs[a.band] == 0.0 || costs[a.band] > 1.04 * best)
+        ++a.band;
+    const int64_t cap = caps[a.band];
     a.img_bands = (a.h_out + a.band - 1) / a.band;
     a.bands = int(n * a.img_bands);
     a.patch_w = staged ? int(cols) : 1;
