@@ -338,15 +338,15 @@ def _stem_groups(q, cases):
 
 
 def test_stem_work_groups_have_pixels_for_their_table(so):
-    """Every work-group builds the layer's weight table, so beyond one per compute
-    unit (256), which build theirs side by side, none is launched for a short
+    """Every work-group builds the layer's weight table, so beyond two per compute
+    unit (512), which build theirs side by side, none is launched for a short
     row of a narrow image: 64 output pixels or more each."""
     cases = [(n, h, h, c, k, s) for n in (1, 8, 64) for h in (9, 14, 27, 37, 56, 86, 138, 224) for s in (1, 2)
              for c, k in ((4, 3), (16, 3), (24, 5), (36, 3), (64, 1), (64, 3), (16, 7))]
     for case, groups in zip(cases, host_calls.in_child(_stem_groups, so, cases)):
         n, h, _, c, k, s = case
         pixels = n * ((h - 1) // s + 1) ** 2
-        assert len(groups) == 1 and groups[0] <= max(256, n, pixels / 64), (case, groups)
+        assert len(groups) == 1 and groups[0] <= max(512, n, pixels / 64), (case, groups)
 
 
 # ---- forms by size ----
