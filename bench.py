@@ -21,7 +21,8 @@ Prints ONE JSON line:
   qconv2d      the convolution kernel alone: TFLOP/s and fraction of the bf16
                dense MFMA peak (2516.6 TFLOP/s)
   iqbn         the stand-alone IQBN: GB/s of algorithmic traffic (two reads +
-               one write of the tensor) and fraction of 8 TB/s, cold (input
+               one write of the tensor, also where the one-launch form reads it
+               once: an effective rate) and fraction of 8 TB/s, cold (input
                evicted from the caches first; the headline) and warm (input
                just written by the convolution)
   other_configs  the same figures for the detection pair (3x3 s2 + 1x1) and

@@ -316,24 +316,33 @@ enum quan_stats_mode {
  *   stats   a quan_stats_mode.  QUAN_STATS_EPILOGUE has every output tile's
  *           mean and squared deviations computed in the convolution's
  *           epilogue and merged exactly in fp64 afterwards (normalising then
- *           costs one read and one write of out); tiles that cannot gather
- *           them (fewer than 32 output channels, or c_out not a multiple of
- *           8 for bf16 / 4 for fp32) use the separate pass instead.
+ *           costs one read and one write of out), and the convolution to run
+ *           whole; tiles that cannot gather them (fp32; c_out not a multiple
+ *           of 8) use the separate pass instead.
  *           QUAN_STATS_PASS runs the plain convolution and then
  *           quan_iqbn_forward's normalisation on out: on tensors of up to
- *           32 MiB whose rows hold at least 193 reals (4 c_out), two
- *           launches (statistics, then the normalisation with the finalize
- *           merged in); on other tensors of 16 MiB or more that one
- *           work-group per compute unit can hold (about 100 MB on MI355X),
- *           one launch that reads out once and writes it once; otherwise
- *           three launches that read it twice.
- *           QUAN_STATS_AUTO picks the pass where it takes two launches, or
- *           one launch on a tensor of at least 64 MiB (measured on MI355X:
- *           133.0 against 137.3 us for the 32 x 14 x 14, 256-channel
- *           layer's 12.8 MB; 262.7 against 267.5 us for the 64 x 56 x 56,
- *           64-channel layer's 103 MB; 52 MB layers are faster with the
- *           epilogue), and the epilogue elsewhere.  All modes are
- *           deterministic.
+ *           1024 pixels (128 where 4 c_out reals are no whole 16-byte
+ *           chunks), one launch that holds whole columns, except fp32 ones
+ *           above 4 MiB that the next form takes; on tensors of up to 32 MiB
+ *           whose rows hold at least 193 reals (4 c_out), two launches
+ *           (statistics, then the normalisation with the finalize merged
+ *           in); on other tensors of 16 MiB or more that one work-group per
+ *           compute unit can hold (about 100 MB on MI355X), one launch that
+ *           reads out once and writes it once; otherwise three launches that
+ *           read it twice.
+ *           QUAN_STATS_AUTO picks the pass where it takes whole columns or
+ *           two launches, or one launch on a tensor of at least 64 MiB
+ *           (measured on MI355X: 133.0 against 137.3 us for the 32 x 14 x 14,
+ *           256-channel layer's 12.8 MB; 262.7 against 267.5 us for the 64 x
+ *           56 x 56, 64-channel layer's 103 MB; 52 MB layers are faster with
+ *           the epilogue), and the epilogue elsewhere.  In AUTO and PASS a
+ *           convolution of few tiles and many stages may split its sums over
+ *           K; its statistics then come from the pass.
+ *
+ * All modes are deterministic: the same call gives the same bits, with one
+ * exception shared by every convolution call.  A call captured into a graph
+ * that cannot have the buffer for its partial tiles sums K in one piece, and
+ * so may differ from an eager one in rounding.
  */
 QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const void *bias,
                                        int32_t stride_h, int32_t stride_w,
@@ -358,8 +367,9 @@ QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const 
  * eps) and shift = (bias - mean) * scale + beta formed in fp64 on the
  * device.  running_mean, running_var, gamma, beta are [4, c_out] fp32 device
  * arrays (4-byte aligned) that out may not overlap; every other argument is
- * as in quan_qconv2d_forward_packed.  Uses a small library workspace per
- * (device, stream) for scale and shift.
+ * as in quan_qconv2d_forward_packed.  scale and shift lie in library
+ * workspaces per (device, stream): 8 c_out floats, and tables of as many per
+ * work-group of the convolution, up to 20 MiB.
  */
 QUAN_API int quan_qconv2d_iqbn_inference(const void *x, const void *packed, const void *bias,
                                          int32_t stride_h, int32_t stride_w,

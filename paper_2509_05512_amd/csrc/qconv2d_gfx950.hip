@@ -1942,9 +1942,6 @@ __global__ __launch_bounds__(256) void qconv2d_pack(const T *__restrict__ w0, co
     wp[idx] = v;
 }
 
-// Scatters dY [n][ho][wo][row] into the zero-filled z [n][hz][wz][row] at
-// rows and columns (oy * s_h, ox * s_w): the input of the input-gradient
-// convolution of a strided layer.  One thread per VW elements.
 // The forward pack of bf16 kernels whose input channels come in whole
 // 8-channel octets, TAPS taps: one thread per (channel block, kernel, output
 // row, octet).  The thread's source is 8 x TAPS consecutive elements
@@ -2039,6 +2036,9 @@ __global__ __launch_bounds__(256) void qconv2d_pad_channels(const T *__restrict_
     reinterpret_cast<Chunk *>(out)[idx] = v;
 }
 
+// Scatters dY [n][ho][wo][row] into the zero-filled z [n][hz][wz][row] at
+// rows and columns (oy * s_h, ox * s_w): the input of the input-gradient
+// convolution of a strided and dilated layer.  One thread per VW elements.
 template <typename T, int VW>
 __global__ __launch_bounds__(256) void qconv2d_grad_dilate(const T *__restrict__ dy, T *__restrict__ z, int ho,
                                                            int wo, int hz, int wz, int s_h, int s_w, int row_vecs,
@@ -2385,7 +2385,8 @@ ConvPlan qconv2d_plan(const ConvGeom &g, DType dt, ConvForm form, bool split)
             id = i;
         }
     }
-    // a split of the tile above or of the other one, whichever is faster
+    // a split of the tile above or of the other one, whichever is faster (the
+    // separable form and its input gradient have no kernels for partial tiles)
     int splits = 1;
     if (split && form == ConvForm::Hamilton) {
         double us = split_cost(kKernels[id], m, g.c_out, stages, cus).us;
@@ -2527,6 +2528,9 @@ int64_t fold_groups(const ConvPlan &plan)
 
 // The pointwise kernel and a split's second launch keep the map on chip; wide
 // layers' tables on many work-groups (over 16 MiB) are not worth it: 0 too.
+// Every work-group forms all columns.  Against a launch of its own, bf16 us: 128 x
+// 14 x 14, 256 -> 256, 3x3 446 / 438; 64 x 28 x 28, 256 -> 512, 1x1 260 / 250; 8 x 56 x
+// 56, 16 -> 512, 1x1 55.1 / 53.4; 64 x 7 x 7, 1024 -> 1024, 1x1 109.7 / 111.5.
 size_t qconv2d_fold_bytes(const ConvPlan &plan, int c_out)
 {
     if (plan.pointwise || plan.splits > 1)

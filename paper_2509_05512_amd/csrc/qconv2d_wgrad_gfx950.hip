@@ -7,26 +7,27 @@
 //   dW_m[o][c] = sum_p s(p, p xor m) sum_pix dY[pix][p][o] X[pix + tap][p xor m][c],
 //
 // a GEMM whose reduction dimension is the output pixels (N * Ho * Wo), over
-// both operands stored channels-last.  One work-group takes one tap, a
-// 64 x 64 tile of (output, input) channels and a contiguous slice of the
-// pixels; it stages 32-pixel chunks of dY (all four components) and of the
-// tap-shifted X (zero outside the image) in LDS, bank-conflict free (see
-// kRowBf16) and double-buffered, with the global loads (16-byte buffer loads
-// at 32-bit offsets, zeros past the end, each thread's pixel coordinates
-// advanced incrementally) issued two chunks ahead; its four waves each
-// accumulate the four dW_m of one 32 x 32 (o, c) block, reading the next
-// k-step's fragments while the MFMAs of the current one run, a sign flip
-// being one XOR per fragment dword.  The taps of one (slice, tile) are placed
+// both operands stored channels-last.  One work-group takes one tap, a tile of
+// 32 or 64 output by 32 or 64 input channels and a contiguous slice of the
+// pixels; it stages chunks of 32 pixels (64 on the 32 x 32 bf16 tile) of dY (all
+// four components) and of the tap-shifted X (zero outside the image) in LDS,
+// bank-conflict free (see row_elems) and double-buffered, with the global loads
+// (16-byte buffer loads at 32-bit offsets, zeros past the end, each thread's
+// pixel coordinates advanced incrementally; element by element where channels
+// fill no whole 16-byte chunks) issued two chunks ahead; its four waves each
+// accumulate the four dW_m of one 32 x 32 (o, c) block, on the smaller tiles a
+// share of a chunk's K steps, reading the next k-step's fragments while the
+// MFMAs of the current one run, a sign flip being one XOR per fragment dword.  The taps of one (slice, tile) are placed
 // on one XCD (work-group b runs on XCD b % 8), so the nine reads of a slice
 // of dY and its shifted copies of X share that XCD's L2.  MFMA operands need
 // eight consecutive pixels per lane: bf16 fragments come from the pixel-major
 // rows with two transposing LDS reads (ds_read_b64_tr_b16), fp32 fragments
 // (one pixel per lane) with plain reads.  Slices write fp32 partial sums; a
-// second kernel adds them in slice order in fp64
-// (deterministic) into dW.  Layers of at most 16 channels run the kernel on
-// whole pixel rows (one component of 4*C channels) for the dense product of
-// all sixteen component pairs, and the reduction forms dW from it.  The bias
-// gradient is the column sum of dY.
+// second kernel adds them in slice order in fp64 (deterministic) into dW.
+// Layers of at most 16 channels, and others that it is the faster for, go to
+// the row kernel (qconv2d_wgrad_rows), which leaves either such sums or the
+// dense products of all sixteen component pairs, from which the reduction forms
+// dW.  The bias gradient is the column sum of dY.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -86,29 +87,21 @@ struct Frag<float> {
 // a row of `len` channels starting at src, zeros where `valid` is false or
 // past len.  Branch-free: an invalid lane loads from `safe` (the tensor's
 // first element) and selects zero, so every load of a chunk stays in flight
-// together.  VEC: rows 16-byte aligned and len a multiple of EPC, so a chunk
-// is wholly inside or outside; otherwise element by element.
-template <typename T, bool VEC>
+// together.
+template <typename T>
 __device__ __forceinline__ u32x4 load_chunk(const T *src, bool valid, int ch0, int len, const T *safe)
 {
     constexpr int EPC = 16 / int(sizeof(T));
-    if constexpr (VEC) {
-        const bool ok = valid && ch0 < len;
-        const u32x4 v = *reinterpret_cast<const u32x4 *>(ok ? src + ch0 : safe);
-        const unsigned keep = ok ? 0xffffffffu : 0u;
-        return u32x4{v[0] & keep, v[1] & keep, v[2] & keep, v[3] & keep};
-    } else {
-        T e[EPC];
+    T e[EPC];
 #pragma unroll
-        for (int i = 0; i < EPC; ++i) {
-            const bool ok = valid && ch0 + i < len;
-            const T u = *(ok ? src + ch0 + i : safe);
-            e[i] = ok ? u : T(0);
-        }
-        u32x4 v;
-        __builtin_memcpy(&v, e, 16);
-        return v;
+    for (int i = 0; i < EPC; ++i) {
+        const bool ok = valid && ch0 + i < len;
+        const T u = *(ok ? src + ch0 + i : safe);
+        e[i] = ok ? u : T(0);
     }
+    u32x4 v;
+    __builtin_memcpy(&v, e, 16);
+    return v;
 }
 
 // 16 bytes at byte offset off of the buffer [base, base + bytes); offsets
@@ -214,7 +207,7 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
                 const T *yrow = dy_s + int64_t(yok ? rel : 0) * NC * a.c_out;
 #pragma unroll
                 for (int q = 0; q < NQ[0]; ++q)
-                    st.y[i][q] = load_chunk<T, VEC>(yrow + (qy + QT[0] * q) * a.c_out + o0, yok, cy * EPC, a.c_out - o0, dy);
+                    st.y[i][q] = load_chunk<T>(yrow + (qy + QT[0] * q) * a.c_out + o0, yok, cy * EPC, a.c_out - o0, dy);
             }
         }
 #pragma unroll
@@ -235,7 +228,7 @@ __global__ __launch_bounds__(kThreads) void qconv2d_wgrad(WArgs a)
                 const T *xrow = x_s + ((int64_t(cur_img[i]) * a.h + (xok ? iy : 0)) * a.w + (xok ? ix : 0)) * NC * a.c_in;
 #pragma unroll
                 for (int q = 0; q < NQ[1]; ++q)
-                    st.x[i][q] = load_chunk<T, VEC>(xrow + (qx + QT[1] * q) * a.c_in + c0, xok, cx * EPC, a.c_in - c0, x);
+                    st.x[i][q] = load_chunk<T>(xrow + (qx + QT[1] * q) * a.c_in + c0, xok, cx * EPC, a.c_in - c0, x);
             }
             // next chunk: CH pixels on
             int ox = cur_ox[i] + CH, oy = cur_oy[i], im = cur_img[i];

@@ -656,7 +656,10 @@ QUAN_API int quan_qconv2d_iqbn_forward(const void *x, const void *packed, const 
     // Measured per layer on MI355X: 103 MB tensors (64 x 56 x 56, 64
     // channels) 262.7 us with the pass against 267.5 with the epilogue; 52 MB
     // (16 x 80 x 80, 64 channels, two layers) 162.3 against 160.1; 12.8 MB
-    // (32 x 14 x 14, 256 channels, merged form) 133.0 against 137.3.
+    // (32 x 14 x 14, 256 channels, merged form) 133.0 against 137.3.  Tensors
+    // of at most 1024 pixels, one launch over whole columns: 32 x 32, 32 -> 32, 3x3
+    // 18.8 against 19.5, 8 x 8, 64 -> 64, 1x1 12.9 against 15.7, 4 x 16 x 16, 64 ->
+    // 1024, 1x1 22.3 against 28.4.
     constexpr int64_t kPassMinBytes = int64_t(64) << 20;
     const bool big = pixels * 4 * c_out * int64_t(elem_size(dtype)) >= kPassMinBytes;
     const bool pass = (big && quan::iqbn_one_launch(pixels, c_out, dt)) || quan::iqbn_merged(pixels, c_out, dt);
